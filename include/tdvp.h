@@ -63,7 +63,8 @@ typedef enum {
 /* Precision of the contractions (environments, effective Hamiltonians, MPO
  * application).  Lanczos recurrences, reorthogonalisation, the tridiagonal
  * exponential, QR/SVD/eigh and the stored site tensors are always FP64.
- *   TDVP_FP32            complex64 operands, FP32 MFMA;
+ *   TDVP_FP32            complex64 operands in full (each real number as three
+ *                        BF16 terms, which hold its 24 bits), FP32 accumulation;
  *   TDVP_BF16_FP32ACC    complex64 operands rounded to BF16 (nearest even) as
  *                        they enter the matrix cores, FP32 accumulation;
  *   TDVP_BF16X3_FP32ACC  each FP32 operand split into two BF16 terms

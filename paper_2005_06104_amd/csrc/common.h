@@ -312,8 +312,8 @@ void shift_by_trace(hipStream_t s, void* G, int n, double frac, const void* S = 
 // out[j][m] = Z[m][n-1-j] (complex), Z column-major real n x n
 void zrows_from_real_desc(hipStream_t s, void* out, const double* Z, int n);
 // Arithmetic of the complex64 GEMMs issued from the calling host thread:
-// 0 FP32 MFMA; 1 BF16 inputs (rounded to nearest even), FP32 accumulation;
-// 2 BF16 three-term split x = hi + lo with FP32 accumulation.
+// 0 FP32 (operands as three BF16 terms, exact); 1 BF16 inputs (rounded to
+// nearest even); 2 two BF16 terms x = hi + lo; all with FP32 accumulation.
 void set_float_mode(int mode);
 int float_mode();
 struct FloatModeScope {

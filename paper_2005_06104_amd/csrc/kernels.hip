@@ -1,13 +1,15 @@
 // Device kernels of the GSE-TDVP1 hot path (gfx950 / CDNA4).
 //
-// * zgemm/cgemm: complex GEMM split into real MFMA products.  A complex
-//   product (Ar + i Ai)(Br + i Bi) is three real MFMA accumulations,
-//   Ar Br, Ai Bi and (Ar + Ai)(Br + Bi), combined into Ar Br - Ai Bi and
-//   Ar Bi + Ai Br at the store; operand tiles are de-interleaved into real
+// * FP64 GEMM: complex GEMM split into real MFMA products.  A complex product
+//   (Ar + i Ai)(Br + i Bi) is three real MFMA accumulations, Ar Br, Ai Bi and
+//   (Ar + Ai)(Br + Bi), combined into Ar Br - Ai Bi and Ar Bi + Ai Br at the
+//   store (v_mfma_f64_16x16x4f64); operand tiles are de-interleaved into real
 //   and imaginary planes in LDS.
-//   FP64 uses v_mfma_f64_16x16x4f64, FP32 v_mfma_f32_16x16x4f32 (same lane
-//   layout).  These carry every contraction of the method: effective
-//   Hamiltonians, environments, MPO application, basis extension.
+// * complex64 GEMM: every operand as one, two or three BF16 terms on the BF16
+//   matrix cores, which are sixteen times as fast as the FP32 ones; three
+//   terms hold an FP32 number exactly.
+//   These carry every contraction of the method: effective Hamiltonians,
+//   environments, MPO application, basis extension.
 // * wapply: contraction with the sparse MPO tensor over (MPO index, physical
 //   index), staged through LDS; memory bound.
 // * complex128 vector helpers for the Lanczos recurrence (FP64 always).
@@ -28,19 +30,15 @@ template <> struct VT<float> { using c2 = float2; using acc = f4; };
 __device__ inline d4 mfma(double a, double b, d4 c) {
   return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
 }
-__device__ inline f4 mfma(float a, float b, f4 c) {
-  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-}
 
 // ---------------------------------------------------------------- GEMM
-// Block tile BM x BN complex outputs, BK complex per stage.  FP64: 1024
+// FP64: block tile BM x BN complex outputs, BK complex per stage, 1024
 // threads = 16 waves in a 4 x 4 grid, one 16x16 MFMA tile each (four waves
 // per SIMD keep the long FP64 MFMA pipeline fed while others wait on LDS or
-// the stage barrier); FP32: 256 threads = 4 waves in a 2 x 2 grid, each
-// 32 x 32 outputs = 2 x 2 MFMA tiles, for the real and for the imaginary part.
-constexpr int BM = 64, BN = 64, BK = 16, NT = 256;
+// the stage barrier).
+constexpr int BM = 64, BN = 64, BK = 16;
 constexpr int PAD = 1;
-template <typename T> struct WaveGrid { static constexpr int WM = 2, WN = 2; };
+template <typename T> struct WaveGrid;
 template <> struct WaveGrid<double> { static constexpr int WM = 4, WN = 4; };
 template <typename T> constexpr int gemm_threads() { return WaveGrid<T>::WM * WaveGrid<T>::WN * 64; }
 
@@ -70,6 +68,7 @@ struct TileJob {
   KIter kr;
 };
 
+template <int TM, int TN>
 __device__ inline TileJob tile_job(int M, int N, int K, int S, int Kc, const int4* __restrict__ kit,
                                    const int2* __restrict__ kiv) {
   TileJob j;
@@ -101,19 +100,66 @@ __device__ inline TileJob tile_job(int M, int N, int K, int S, int Kc, const int
   const unsigned tot = gx * gy * gz;
   const unsigned t = (tot % 8u == 0u) ? (lin % 8u) * (tot / 8u) + lin / 8u : lin;
   const unsigned tz = t / (gx * gy), trem = t % (gx * gy);
-  j.m0 = (int)(trem / gx) * BM;
-  j.n0 = (int)(trem % gx) * BN;
+  j.m0 = (int)(trem / gx) * TM;
+  j.n0 = (int)(trem % gx) * TN;
   j.bz = tz / S;
   j.split = tz % S;
   j.r0 = 0;
-  j.r1 = BM;
+  j.r1 = TM;
   j.c0 = 0;
-  j.c1 = BN;
+  j.c1 = TN;
   const int kb = j.split * Kc, ke = min(K, kb + Kc);
   j.kr.iv = nullptr;
   j.kr.n = kb < ke ? 1 : 0;
   j.kr.one = make_int2(kb, ke);
   return j;
+}
+
+// The wave's piece rows ro[i] and columns co[j] (tile offsets) and which of
+// its pieces it computes, on entry by quadrant.  By quadrant, a sub-block
+// covering part of the tile can leave some waves with four pieces and others
+// with none, and the item lasts as long as its busiest wave.  With four waves
+// of 2 x 2 pieces, a block-sparse item whose covered pieces (ni x nj of
+// 16 x 16) number at most four gets one per wave, one at most two pieces wide
+// a row strip per wave, one at most two pieces tall a column strip per wave;
+// larger ones keep the quadrants.
+__device__ inline void deal_pieces(const TileJob& job, bool mapped, int wave, int (&ro)[2], int (&co)[2],
+                                   bool (&pact)[2][2]) {
+  const int pi0 = job.r0 >> 4, pj0 = job.c0 >> 4;
+  const int ni = ((job.r1 + 15) >> 4) - pi0, nj = ((job.c1 + 15) >> 4) - pj0;
+  const int shape = !mapped ? 0 : ni * nj <= 4 ? 1 : nj <= 2 ? 2 : ni <= 2 ? 3 : 0;
+  if (shape == 0) return;
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) pact[i][j] = false;
+  ro[1] = ro[0] = 0;
+  co[1] = co[0] = 0;
+  if (shape == 1) {   // one piece per wave
+    if (wave < ni * nj) {
+      ro[0] = (pi0 + wave / nj) * 16;
+      co[0] = (pj0 + wave % nj) * 16;
+      pact[0][0] = true;
+    }
+  } else if (shape == 2) {   // row strips: row pi0 + wave, nj <= 2 pieces
+    if (wave < ni) {
+      ro[0] = (pi0 + wave) * 16;
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        co[j] = (pj0 + (j < nj ? j : 0)) * 16;
+        pact[0][j] = j < nj;
+      }
+    }
+  } else {   // column strips: column pj0 + wave, ni <= 2 pieces
+    if (wave < nj) {
+      co[0] = (pj0 + wave) * 16;
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        ro[i] = (pi0 + (i < ni ? i : 0)) * 16;
+        pact[i][0] = i < ni;
+      }
+    }
+  }
 }
 
 template <typename T, bool TA, bool CA, bool TB, bool CB, int TAG>
@@ -134,7 +180,7 @@ __global__ __launch_bounds__(gemm_threads<T>()) void gemm_kernel(int M, int N, i
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / WN, wn = wave % WN;
-  const TileJob job = tile_job(M, N, K, S, Kc, kit, kiv);
+  const TileJob job = tile_job<BM, BN>(M, N, K, S, Kc, kit, kiv);
   const int m0 = job.m0, n0 = job.n0, split = job.split;
   const long long bz = job.bz;
   const c2* Ab = reinterpret_cast<const c2*>(A) + bz * sa;
@@ -221,14 +267,6 @@ __global__ __launch_bounds__(gemm_threads<T>()) void gemm_kernel(int M, int N, i
     const int c = wn * (BN / WN) + j * 16;
     act_j[j] = c < job.c1 && c + 16 > job.c0;
   }
-  // The wave's piece rows ro[i] and columns co[j] (tile offsets) and which
-  // of its pieces it computes.  By quadrant, a sub-block covering part of the
-  // tile can leave some waves with four pieces and others with none, and the
-  // item lasts as long as its busiest wave.  With four waves of 2 x 2 pieces,
-  // a block-sparse item whose covered pieces (ni x nj of 16 x 16) number at
-  // most four gets one per wave, one at most two pieces wide a row strip per
-  // wave, one at most two pieces tall a column strip per wave; larger ones
-  // keep the quadrants.
   int ro[SI], co[SJ];
   bool pact[SI][SJ];
 #pragma unroll
@@ -239,44 +277,6 @@ __global__ __launch_bounds__(gemm_threads<T>()) void gemm_kernel(int M, int N, i
   for (int i = 0; i < SI; ++i)
 #pragma unroll
     for (int j = 0; j < SJ; ++j) pact[i][j] = act_i[i] && act_j[j];
-  if constexpr (SI == 2 && SJ == 2 && WM * WN == 4) {
-    const int pi0 = job.r0 >> 4, pj0 = job.c0 >> 4;
-    const int ni = ((job.r1 + 15) >> 4) - pi0, nj = ((job.c1 + 15) >> 4) - pj0;
-    const int shape = kit == nullptr ? 0 : ni * nj <= 4 ? 1 : nj <= 2 ? 2 : ni <= 2 ? 3 : 0;
-    if (shape != 0) {
-#pragma unroll
-      for (int i = 0; i < SI; ++i)
-#pragma unroll
-        for (int j = 0; j < SJ; ++j) pact[i][j] = false;
-      ro[1] = ro[0] = 0;
-      co[1] = co[0] = 0;
-      if (shape == 1) {   // one piece per wave
-        if (wave < ni * nj) {
-          ro[0] = (pi0 + wave / nj) * 16;
-          co[0] = (pj0 + wave % nj) * 16;
-          pact[0][0] = true;
-        }
-      } else if (shape == 2) {   // row strips: row pi0 + wave, nj <= 2 pieces
-        if (wave < ni) {
-          ro[0] = (pi0 + wave) * 16;
-#pragma unroll
-          for (int j = 0; j < SJ; ++j) {
-            co[j] = (pj0 + (j < nj ? j : 0)) * 16;
-            pact[0][j] = j < nj;
-          }
-        }
-      } else {   // column strips: column pj0 + wave, ni <= 2 pieces
-        if (wave < nj) {
-          co[0] = (pj0 + wave) * 16;
-#pragma unroll
-          for (int i = 0; i < SI; ++i) {
-            ro[i] = (pi0 + (i < ni ? i : 0)) * 16;
-            pact[i][0] = i < ni;
-          }
-        }
-      }
-    }
-  }
   // double-buffered LDS: compute on `cur` while the next tile's global loads
   // are in flight, then store them into the other buffer; one barrier per
   // tile.  The K steps walk the tile's intervals in order.
@@ -348,10 +348,10 @@ __global__ __launch_bounds__(gemm_threads<T>()) void gemm_kernel(int M, int N, i
     for (int j = 0; j < SJ; ++j)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        // output row inside the 16x16 tile: the f32 MFMA puts rows 4*(lane/16)+r
-        // in a lane, the f64 MFMA rows (lane/16)+4*r (columns are lane%16 for both)
+        // output row inside the 16x16 tile: the f64 MFMA puts rows (lane/16)+4*r
+        // in a lane (columns are lane%16)
         if (!pact[i][j]) continue;
-        const int tr = sizeof(T) == 8 ? (lk + 4 * r) : (lk * 4 + r);
+        const int tr = lk + 4 * r;
         const int lm = ro[i] + tr, ln = co[j] + lr;
         const int gm = m0 + lm;
         const int gn = n0 + ln;
@@ -371,141 +371,309 @@ __global__ __launch_bounds__(gemm_threads<T>()) void gemm_kernel(int M, int N, i
       }
 }
 
-// ---------------------------------------------------------------- BF16 GEMM
-// Complex GEMM on complex64 operands with BF16 MFMA inputs and FP32
-// accumulation (v_mfma_f32_16x16x32_bf16: lane l holds row l%16 and the
-// eight k values 8*(l/16)..+7 of its operand; outputs as the f32 MFMA).
-// Operand tiles are rounded to BF16 (nearest even) as they are staged into
-// LDS, one plane per real/imaginary part, k contiguous.  SPLIT = 1 keeps the
-// rounding residual as a second BF16 term, x = hi + lo, and forms each real
-// product as ah bh + ah bl + al bh (three MFMA products, ~16-bit operands).
-constexpr int BK2 = 32, BKP2 = BK2 + 8, PL2 = 64 * BKP2;
+// ---------------------------------------------------------------- BF16-term GEMM
+// Complex GEMM on complex64 operands through the BF16 matrix cores with FP32
+// accumulation (v_mfma_f32_16x16x32_bf16: lane l holds row l%16 and the eight
+// k values 8*(l/16)..+7 of its operand; outputs as the f32 MFMA).  Each real
+// number is written as a sum of TERMS BF16 numbers, each the nearest to what
+// the ones before leave, and the products of two numbers whose terms' places
+// add up to less than TERMS are formed, the smallest first:
+//   TERMS 1: plain BF16 inputs;
+//   TERMS 2: x = h + l, three products (about 16 bits);
+//   TERMS 3: x = h + m + l exactly (24 bits), six products; what is left out
+//            (m l, l m, l l) is at most 2^-25 of the product.
+// BF16 ends at 2^-133, FP32 at 2^-149: for TERMS 3 both operands are multiplied
+// by 2^20 on the way in (exact) and the sums by 2^-40 on the way out, so that
+// the last term of every normal FP32 number is there (2% of a large product's
+// time).  What overflows on the way is formed again, see the store.
+//
+// What bounds it (TERMS 3, 20480 x 2048 x 1024): the matrix cores and the
+// conversion at once; a K step of a 128 x 64 tile is 192 MFMAs a wave (3190
+// cycles) and about 500 other vector instructions (2300), which the CU's two
+// workgroups overlap in part: 1.86 ms, 184 TFLOP/s at 8 a complex
+// multiply-add, 1.1 PFLOP/s in BF16 (a register-only loop of these MFMAs on
+// such data: 1.9).  The FP32 matrix cores in the 3M form: 2.67 ms.
+constexpr int BKS = 32;
+constexpr float UP3 = 0x1p20f;
 
 typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
+typedef float f2v __attribute__((ext_vector_type(2)));
 
-typedef unsigned short us4 __attribute__((ext_vector_type(4)));
-
-__device__ inline unsigned short bf16_rne(float x) {
-  unsigned u = __float_as_uint(x);
-  u += 0x7fffu + ((u >> 16) & 1u);
-  return (unsigned short)(u >> 16);
-}
-__device__ inline float bf16_val(unsigned short h) { return __uint_as_float((unsigned)h << 16); }
 __device__ inline f4 mfma_bf16(uint4 a, uint4 b, f4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf8, a), __builtin_bit_cast(bf8, b), c, 0, 0,
                                                   0);
 }
-__device__ inline uint4 bf16_neg(uint4 v) {
-  const unsigned s = 0x80008000u;
-  return uint4{v.x ^ s, v.y ^ s, v.z ^ s, v.w ^ s};
-}
+__device__ inline uint4 bf16_flip(uint4 v, unsigned s) { return uint4{v.x ^ s, v.y ^ s, v.z ^ s, v.w ^ s}; }
 
-// A ROWS x 32 complex operand tile (rows r = m of A or n of B) as ROWS/32
-// quads of four consecutive k per thread.  KC: k is the contiguous index in
-// memory.  Planes (real, imaginary; and the residual terms with SPLIT) of
-// ROWS x BKP2 bf16 each, k contiguous.
-// (rows lo .. hi of the tile only: the others are not needed)
-template <bool KC, bool CONJ, int ROWS = 64>
-__device__ inline void bf_load(const float2* __restrict__ X, long long ld, int r0, int R, int k0, int ke, int tid,
-                               float2 (&v)[ROWS / 32][4], int lo = 0, int hi = ROWS) {
+// Operand tile of ROWS rows (m of A or n of B) x 32 k in chunks of eight
+// consecutive k of one row, 4 ROWS / NTH of them per thread.  KC: k is the
+// contiguous index in memory (the four chunks of a row on four neighbouring
+// lanes, 64 bytes each); otherwise the rows are (neighbouring lanes on
+// neighbouring rows, eight loads of eight bytes).
+template <bool KC, int ROWS>
+__device__ inline void chunk_at(int q, int& row, int& ch) {
+  row = KC ? q >> 2 : q % ROWS;
+  ch = KC ? q & 3 : q / ROWS;
+}
+// entry (row, chunk) of an LDS plane, k contiguous, 64 bytes a row: the chunks
+// of a row are permuted by its place in the group of 16 so that neither the
+// operand reads nor the stores of either order meet in a bank
+__device__ inline int plane_at(int row, int ch) { return row * BKS + ((ch ^ (-(row >> 2) & 3)) << 3); }
+
+// Chunk loads of the interior: buffer loads at a uniform base (the tile's
+// first row at k0) and 32-bit offsets, so a chunk costs one address register;
+// rows outside the operand or the sub-block and k past the interval take an
+// offset past the buffer's 2^31 bytes, which loads zero.  WIDE: leading
+// dimensions whose tile reaches past those 2^31 bytes, plain addresses.
+constexpr unsigned BUF_BYTES = 0x80000000u;
+constexpr long long LD_WIDE = 1LL << 20;   // 128 rows of 2^20 complex64: 2^30 bytes
+
+template <bool KC, int ROWS, int NTH>
+__device__ inline void chunk_offsets(long long ld, int r0, int R, int tid, unsigned (&off)[ROWS * 4 / NTH], int lo,
+                                     int hi) {
 #pragma unroll
-  for (int it = 0; it < ROWS / 32; ++it) {
-    const int q = tid + it * NT;
-    const int row = KC ? (q >> 3) : (q % ROWS);
-    const int kq = KC ? (q & 7) : (q / ROWS);
-    const int gr = r0 + row;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int gk = k0 + 4 * kq + j;
-      float2 e;
-      e.x = 0.f;
-      e.y = 0.f;
-      if (gr < R && gk < ke && row >= lo && row < hi) e = KC ? X[(long long)gr * ld + gk] : X[(long long)gk * ld + gr];
-      if (CONJ) e.y = -e.y;
-      v[it][j] = e;
-    }
+  for (int it = 0; it < ROWS * 4 / NTH; ++it) {
+    int row, ch;
+    chunk_at<KC, ROWS>(tid + it * NTH, row, ch);
+    const bool rok = r0 + row < R && row >= lo && row < hi;
+    off[it] = rok ? (KC ? (unsigned)row * (unsigned)ld + 8u * ch : 8u * ch * (unsigned)ld + row) * 8u : BUF_BYTES;
   }
 }
 
-template <bool KC, int SPLIT, int ROWS = 64>
-__device__ inline void bf_store(unsigned short* P, int tid, const float2 (&v)[ROWS / 32][4]) {
-  constexpr int PL = ROWS * BKP2;
+template <bool KC, bool WIDE, int ROWS, int NTH>
+__device__ inline void chunk_load(const float2* __restrict__ X, long long ld, int r0, int R, int k0, int ke, int tid,
+                                  const unsigned (&off)[ROWS * 4 / NTH], float2 (&v)[ROWS * 4 / NTH][8], int lo,
+                                  int hi) {
+  k0 = __builtin_amdgcn_readfirstlane(k0);   // uniform: the buffer's base is scalar
+  ke = __builtin_amdgcn_readfirstlane(ke);
+  if constexpr (WIDE) {
 #pragma unroll
-  for (int it = 0; it < ROWS / 32; ++it) {
-    const int q = tid + it * NT;
-    const int row = KC ? (q >> 3) : (q % ROWS);
-    const int kq = KC ? (q & 7) : (q / ROWS);
-    us4 hr, hi, lr, li;
+    for (int it = 0; it < ROWS * 4 / NTH; ++it) {
+      int row, ch;
+      chunk_at<KC, ROWS>(tid + it * NTH, row, ch);
+      const int gr = r0 + row, gk = k0 + 8 * ch;
+      const bool rok = gr < R && row >= lo && row < hi;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      hr[j] = bf16_rne(v[it][j].x);
-      hi[j] = bf16_rne(v[it][j].y);
-      if (SPLIT) {
-        lr[j] = bf16_rne(v[it][j].x - bf16_val(hr[j]));
-        li[j] = bf16_rne(v[it][j].y - bf16_val(hi[j]));
+      for (int j = 0; j < 8; ++j) {
+        v[it][j] = float2{0.f, 0.f};
+        if (rok && gk + j < ke) v[it][j] = KC ? X[(long long)gr * ld + gk + j] : X[(long long)(gk + j) * ld + gr];
       }
     }
-    const int off = row * BKP2 + 4 * kq;
-    *reinterpret_cast<us4*>(P + off) = hr;
-    *reinterpret_cast<us4*>(P + PL + off) = hi;
-    if (SPLIT) {
-      *reinterpret_cast<us4*>(P + 2 * PL + off) = lr;
-      *reinterpret_cast<us4*>(P + 3 * PL + off) = li;
+  } else {
+    const float2* base = KC ? X + (long long)r0 * ld + k0 : X + (long long)k0 * ld + r0;
+    const __amdgpu_buffer_rsrc_t rs =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<float2*>(base), 0, (int)BUF_BYTES, 0x00020000);
+    const int ldb = (int)ld * 8;   // bytes from one k to the next (not KC)
+    if (k0 + BKS <= ke) {
+#pragma unroll
+      for (int it = 0; it < ROWS * 4 / NTH; ++it) {
+        unsigned o = off[it];
+        asm("" : "+v"(o));   // one register and immediate offsets, not four sums kept through the loop
+        if (KC) {
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            const f4 w = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(rs, (int)(o + 16u * j), 0, 0));
+            v[it][2 * j] = float2{w.x, w.y};
+            v[it][2 * j + 1] = float2{w.z, w.w};
+          }
+        } else {
+#pragma unroll
+          for (int j = 0; j < 8; ++j)
+            v[it][j] = __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(rs, (int)o, j * ldb, 0));
+        }
+      }
+    } else {   // the last step of an interval
+#pragma unroll
+      for (int it = 0; it < ROWS * 4 / NTH; ++it) {
+        int row, ch;
+        chunk_at<KC, ROWS>(tid + it * NTH, row, ch);
+        const int left = ke - k0 - 8 * ch;
+        unsigned o0 = off[it];
+        asm("" : "+v"(o0));
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+          const unsigned o = j < left ? o0 + (KC ? 8u * j : 0u) : BUF_BYTES;
+          v[it][j] = __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(rs, (int)o, KC ? 0 : j * ldb, 0));
+        }
+      }
     }
   }
 }
 
-template <int SPLIT, bool TA, bool CA, bool TB, bool CB, int TAG>
-__global__ __launch_bounds__(NT) void gemm_bf16_kernel(int M, int N, int K, float ar, float ai,
-                                                        const float* __restrict__ A, long long lda, long long sa,
-                                                        const float* __restrict__ B, long long ldb, long long sb,
-                                                        float br, float bi, float* __restrict__ C, long long ldc,
-                                                        long long sc, int S, int Kc, long long sps,
-                                                        const int4* __restrict__ kit, const int2* __restrict__ kiv) {
-  constexpr int NPL = SPLIT ? 4 : 2;
-  __shared__ __attribute__((aligned(16))) unsigned short As[2][NPL * PL2];
-  __shared__ __attribute__((aligned(16))) unsigned short Bs[2][NPL * PL2];
+// the TERMS BF16 terms of eight numbers, packed
+template <int TERMS>
+__device__ inline void bf16_terms(const float (&x)[8], uint4 (&o)[TERMS]) {
+  unsigned w[TERMS][4];
+#pragma unroll
+  for (int p = 0; p < 4; ++p) {
+    f2v v;
+    v.x = TERMS == 3 ? x[2 * p] * UP3 : x[2 * p];
+    v.y = TERMS == 3 ? x[2 * p + 1] * UP3 : x[2 * p + 1];
+#pragma unroll
+    for (int t = 0; t < TERMS; ++t) {
+      w[t][p] = __builtin_bit_cast(unsigned, __builtin_convertvector(v, bf2));
+      if (t + 1 < TERMS) {   // the rest, exact
+        v.x -= __uint_as_float(w[t][p] << 16);
+        v.y -= __uint_as_float(w[t][p] & 0xffff0000u);
+      }
+    }
+  }
+#pragma unroll
+  for (int t = 0; t < TERMS; ++t) o[t] = uint4{w[t][0], w[t][1], w[t][2], w[t][3]};
+}
+
+// planes: term t, real then imaginary part, ROWS x 32 each
+template <bool KC, int TERMS, int ROWS, int NTH>
+__device__ inline void chunk_store(unsigned short* P, int tid, const float2 (&v)[ROWS * 4 / NTH][8]) {
+#pragma unroll
+  for (int it = 0; it < ROWS * 4 / NTH; ++it) {
+    int row, ch;
+    chunk_at<KC, ROWS>(tid + it * NTH, row, ch);
+    float re[8], im[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      re[j] = v[it][j].x;
+      im[j] = v[it][j].y;
+    }
+    uint4 tr[TERMS], ti[TERMS];
+    bf16_terms<TERMS>(re, tr);
+    bf16_terms<TERMS>(im, ti);
+    unsigned short* p = P + plane_at(row, ch);
+#pragma unroll
+    for (int t = 0; t < TERMS; ++t) {
+      *reinterpret_cast<uint4*>(p + (2 * t) * ROWS * BKS) = tr[t];
+      *reinterpret_cast<uint4*>(p + (2 * t + 1) * ROWS * BKS) = ti[t];
+    }
+  }
+}
+
+// cr += a_r b_r + s_r a_i b_i, ci += a_r b_i + s_i a_i b_r (s_i = -s_r) over a
+// step's 32 k, for one row piece and NJ column pieces.
+template <int TERMS, int NJ>
+__device__ inline void step_products(const uint4 (&a_r)[TERMS], const uint4 (&a_i)[TERMS],
+                                     const uint4 (&b_r)[NJ][TERMS], const uint4 (&b_i)[NJ][TERMS], float s_r,
+                                     f4 (&cr)[NJ], f4 (&ci)[NJ]) {
+  if constexpr (TERMS == 3) {
+    // The four products of a step are summed on their own and added to the
+    // running sums once: the signs cost no pass over the operands, and a sum
+    // over K rounds K / 32 times at its full size instead of 3/8 K times
+    // (M x N x K = 20480 x 2048 x 1024: error 1.2e-7 against 7.1e-7 with the
+    // running sums in the matrix cores and 8.0e-7 on the FP32 matrix cores).
+    f4 rr[NJ], ri[NJ], ir[NJ], ii[NJ];
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) rr[j] = ri[j] = ir[j] = ii[j] = f4{0, 0, 0, 0};
+#pragma unroll
+    for (int g = TERMS - 1; g >= 0; --g)   // the products of 2^-8g, the smallest first
+#pragma unroll
+      for (int t = 0; t <= g; ++t)
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+          rr[j] = mfma_bf16(a_r[t], b_r[j][g - t], rr[j]);
+          ri[j] = mfma_bf16(a_r[t], b_i[j][g - t], ri[j]);
+          ir[j] = mfma_bf16(a_i[t], b_r[j][g - t], ir[j]);
+          ii[j] = mfma_bf16(a_i[t], b_i[j][g - t], ii[j]);
+        }
+#pragma unroll
+    for (int j = 0; j < NJ; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        cr[j][r] += fmaf(s_r, ii[j][r], rr[j][r]);
+        ci[j][r] += fmaf(-s_r, ir[j][r], ri[j][r]);
+      }
+  } else {
+    // too few products a step for that: running sums in the matrix cores, the
+    // signs on A's imaginary part
+    const unsigned m_r = s_r < 0.f ? 0x80008000u : 0u, m_i = m_r ^ 0x80008000u;
+    uint4 a_n[TERMS], a_p[TERMS];
+#pragma unroll
+    for (int t = 0; t < TERMS; ++t) {
+      a_n[t] = bf16_flip(a_i[t], m_r);
+      a_p[t] = bf16_flip(a_i[t], m_i);
+    }
+#pragma unroll
+    for (int g = TERMS - 1; g >= 0; --g)
+#pragma unroll
+      for (int t = 0; t <= g; ++t) {
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+          cr[j] = mfma_bf16(a_r[t], b_r[j][g - t], cr[j]);
+          ci[j] = mfma_bf16(a_r[t], b_i[j][g - t], ci[j]);
+        }
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+          cr[j] = mfma_bf16(a_n[t], b_i[j][g - t], cr[j]);
+          ci[j] = mfma_bf16(a_p[t], b_r[j][g - t], ci[j]);
+        }
+      }
+  }
+}
+
+// Tile TM x TN, WM x WN waves.  MAPPED: block-sparse work items (or the dense
+// grid) with sub-blocks of the tile; otherwise the dense grid only, without
+// the branches on a piece's place.
+template <int TERMS_, int TM_, int TN_, int WM_, int WN_, int OCC_, bool MAPPED_ = false, bool WIDE_ = false>
+struct SplitTile {
+  static constexpr int TERMS = TERMS_, TM = TM_, TN = TN_, WM = WM_, WN = WN_, OCC = OCC_, NTH = WM * WN * 64;
+  static constexpr bool MAPPED = MAPPED_, WIDE = WIDE_;
+};
+
+// conj: bit 0 conjugates A, bit 1 conjugates B.  A B* = (A* B)*, so two signs
+// of the products with A's imaginary part and one at the store serve all four.
+template <class TL, bool TA, bool TB, int TAG>
+__global__ __launch_bounds__(TL::NTH, TL::OCC) void gemm_split_kernel(
+    int M, int N, int K, float ar, float ai, const float* __restrict__ A, long long lda, long long sa,
+    const float* __restrict__ B, long long ldb, long long sb, float br, float bi, float* __restrict__ C, long long ldc,
+    long long sc, int S, int Kc, long long sps, const int4* __restrict__ kit, const int2* __restrict__ kiv, int conj) {
+  constexpr int TERMS = TL::TERMS, TM = TL::TM, TN = TL::TN, WM = TL::WM, WN = TL::WN, NTH = TL::NTH;
+  constexpr int SI = TM / WM / 16, SJ = TN / WN / 16, PA = TM * BKS, PB = TN * BKS;
+  __shared__ __attribute__((aligned(16))) unsigned short As[2 * TERMS * PA], Bs[2 * TERMS * PB];
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
-  const int wave = tid >> 6;
-  const int wm = wave >> 1, wn = wave & 1;
-  const TileJob job = tile_job(M, N, K, S, Kc, kit, kiv);
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave / WN, wn = wave % WN;
+  const TileJob job = tile_job<TM, TN>(M, N, K, S, Kc, TL::MAPPED ? kit : nullptr, kiv);
   const int m0 = job.m0, n0 = job.n0, split = job.split;
   const long long bz = job.bz;
   const float2* Ab = reinterpret_cast<const float2*>(A) + bz * sa;
   const float2* Bb = reinterpret_cast<const float2*>(B) + bz * sb;
   float2* Cb = reinterpret_cast<float2*>(C) + bz * sc + split * sps;
 
-  // A tile rows are m (k contiguous when A is not transposed); B tile rows
-  // are n (k contiguous when B is transposed)
-  float2 va[2][4], vb[2][4];
+  float2 va[TM * 4 / NTH][8], vb[TN * 4 / NTH][8];
+  unsigned oa[TM * 4 / NTH], ob[TN * 4 / NTH];
+  chunk_offsets<!TA, TM, NTH>(lda, m0, M, tid, oa, job.r0, job.r1);
+  chunk_offsets<TB, TN, NTH>(ldb, n0, N, tid, ob, job.c0, job.c1);
   auto load = [&](int k0, int kend) {
-    bf_load<!TA, CA>(Ab, lda, m0, M, k0, kend, tid, va, job.r0, job.r1);
-    bf_load<TB, CB>(Bb, ldb, n0, N, k0, kend, tid, vb, job.c0, job.c1);
-  };
-  auto store = [&](int buf) {
-    bf_store<!TA, SPLIT>(As[buf], tid, va);
-    bf_store<TB, SPLIT>(Bs[buf], tid, vb);
+    chunk_load<!TA, TL::WIDE, TM, NTH>(Ab, lda, m0, M, k0, kend, tid, oa, va, job.r0, job.r1);
+    chunk_load<TB, TL::WIDE, TN, NTH>(Bb, ldb, n0, N, k0, kend, tid, ob, vb, job.c0, job.c1);
   };
 
-  f4 cr[2][2], ci[2][2];
+  f4 cr[SI][SJ], ci[SI][SJ];
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int i = 0; i < SI; ++i)
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
+    for (int j = 0; j < SJ; ++j) {
       cr[i][j] = f4{0, 0, 0, 0};
       ci[i][j] = f4{0, 0, 0, 0};
     }
 
   const int lr = lane & 15, lk = lane >> 4;
-  bool act_i[2], act_j[2];
+  int ro[SI], co[SJ];
+  bool pact[SI][SJ];
 #pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const int r = wm * 32 + i * 16, c = wn * 32 + i * 16;
-    act_i[i] = r < job.r1 && r + 16 > job.r0;
-    act_j[i] = c < job.c1 && c + 16 > job.c0;
-  }
+  for (int i = 0; i < SI; ++i) ro[i] = wm * (TM / WM) + i * 16;
+#pragma unroll
+  for (int j = 0; j < SJ; ++j) co[j] = wn * (TN / WN) + j * 16;
+#pragma unroll
+  for (int i = 0; i < SI; ++i)
+#pragma unroll
+    for (int j = 0; j < SJ; ++j)
+      pact[i][j] = !TL::MAPPED ||
+                   (ro[i] < job.r1 && ro[i] + 16 > job.r0 && co[j] < job.c1 && co[j] + 16 > job.c0);
+  if constexpr (TL::MAPPED) deal_pieces(job, kit != nullptr, wave, ro, co, pact);
+  const float s_r = ((conj ^ (conj >> 1)) & 1) ? 1.f : -1.f;
+
   const KIter kr_ = job.kr;
   int iv = 0, k0 = 0, kend = 0;
   if (kr_.n > 0) {
@@ -513,12 +681,10 @@ __global__ __launch_bounds__(NT) void gemm_bf16_kernel(int M, int N, int K, floa
     k0 = I0.x;
     kend = I0.y;
     load(k0, kend);
-    store(0);
   }
-  __syncthreads();
-  int cur = 0;
+  const int la = plane_at(lr, lk);   // rows ro + lr, ro a multiple of 16
   for (bool go = kr_.n > 0; go;) {
-    int nk0 = k0 + BK2, nkend = kend, niv = iv;
+    int nk0 = k0 + BKS, nkend = kend, niv = iv;
     if (nk0 >= kend) {
       ++niv;
       if (niv < kr_.n) {
@@ -528,55 +694,50 @@ __global__ __launch_bounds__(NT) void gemm_bf16_kernel(int M, int N, int K, floa
       }
     }
     const bool more = niv < kr_.n;
-    if (more) load(nk0, nkend);
-    const unsigned short* Ap = As[cur];
-    const unsigned short* Bp = Bs[cur];
-    uint4 a_hr[2], a_hi[2], a_lr[2], a_li[2], b_hr[2], b_hi[2], b_hn[2], b_lr[2], b_li[2], b_ln[2];
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const int off = (wm * 32 + i * 16 + lr) * BKP2 + 8 * lk;
-      a_hr[i] = *reinterpret_cast<const uint4*>(Ap + off);
-      a_hi[i] = *reinterpret_cast<const uint4*>(Ap + PL2 + off);
-      if (SPLIT) {
-        a_lr[i] = *reinterpret_cast<const uint4*>(Ap + 2 * PL2 + off);
-        a_li[i] = *reinterpret_cast<const uint4*>(Ap + 3 * PL2 + off);
-      }
-    }
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const int off = (wn * 32 + j * 16 + lr) * BKP2 + 8 * lk;
-      b_hr[j] = *reinterpret_cast<const uint4*>(Bp + off);
-      b_hi[j] = *reinterpret_cast<const uint4*>(Bp + PL2 + off);
-      b_hn[j] = bf16_neg(b_hi[j]);
-      if (SPLIT) {
-        b_lr[j] = *reinterpret_cast<const uint4*>(Bp + 2 * PL2 + off);
-        b_li[j] = *reinterpret_cast<const uint4*>(Bp + 3 * PL2 + off);
-        b_ln[j] = bf16_neg(b_li[j]);
-      }
-    }
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        if (!(act_i[i] && act_j[j])) continue;
-        if (SPLIT) {
-          cr[i][j] = mfma_bf16(a_hr[i], b_lr[j], cr[i][j]);
-          cr[i][j] = mfma_bf16(a_lr[i], b_hr[j], cr[i][j]);
-          cr[i][j] = mfma_bf16(a_hi[i], b_ln[j], cr[i][j]);
-          cr[i][j] = mfma_bf16(a_li[i], b_hn[j], cr[i][j]);
-          ci[i][j] = mfma_bf16(a_hr[i], b_li[j], ci[i][j]);
-          ci[i][j] = mfma_bf16(a_lr[i], b_hi[j], ci[i][j]);
-          ci[i][j] = mfma_bf16(a_hi[i], b_lr[j], ci[i][j]);
-          ci[i][j] = mfma_bf16(a_li[i], b_hr[j], ci[i][j]);
-        }
-        cr[i][j] = mfma_bf16(a_hr[i], b_hr[j], cr[i][j]);
-        cr[i][j] = mfma_bf16(a_hi[i], b_hn[j], cr[i][j]);
-        ci[i][j] = mfma_bf16(a_hr[i], b_hi[j], ci[i][j]);
-        ci[i][j] = mfma_bf16(a_hi[i], b_hr[j], ci[i][j]);
-      }
-    if (more) store(cur ^ 1);
+    chunk_store<!TA, TERMS, TM, NTH>(As, tid, va);
+    chunk_store<TB, TERMS, TN, NTH>(Bs, tid, vb);
     __syncthreads();
-    cur ^= 1;
+    if (more) load(nk0, nkend);   // in flight while this step is multiplied
+    uint4 b_r[SJ][TERMS], b_i[SJ][TERMS];
+#pragma unroll
+    for (int j = 0; j < SJ; ++j)
+#pragma unroll
+      for (int t = 0; t < TERMS; ++t) {
+        b_r[j][t] = *reinterpret_cast<const uint4*>(Bs + (2 * t) * PB + co[j] * BKS + la);
+        b_i[j][t] = *reinterpret_cast<const uint4*>(Bs + (2 * t + 1) * PB + co[j] * BKS + la);
+      }
+    // the CU's other workgroup converts its next step meanwhile
+    if constexpr (TERMS == 3) __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+    for (int i = 0; i < SI; ++i) {
+      bool any = false, all = true;
+#pragma unroll
+      for (int j = 0; j < SJ; ++j) {
+        any = any || pact[i][j];
+        all = all && pact[i][j];
+      }
+      if (!any) continue;
+      uint4 a_r[TERMS], a_i[TERMS];
+#pragma unroll
+      for (int t = 0; t < TERMS; ++t) {
+        a_r[t] = *reinterpret_cast<const uint4*>(As + (2 * t) * PA + ro[i] * BKS + la);
+        a_i[t] = *reinterpret_cast<const uint4*>(As + (2 * t + 1) * PA + ro[i] * BKS + la);
+      }
+      if (all) {
+        step_products<TERMS, SJ>(a_r, a_i, b_r, b_i, s_r, cr[i], ci[i]);
+      } else if constexpr (TL::MAPPED) {
+#pragma unroll
+        for (int j = 0; j < SJ; ++j)
+          if (pact[i][j])
+            step_products<TERMS, 1>(a_r, a_i, reinterpret_cast<uint4(&)[1][TERMS]>(b_r[j]),
+                                    reinterpret_cast<uint4(&)[1][TERMS]>(b_i[j]), s_r,
+                                    reinterpret_cast<f4(&)[1]>(cr[i][j]), reinterpret_cast<f4(&)[1]>(ci[i][j]));
+      }
+      // one row piece's operands at a time (192 more registers otherwise)
+      if constexpr (TERMS == 3) __builtin_amdgcn_sched_barrier(0);
+    }
+    if constexpr (TERMS == 3) __builtin_amdgcn_s_setprio(0);
+    __syncthreads();
     go = more;
     iv = niv;
     k0 = nk0;
@@ -585,16 +746,39 @@ __global__ __launch_bounds__(NT) void gemm_bf16_kernel(int M, int N, int K, floa
 
   const bool has_beta = (br != 0.f) || (bi != 0.f);
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int i = 0; i < SI; ++i)
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
+    for (int j = 0; j < SJ; ++j) {
+      if (!pact[i][j]) continue;
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int lm = wm * 32 + i * 16 + lk * 4 + r, ln = wn * 32 + j * 16 + lr;
+        const int lm = ro[i] + lk * 4 + r, ln = co[j] + lr;
         const int gm = m0 + lm;
         const int gn = n0 + ln;
         if (gm < M && gn < N && lm >= job.r0 && lm < job.r1 && ln >= job.c0 && ln < job.c1) {
-          const float xr = cr[i][j][r], xi = ci[i][j][r];
+          const float down = TERMS == 3 ? 1.f / (UP3 * UP3) : 1.f;
+          float xr = down * cr[i][j][r], xi = ((conj & 2) ? -down : down) * ci[i][j][r];
+          if constexpr (TERMS == 3) {
+            // An infinity, or a number or sum that the scale takes to one, has
+            // no such terms (h - x is not finite): the element is formed again
+            // from the operands themselves, in the 3M form of the FP64 kernel.
+            if (!(__builtin_isfinite(xr) && __builtin_isfinite(xi))) {
+              float p1 = 0.f, p2 = 0.f, p3 = 0.f;
+              for (int v = 0; v < kr_.n; ++v) {
+                const int2 I = kr_.at(v);
+                for (int k = I.x; k < I.y; ++k) {
+                  const float2 a = TA ? Ab[(long long)k * lda + gm] : Ab[(long long)gm * lda + k];
+                  const float2 b = TB ? Bb[(long long)gn * ldb + k] : Bb[(long long)k * ldb + gn];
+                  const float ay = (conj & 1) ? -a.y : a.y, by = (conj & 2) ? -b.y : b.y;
+                  p1 = fmaf(a.x, b.x, p1);
+                  p2 = fmaf(ay, by, p2);
+                  p3 = fmaf(a.x + ay, b.x + by, p3);
+                }
+              }
+              xr = p1 - p2;
+              xi = p3 - p1 - p2;
+            }
+          }
           float2 o;
           o.x = ar * xr - ai * xi;
           o.y = ar * xi + ai * xr;
@@ -606,6 +790,7 @@ __global__ __launch_bounds__(NT) void gemm_bf16_kernel(int M, int N, int K, floa
           Cb[(long long)gm * ldc + gn] = o;
         }
       }
+    }
 }
 
 // Deterministic split-K reduction: C = alpha * sum_s P[s] + beta * C.
@@ -681,100 +866,207 @@ inline int choose_splits(int M, int N, int K, int batch, size_t ws_bytes, size_t
   return std::max(S, 1);
 }
 
-// Compute mode of the complex64 GEMMs on the calling host thread:
-// 0 FP32 MFMA, 1 BF16 MFMA, 2 three-term BF16 split (see gemm_bf16_kernel).
+// Compute mode of the complex64 GEMMs on the calling host thread (kern::set_float_mode):
+// 0 FP32 (three BF16 terms), 1 BF16, 2 two BF16 terms.
 thread_local int tl_float_mode = 0;
 
 // block-sparse map of the next product issued from the calling host thread
 thread_local const kern::KMap* tl_kmap = nullptr;
 
-template <typename T, int MODE, bool TA, bool CA, bool TB, bool CB, int TAG>
-void launch_tiles(dim3 grid, hipStream_t s, int M, int N, int K, T ar, T ai, const T* A, long long lda,
-                  long long sa, const T* B, long long ldb, long long sb, T br, T bi, T* C, long long ldc,
-                  long long sc, int S, int Kc, long long sps, const int4* kit = nullptr, const int2* kiv = nullptr) {
-  if constexpr (MODE == 0) {
-    hipLaunchKernelGGL((gemm_kernel<T, TA, CA, TB, CB, TAG>), grid, dim3(gemm_threads<T>()), 0, s, M, N, K, ar, ai, A,
-                       lda, sa, B, ldb, sb, br, bi, C, ldc, sc, S, Kc, sps, kit, kiv);
-  } else {
-    hipLaunchKernelGGL((gemm_bf16_kernel<MODE - 1, TA, CA, TB, CB, TAG>), grid, dim3(NT), 0, s, M, N, K, ar, ai,
-                       A, lda, sa, B, ldb, sb, br, bi, C, ldc, sc, S, Kc, sps, kit, kiv);
+// One product as its kernels take it.
+template <typename T> struct Product {
+  hipStream_t s;
+  int M, N, K, batch;
+  const T* A;
+  long long lda, sa;
+  const T* B;
+  long long ldb, sb;
+  T* C;
+  long long ldc, sc;
+  T ar, ai, br, bi;
+  void* ws;
+  size_t ws_bytes;
+};
+
+// Tiles of the BF16-term products, the largest first, with the time of one
+// 32-wide K step of a workgroup in us: alone on its CU, and its share when
+// the CU's other workgroups keep it busy (20480 x 2048 x 1024, 4096 x 509 x
+// 512).  A larger tile converts and reads each operand entry fewer times and
+// so costs less per output, a smaller one fills the 256 CUs on smaller
+// outputs: complete products of 20480 x 2048 x 1024 / 4096 x 509 x 512 take,
+// largest to smallest tile, TERMS 3: 1850 / 68, 2020 / 52 us; TERMS 2: 1165 /
+// 50, 1370 / 41 us; TERMS 1: 583 / 45, 663 / 29, 895 / 27 us.
+struct TileCost {
+  int tm, tn;
+  double alone, shared;
+};
+template <int TERMS> struct SplitTiles;
+template <> struct SplitTiles<3> {
+  static constexpr int n = 2;
+  static constexpr TileCost cost[n] = {{128, 64, 3.9, 2.9}, {64, 64, 2.2, 1.55}};
+  using T0 = SplitTile<3, 128, 64, 2, 2, 2>;
+  using T1 = T0;
+  using Small = SplitTile<3, 64, 64, 2, 2, 2>;
+  using Mapped = SplitTile<3, 64, 64, 2, 2, 2, true>;
+  using Wide = SplitTile<3, 64, 64, 2, 2, 2, true, true>;
+};
+template <> struct SplitTiles<2> {
+  static constexpr int n = 2;
+  static constexpr TileCost cost[n] = {{128, 128, 2.9, 3.65}, {64, 64, 1.6, 1.05}};
+  using T0 = SplitTile<2, 128, 128, 2, 4, 2>;
+  using T1 = T0;
+  using Small = SplitTile<2, 64, 64, 2, 2, 3>;
+  using Mapped = SplitTile<2, 64, 64, 2, 2, 3, true>;
+  using Wide = SplitTile<2, 64, 64, 2, 2, 2, true, true>;
+};
+template <> struct SplitTiles<1> {
+  static constexpr int n = 3;
+  static constexpr TileCost cost[n] = {{256, 128, 2.7, 3.5}, {128, 128, 1.8, 2.05}, {64, 64, 1.1, 0.69}};
+  using T0 = SplitTile<1, 256, 128, 4, 2, 1>;
+  using T1 = SplitTile<1, 128, 128, 4, 2, 2>;
+  using Small = SplitTile<1, 64, 64, 2, 2, 3>;
+  using Mapped = SplitTile<1, 64, 64, 2, 2, 3, true>;
+  using Wide = SplitTile<1, 64, 64, 2, 2, 2, true, true>;
+};
+
+template <class TL, bool TA, bool TB, int TAG>
+void launch_split_tile(dim3 grid, const Product<float>& p, float* C, long long ldc, long long sc, bool plain, int S,
+                       int Kc, long long sps, const int4* kit, const int2* kiv, int conj) {
+  hipLaunchKernelGGL((gemm_split_kernel<TL, TA, TB, TAG>), grid, dim3(TL::NTH), 0, p.s, p.M, p.N, p.K,
+                     plain ? 1.f : p.ar, plain ? 0.f : p.ai, p.A, p.lda, p.sa, p.B, p.ldb, p.sb, plain ? 0.f : p.br,
+                     plain ? 0.f : p.bi, C, ldc, sc, S, Kc, sps, kit, kiv, conj);
+}
+
+// kit null: the dense grid on tile `tile` of SplitTiles (S > 1: partial
+// products, plain); otherwise a block-sparse map of n_items items.
+template <int TERMS, bool TA, bool TB, int TAG>
+void launch_split(const Product<float>& p, int conj, int tile, int n_items, float* C, long long ldc, long long sc,
+                  bool plain, int S, int Kc, long long sps, const int4* kit, const int2* kiv) {
+  using TS = SplitTiles<TERMS>;
+  const bool wide = p.lda >= LD_WIDE || p.ldb >= LD_WIDE;
+  const int tm = wide ? 64 : TS::cost[tile].tm, tn = wide ? 64 : TS::cost[tile].tn;
+  const dim3 grid = kit ? dim3(n_items)
+                        : dim3((p.N + tn - 1) / tn, (p.M + tm - 1) / tm, S > 1 ? S : p.batch);
+  if (wide)
+    launch_split_tile<typename TS::Wide, TA, TB, TAG>(grid, p, C, ldc, sc, plain, S, Kc, sps, kit, kiv, conj);
+  else if (kit)
+    launch_split_tile<typename TS::Mapped, TA, TB, TAG>(grid, p, C, ldc, sc, plain, S, Kc, sps, kit, kiv, conj);
+  else if (tile == TS::n - 1)
+    launch_split_tile<typename TS::Small, TA, TB, TAG>(grid, p, C, ldc, sc, plain, S, Kc, sps, kit, kiv, conj);
+  else if (tile == 0)
+    launch_split_tile<typename TS::T0, TA, TB, TAG>(grid, p, C, ldc, sc, plain, S, Kc, sps, kit, kiv, conj);
+  else
+    launch_split_tile<typename TS::T1, TA, TB, TAG>(grid, p, C, ldc, sc, plain, S, Kc, sps, kit, kiv, conj);
+}
+
+// Tile and K splits of a dense BF16-term product: the pair of least estimated
+// time, from the steps each CU works off (the costs above), about 5 us of
+// launch, first loads and stores, and for a split the reduction's launch and
+// its pass over the partial products (about 3 TB/s).  Splits keep at least two
+// K steps each.
+template <int TERMS>
+void choose_split_tile(int M, int N, int K, int batch, size_t ws_bytes, int* tile, int* S) {
+  using TS = SplitTiles<TERMS>;
+  const double mn = (double)M * N * sizeof(float2);
+  double best = 0.0;
+  *tile = TS::n - 1;
+  *S = 1;
+  for (int t = 0; t < TS::n; ++t) {
+    const TileCost& c = TS::cost[t];
+    const double tiles = (double)((M + c.tm - 1) / c.tm) * ((N + c.tn - 1) / c.tn) * batch;
+    for (int q : {1, 2, 3, 4, 6, 8, 12, 16, 24, 32}) {
+      if (q > 1 && (batch != 1 || K < 2 * BKS * q || q * mn > (double)ws_bytes)) break;
+      const double steps = std::ceil(std::ceil((double)K / q) / BKS), per_cu = std::ceil(tiles * q / 256.0);
+      double us = 5.0 + steps * (per_cu > 1.0 ? std::max(c.alone, per_cu * c.shared) : c.alone);
+      if (q > 1) us += 4.0 + (2 * q + 1) * mn / 3e6;
+      if (best == 0.0 || us < best) {
+        best = us;
+        *tile = t;
+        *S = q;
+      }
+    }
   }
 }
 
-template <typename T, int MODE, int OA, int OB, int TAG>
-void launch_gemm_mode(hipStream_t s, int M, int N, int K, zc alpha, const void* A, long long lda, long long sa,
-                      const void* B, long long ldb, long long sb, zc beta, void* C, long long ldc, long long sc,
-                      int batch, void* ws, size_t ws_bytes) {
+template <bool TA, bool CA, bool TB, bool CB, int TAG>
+void launch_fp64(dim3 grid, const Product<double>& p, double* C, long long ldc, long long sc, bool plain, int S, int Kc,
+                 long long sps, const int4* kit, const int2* kiv) {
+  hipLaunchKernelGGL((gemm_kernel<double, TA, CA, TB, CB, TAG>), grid, dim3(gemm_threads<double>()), 0, p.s, p.M, p.N,
+                     p.K, plain ? 1.0 : p.ar, plain ? 0.0 : p.ai, p.A, p.lda, p.sa, p.B, p.ldb, p.sb,
+                     plain ? 0.0 : p.br, plain ? 0.0 : p.bi, C, ldc, sc, S, Kc, sps, kit, kiv);
+}
+
+// TERMS 0: FP64; otherwise complex64 operands as TERMS BF16 terms.
+template <typename T, int TERMS, int OA, int OB, int TAG>
+void launch_gemm_mode(const Product<T>& p) {
   constexpr bool TA = (OA == TDVP_OP_T || OA == TDVP_OP_C), CA = (OA == TDVP_OP_C || OA == TDVP_OP_R);
   constexpr bool TB = (OB == TDVP_OP_T || OB == TDVP_OP_C), CB = (OB == TDVP_OP_C || OB == TDVP_OP_R);
-  constexpr int KSTEP = MODE == 0 ? BK : BK2;
-  const T* a = static_cast<const T*>(A);
-  const T* b = static_cast<const T*>(B);
+  constexpr int KSTEP = TERMS == 0 ? BK : BKS;
+  using c2 = typename VT<T>::c2;
+  const int M = p.M, N = p.N, K = p.K, batch = p.batch;
+  const long long MN = (long long)M * N;
+  // S > 1 or `plain`: partial products (alpha 1, beta 0)
+  auto launch = [&](int tile, int n_items, T* C, long long ldc, long long sc, bool plain, int S, int Kc, long long sps,
+                    const int4* kit, const int* kiv) {
+    const int2* iv = reinterpret_cast<const int2*>(kiv);
+    if constexpr (TERMS == 0) {
+      (void)tile;
+      const dim3 grid = kit ? dim3(n_items) : dim3((N + BN - 1) / BN, (M + BM - 1) / BM, S > 1 ? S : batch);
+      launch_fp64<TA, CA, TB, CB, TAG>(grid, p, C, ldc, sc, plain, S, Kc, sps, kit, iv);
+    } else {
+      launch_split<TERMS, TA, TB, TAG>(p, (CA ? 1 : 0) | (CB ? 2 : 0), tile, n_items, C, ldc, sc, plain, S, Kc, sps,
+                                       kit, iv);
+    }
+  };
   const kern::KMap* km = tl_kmap;
   if (km && km->batch == batch) {
     if (km->M != M || km->N != N || km->K != K) TDVP_THROW(TDVP_ERR_ARG, "block-sparse map does not fit the product");
     const int gx = (N + BN - 1) / BN;
     if (km->splits > 1) {
-      using c2 = typename VT<T>::c2;
-      const long long MN = (long long)M * N;
       if (!km->part || km->part_bytes < (size_t)km->splits * batch * MN * sizeof(c2))
         TDVP_THROW(TDVP_ERR_ARG, "block-sparse map without room for its partial products");
       T* P = static_cast<T*>(km->part);
       if (km->n_items > 0)
-        launch_tiles<T, MODE, TA, CA, TB, CB, TAG>(dim3(km->n_items), s, M, N, K, T(1), T(0), a, lda, sa, b, ldb, sb,
-                                                   T(0), T(0), P, (long long)N, MN, km->splits, std::max(K, 1),
-                                                   MN * batch, km->items, reinterpret_cast<const int2*>(km->iv));
-      hipLaunchKernelGGL(splitk_reduce_map_kernel<T>, dim3((unsigned)((MN * batch + 255) / 256)), dim3(256), 0, s, P,
-                         batch, (long long)M, (long long)N, gx, km->tinfo, T(alpha.real()), T(alpha.imag()),
-                         T(beta.real()), T(beta.imag()), static_cast<T*>(C), ldc, sc);
+        launch(0, km->n_items, P, N, MN, true, km->splits, std::max(K, 1), MN * batch, km->items, km->iv);
+      hipLaunchKernelGGL(splitk_reduce_map_kernel<T>, dim3((unsigned)((MN * batch + 255) / 256)), dim3(256), 0, p.s, P,
+                         batch, (long long)M, (long long)N, gx, km->tinfo, p.ar, p.ai, p.br, p.bi, p.C, p.ldc, p.sc);
       return;
     }
     if (!km->partial && km->n_items < batch * gx * ((M + BM - 1) / BM))
       TDVP_THROW(TDVP_ERR_ARG, "block-sparse map without every tile");
     if (km->n_items == 0) return;   // a partial map with nothing to write
-    launch_tiles<T, MODE, TA, CA, TB, CB, TAG>(dim3(km->n_items), s, M, N, K, T(alpha.real()), T(alpha.imag()), a,
-                                               lda, sa, b, ldb, sb, T(beta.real()), T(beta.imag()),
-                                               static_cast<T*>(C), ldc, sc, 1, std::max(K, 1), 0LL, km->items,
-                                               reinterpret_cast<const int2*>(km->iv));
+    launch(0, km->n_items, p.C, p.ldc, p.sc, false, 1, std::max(K, 1), 0, km->items, km->iv);
     return;
   }
-  const int S = choose_splits(M, N, K, batch, ws_bytes, sizeof(typename VT<T>::c2));
+  int S, tile = 0;
+  if constexpr (TERMS == 0) S = choose_splits(M, N, K, batch, p.ws_bytes, sizeof(c2));
+  else choose_split_tile<TERMS>(M, N, K, batch, p.ws_bytes, &tile, &S);
   if (S == 1) {
-    dim3 grid((N + BN - 1) / BN, (M + BM - 1) / BM, batch);
-    launch_tiles<T, MODE, TA, CA, TB, CB, TAG>(grid, s, M, N, K, T(alpha.real()), T(alpha.imag()), a, lda, sa, b,
-                                               ldb, sb, T(beta.real()), T(beta.imag()), static_cast<T*>(C), ldc,
-                                               sc, 1, std::max(K, 1), 0LL);
+    launch(tile, 0, p.C, p.ldc, p.sc, false, 1, std::max(K, 1), 0, nullptr, nullptr);
     return;
   }
   const int Kc = ((K + S - 1) / S + KSTEP - 1) / KSTEP * KSTEP;
   const int Sx = (K + Kc - 1) / Kc;
-  dim3 grid((N + BN - 1) / BN, (M + BM - 1) / BM, Sx);
-  launch_tiles<T, MODE, TA, CA, TB, CB, TAG>(grid, s, M, N, K, T(1), T(0), a, lda, sa, b, ldb, sb, T(0), T(0),
-                                             static_cast<T*>(ws), (long long)N, 0LL, Sx, Kc, (long long)M * N);
-  const long long MN = (long long)M * N;
-  hipLaunchKernelGGL(splitk_reduce_kernel<T>, dim3((unsigned)((MN + 255) / 256)), dim3(256), 0, s,
-                     static_cast<const T*>(ws), Sx, (long long)M, (long long)N, T(alpha.real()), T(alpha.imag()),
-                     T(beta.real()), T(beta.imag()), static_cast<T*>(C), ldc);
+  T* P = static_cast<T*>(p.ws);
+  launch(tile, 0, P, N, 0, true, Sx, Kc, MN, nullptr, nullptr);
+  hipLaunchKernelGGL(splitk_reduce_kernel<T>, dim3((unsigned)((MN + 255) / 256)), dim3(256), 0, p.s, P, Sx,
+                     (long long)M, (long long)N, p.ar, p.ai, p.br, p.bi, p.C, p.ldc);
 }
 
 template <typename T, int OA, int OB, int TAG = 0>
 void launch_gemm(hipStream_t s, int M, int N, int K, zc alpha, const void* A, long long lda,
                  long long sa, const void* B, long long ldb, long long sb, zc beta, void* C,
                  long long ldc, long long sc, int batch, void* ws = nullptr, size_t ws_bytes = 0) {
-  if constexpr (sizeof(T) == 4) {
-    if (tl_float_mode == 1) {
-      launch_gemm_mode<T, 1, OA, OB, TAG>(s, M, N, K, alpha, A, lda, sa, B, ldb, sb, beta, C, ldc, sc, batch, ws,
-                                          ws_bytes);
-      return;
-    }
-    if (tl_float_mode == 2) {
-      launch_gemm_mode<T, 2, OA, OB, TAG>(s, M, N, K, alpha, A, lda, sa, B, ldb, sb, beta, C, ldc, sc, batch, ws,
-                                          ws_bytes);
-      return;
-    }
+  const Product<T> p{s, M, N, K, batch, static_cast<const T*>(A), lda, sa, static_cast<const T*>(B), ldb, sb,
+                     static_cast<T*>(C), ldc, sc, T(alpha.real()), T(alpha.imag()), T(beta.real()), T(beta.imag()),
+                     ws, ws ? ws_bytes : 0};
+  if constexpr (sizeof(T) == 8) {
+    launch_gemm_mode<T, 0, OA, OB, TAG>(p);
+  } else {
+    if (tl_float_mode == 1) launch_gemm_mode<T, 1, OA, OB, TAG>(p);
+    else if (tl_float_mode == 2) launch_gemm_mode<T, 2, OA, OB, TAG>(p);
+    else launch_gemm_mode<T, 3, OA, OB, TAG>(p);
   }
-  launch_gemm_mode<T, 0, OA, OB, TAG>(s, M, N, K, alpha, A, lda, sa, B, ldb, sb, beta, C, ldc, sc, batch, ws,
-                                      ws_bytes);
 }
 
 template <typename T, int OA>
