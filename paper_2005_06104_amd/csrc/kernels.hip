@@ -1,10 +1,7 @@
 // Device kernels of the GSE-TDVP1 hot path (gfx950 / CDNA4).
 //
-// * FP64 GEMM: complex GEMM split into real MFMA products.  A complex product
-//   (Ar + i Ai)(Br + i Bi) is three real MFMA accumulations, Ar Br, Ai Bi and
-//   (Ar + Ai)(Br + Bi), combined into Ar Br - Ai Bi and Ar Bi + Ai Br at the
-//   store (v_mfma_f64_16x16x4f64); operand tiles are de-interleaved into real
-//   and imaginary planes in LDS.
+// * FP64 GEMM: a complex product as three real MFMA accumulations
+//   (v_mfma_f64_16x16x4f64), the operands loaded straight in the MFMA layout.
 // * complex64 GEMM: every operand as one, two or three BF16 terms on the BF16
 //   matrix cores, which are sixteen times as fast as the FP32 ones; three
 //   terms hold an FP32 number exactly.
@@ -15,6 +12,8 @@
 // * complex128 vector helpers for the Lanczos recurrence (FP64 always).
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "common.h"
 #include "wave.h"
 
@@ -24,23 +23,16 @@ typedef double d4 __attribute__((ext_vector_type(4)));
 typedef float f4 __attribute__((ext_vector_type(4)));
 
 template <typename T> struct VT;
-template <> struct VT<double> { using c2 = double2; using acc = d4; };
-template <> struct VT<float> { using c2 = float2; using acc = f4; };
+template <> struct VT<double> { using c2 = double2; };
+template <> struct VT<float> { using c2 = float2; };
 
 __device__ inline d4 mfma(double a, double b, d4 c) {
   return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
 }
 
 // ---------------------------------------------------------------- GEMM
-// FP64: block tile BM x BN complex outputs, BK complex per stage, 1024
-// threads = 16 waves in a 4 x 4 grid, one 16x16 MFMA tile each (four waves
-// per SIMD keep the long FP64 MFMA pipeline fed while others wait on LDS or
-// the stage barrier).
-constexpr int BM = 64, BN = 64, BK = 16;
-constexpr int PAD = 1;
-template <typename T> struct WaveGrid;
-template <> struct WaveGrid<double> { static constexpr int WM = 4, WN = 4; };
-template <typename T> constexpr int gemm_threads() { return WaveGrid<T>::WM * WaveGrid<T>::WN * 64; }
+// Block-sparse maps are built on output tiles of BM x BN.
+constexpr int BM = 64, BN = 64;
 
 // TAG only separates instantiations (the one-site effective Hamiltonian uses
 // its own so that profilers and timers see it apart from the other GEMMs).
@@ -52,6 +44,12 @@ template <typename T> constexpr int gemm_threads() { return WaveGrid<T>::WM * Wa
 // pairs, its partial product at C + part * sps.  kit null: the dense tile
 // grid over the whole K range (or one split-K part).  A tile with no
 // interval writes alpha * 0 + beta * C.
+
+// Operands are read by buffer loads at a uniform base and 32-bit offsets; an
+// entry that is not there (past the operand, the sub-block or the interval)
+// takes an offset past the buffer's 2^31 bytes and loads zero.
+constexpr unsigned BUF_BYTES = 0x80000000u;
+
 struct KIter {
   const int2* iv;
   int n;
@@ -115,260 +113,44 @@ __device__ inline TileJob tile_job(int M, int N, int K, int S, int Kc, const int
   return j;
 }
 
-// The wave's piece rows ro[i] and columns co[j] (tile offsets) and which of
-// its pieces it computes, on entry by quadrant.  By quadrant, a sub-block
-// covering part of the tile can leave some waves with four pieces and others
-// with none, and the item lasts as long as its busiest wave.  With four waves
-// of 2 x 2 pieces, a block-sparse item whose covered pieces (ni x nj of
-// 16 x 16) number at most four gets one per wave, one at most two pieces wide
-// a row strip per wave, one at most two pieces tall a column strip per wave;
-// larger ones keep the quadrants.
-__device__ inline void deal_pieces(const TileJob& job, bool mapped, int wave, int (&ro)[2], int (&co)[2],
-                                   bool (&pact)[2][2]) {
+// The wave's pieces of a block-sparse item: the product of ni rows and nj
+// columns of 16 x 16 pieces at the tile offsets ro, co (on entry its quadrant
+// of the 64 x 64 tile).  By quadrant, a sub-block covering part of the tile
+// can leave some waves with four pieces and others with none, and the item
+// lasts as long as its busiest wave.  An item whose covered pieces number at
+// most four gets one per wave, one at most two pieces wide a row strip per
+// wave, one at most two pieces tall a column strip per wave; larger ones keep
+// the covered pieces of the quadrants.
+__device__ inline void deal_pieces(const TileJob& job, bool mapped, int wave, int (&ro)[2], int (&co)[2], int& ni,
+                                   int& nj) {
+  if (!mapped) return;
   const int pi0 = job.r0 >> 4, pj0 = job.c0 >> 4;
-  const int ni = ((job.r1 + 15) >> 4) - pi0, nj = ((job.c1 + 15) >> 4) - pj0;
-  const int shape = !mapped ? 0 : ni * nj <= 4 ? 1 : nj <= 2 ? 2 : ni <= 2 ? 3 : 0;
-  if (shape == 0) return;
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j) pact[i][j] = false;
-  ro[1] = ro[0] = 0;
-  co[1] = co[0] = 0;
-  if (shape == 1) {   // one piece per wave
-    if (wave < ni * nj) {
-      ro[0] = (pi0 + wave / nj) * 16;
-      co[0] = (pj0 + wave % nj) * 16;
-      pact[0][0] = true;
-    }
-  } else if (shape == 2) {   // row strips: row pi0 + wave, nj <= 2 pieces
-    if (wave < ni) {
-      ro[0] = (pi0 + wave) * 16;
-#pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        co[j] = (pj0 + (j < nj ? j : 0)) * 16;
-        pact[0][j] = j < nj;
-      }
-    }
-  } else {   // column strips: column pj0 + wave, ni <= 2 pieces
-    if (wave < nj) {
-      co[0] = (pj0 + wave) * 16;
-#pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        ro[i] = (pi0 + (i < ni ? i : 0)) * 16;
-        pact[i][0] = i < ni;
-      }
-    }
+  const int mi = ((job.r1 + 15) >> 4) - pi0, mj = ((job.c1 + 15) >> 4) - pj0;
+  if (mi * mj <= 4) {   // one piece per wave
+    ni = nj = wave < mi * mj ? 1 : 0;
+    ro[0] = (pi0 + wave / mj) * 16;
+    co[0] = (pj0 + wave % mj) * 16;
+  } else if (mj <= 2) {   // row strips
+    ni = wave < mi ? 1 : 0;
+    nj = mj;
+    ro[0] = (pi0 + wave) * 16;
+    co[0] = pj0 * 16;
+  } else if (mi <= 2) {   // column strips
+    ni = mi;
+    nj = wave < mj ? 1 : 0;
+    ro[0] = pi0 * 16;
+    co[0] = (pj0 + wave) * 16;
+  } else {   // the covered part of the quadrant
+    const int i0 = max(ro[0] >> 4, pi0), i1 = min((ro[0] >> 4) + 2, pi0 + mi);
+    const int j0 = max(co[0] >> 4, pj0), j1 = min((co[0] >> 4) + 2, pj0 + mj);
+    ni = max(i1 - i0, 0);
+    nj = max(j1 - j0, 0);
+    ro[0] = i0 * 16;
+    co[0] = j0 * 16;
   }
-}
-
-template <typename T, bool TA, bool CA, bool TB, bool CB, int TAG>
-__global__ __launch_bounds__(gemm_threads<T>()) void gemm_kernel(int M, int N, int K, T ar, T ai, const T* __restrict__ A,
-                                                   long long lda, long long sa, const T* __restrict__ B,
-                                                   long long ldb, long long sb, T br, T bi,
-                                                   T* __restrict__ C, long long ldc, long long sc, int S, int Kc,
-                                                   long long sps, const int4* __restrict__ kit,
-                                                   const int2* __restrict__ kiv) {
-  using c2 = typename VT<T>::c2;
-  using acc_t = typename VT<T>::acc;
-  __shared__ T As_r[2][BK][BM + PAD], As_i[2][BK][BM + PAD];
-  __shared__ T Bs_r[2][BK][BN + PAD], Bs_i[2][BK][BN + PAD];
-
-  constexpr int WM = WaveGrid<T>::WM, WN = WaveGrid<T>::WN, NTH = WM * WN * 64;
-  constexpr int SI = BM / WM / 16, SJ = BN / WN / 16;   // MFMA tiles per wave
-  const int tid = threadIdx.x;
-  const int lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm = wave / WN, wn = wave % WN;
-  const TileJob job = tile_job<BM, BN>(M, N, K, S, Kc, kit, kiv);
-  const int m0 = job.m0, n0 = job.n0, split = job.split;
-  const long long bz = job.bz;
-  const c2* Ab = reinterpret_cast<const c2*>(A) + bz * sa;
-  const c2* Bb = reinterpret_cast<const c2*>(B) + bz * sb;
-  c2* Cb = reinterpret_cast<c2*>(C) + bz * sc + split * sps;
-
-  constexpr int PER = (BM * BK) / NTH;  // complex elements per thread per operand
-  c2 ra[PER], rb[PER];
-
-  auto load = [&](int k0, int kend) {
-#pragma unroll
-    for (int it = 0; it < PER; ++it) {
-      const int idx = tid + it * NTH;
-      int m, k;
-      if (!TA) { m = idx / BK; k = idx % BK; } else { k = idx / BM; m = idx % BM; }
-      const int gm = m0 + m, gk = k0 + k;
-      c2 v;
-      v.x = T(0); v.y = T(0);
-      // rows outside the sub-block are not needed (their products are not stored)
-      if (gm < M && gk < kend && m >= job.r0 && m < job.r1)
-        v = TA ? Ab[(long long)gk * lda + gm] : Ab[(long long)gm * lda + gk];
-      if (CA) v.y = -v.y;
-      ra[it] = v;
-    }
-#pragma unroll
-    for (int it = 0; it < PER; ++it) {
-      const int idx = tid + it * NTH;
-      int n, k;
-      if (!TB) { k = idx / BN; n = idx % BN; } else { n = idx / BK; k = idx % BK; }
-      const int gn = n0 + n, gk = k0 + k;
-      c2 v;
-      v.x = T(0); v.y = T(0);
-      if (gn < N && gk < kend && n >= job.c0 && n < job.c1)
-        v = TB ? Bb[(long long)gn * ldb + gk] : Bb[(long long)gk * ldb + gn];
-      if (CB) v.y = -v.y;
-      rb[it] = v;
-    }
-  };
-  auto store = [&](int buf) {
-#pragma unroll
-    for (int it = 0; it < PER; ++it) {
-      const int idx = tid + it * NTH;
-      int m, k;
-      if (!TA) { m = idx / BK; k = idx % BK; } else { k = idx / BM; m = idx % BM; }
-      As_r[buf][k][m] = ra[it].x;
-      As_i[buf][k][m] = ra[it].y;
-    }
-#pragma unroll
-    for (int it = 0; it < PER; ++it) {
-      const int idx = tid + it * NTH;
-      int n, k;
-      if (!TB) { k = idx / BN; n = idx % BN; } else { n = idx / BK; k = idx % BK; }
-      Bs_r[buf][k][n] = rb[it].x;
-      Bs_i[buf][k][n] = rb[it].y;
-    }
-  };
-
-  // Three real products per complex multiply-add (the 3M form):
-  // p1 = sum ar br, p2 = sum ai bi, p3 = sum (ar + ai)(br + bi); then
-  // Re = p1 - p2 and Im = p3 - p1 - p2.  The operand sums are formed in
-  // registers after the LDS reads, so the matrix cores issue 3/4 of the
-  // products of the four-product form at the same LDS traffic.
-  acc_t p1[SI][SJ], p2[SI][SJ], p3[SI][SJ];
-#pragma unroll
-  for (int i = 0; i < SI; ++i)
-#pragma unroll
-    for (int j = 0; j < SJ; ++j) {
-      p1[i][j] = acc_t{0, 0, 0, 0};
-      p2[i][j] = acc_t{0, 0, 0, 0};
-      p3[i][j] = acc_t{0, 0, 0, 0};
-    }
-
-  const int lr = lane & 15, lk = lane >> 4;
-  // the wave's 16 x 16 pieces that meet the sub-block (the others skip their
-  // products and are not stored)
-  bool act_i[SI], act_j[SJ];
-#pragma unroll
-  for (int i = 0; i < SI; ++i) {
-    const int r = wm * (BM / WM) + i * 16;
-    act_i[i] = r < job.r1 && r + 16 > job.r0;
-  }
-#pragma unroll
-  for (int j = 0; j < SJ; ++j) {
-    const int c = wn * (BN / WN) + j * 16;
-    act_j[j] = c < job.c1 && c + 16 > job.c0;
-  }
-  int ro[SI], co[SJ];
-  bool pact[SI][SJ];
-#pragma unroll
-  for (int i = 0; i < SI; ++i) ro[i] = wm * (BM / WM) + i * 16;
-#pragma unroll
-  for (int j = 0; j < SJ; ++j) co[j] = wn * (BN / WN) + j * 16;
-#pragma unroll
-  for (int i = 0; i < SI; ++i)
-#pragma unroll
-    for (int j = 0; j < SJ; ++j) pact[i][j] = act_i[i] && act_j[j];
-  // double-buffered LDS: compute on `cur` while the next tile's global loads
-  // are in flight, then store them into the other buffer; one barrier per
-  // tile.  The K steps walk the tile's intervals in order.
-  const KIter kr_ = job.kr;
-  int iv = 0, k0 = 0, kend = 0;
-  if (kr_.n > 0) {
-    const int2 I0 = kr_.at(0);
-    k0 = I0.x;
-    kend = I0.y;
-    load(k0, kend);
-    store(0);
-  }
-  __syncthreads();
-  int cur = 0;
-  for (bool go = kr_.n > 0; go;) {
-    int nk0 = k0 + BK, nkend = kend, niv = iv;
-    if (nk0 >= kend) {
-      ++niv;
-      if (niv < kr_.n) {
-        const int2 J = kr_.at(niv);
-        nk0 = J.x;
-        nkend = J.y;
-      }
-    }
-    const bool more = niv < kr_.n;
-    if (more) load(nk0, nkend);
-#pragma unroll
-    for (int kk = 0; kk < BK; kk += 4) {
-      // the stage's entries past the interval end are zeros: skip their
-      // MFMA steps (K intervals of charge blocks end anywhere)
-      if (kk > 0 && k0 + kk >= kend) break;
-      const int kr = kk + lk;
-      T a_r[SI], a_i[SI], a_s[SI], b_r[SJ], b_i[SJ], b_s[SJ];
-#pragma unroll
-      for (int i = 0; i < SI; ++i) {
-        a_r[i] = As_r[cur][kr][ro[i] + lr];
-        a_i[i] = As_i[cur][kr][ro[i] + lr];
-        a_s[i] = a_r[i] + a_i[i];
-      }
-#pragma unroll
-      for (int j = 0; j < SJ; ++j) {
-        b_r[j] = Bs_r[cur][kr][co[j] + lr];
-        b_i[j] = Bs_i[cur][kr][co[j] + lr];
-        b_s[j] = b_r[j] + b_i[j];
-      }
-#pragma unroll
-      for (int i = 0; i < SI; ++i)
-#pragma unroll
-        for (int j = 0; j < SJ; ++j) {
-          if (!pact[i][j]) continue;
-          p1[i][j] = mfma(a_r[i], b_r[j], p1[i][j]);
-          p2[i][j] = mfma(a_i[i], b_i[j], p2[i][j]);
-          p3[i][j] = mfma(a_s[i], b_s[j], p3[i][j]);
-        }
-    }
-    if (more) store(cur ^ 1);
-    __syncthreads();
-    cur ^= 1;
-    go = more;
-    iv = niv;
-    k0 = nk0;
-    kend = nkend;
-  }
-
-  const bool has_beta = (br != T(0)) || (bi != T(0));
-#pragma unroll
-  for (int i = 0; i < SI; ++i)
-#pragma unroll
-    for (int j = 0; j < SJ; ++j)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        // output row inside the 16x16 tile: the f64 MFMA puts rows (lane/16)+4*r
-        // in a lane (columns are lane%16)
-        if (!pact[i][j]) continue;
-        const int tr = lk + 4 * r;
-        const int lm = ro[i] + tr, ln = co[j] + lr;
-        const int gm = m0 + lm;
-        const int gn = n0 + ln;
-        if (gm < M && gn < N && lm >= job.r0 && lm < job.r1 && ln >= job.c0 && ln < job.c1) {
-          const T q1 = p1[i][j][r], q2 = p2[i][j][r];
-          const T xr = q1 - q2, xi = p3[i][j][r] - q1 - q2;
-          c2 o;
-          o.x = ar * xr - ai * xi;
-          o.y = ar * xi + ai * xr;
-          if (has_beta) {
-            const c2 old = Cb[(long long)gm * ldc + gn];
-            o.x += br * old.x - bi * old.y;
-            o.y += br * old.y + bi * old.x;
-          }
-          Cb[(long long)gm * ldc + gn] = o;
-        }
-      }
+  if (ni == 0 || nj == 0) ni = nj = ro[0] = co[0] = 0;
+  ro[1] = ni == 2 ? ro[0] + 16 : ro[0];
+  co[1] = nj == 2 ? co[0] + 16 : co[0];
 }
 
 // ---------------------------------------------------------------- BF16-term GEMM
@@ -421,12 +203,9 @@ __device__ inline void chunk_at(int q, int& row, int& ch) {
 // operand reads nor the stores of either order meet in a bank
 __device__ inline int plane_at(int row, int ch) { return row * BKS + ((ch ^ (-(row >> 2) & 3)) << 3); }
 
-// Chunk loads of the interior: buffer loads at a uniform base (the tile's
-// first row at k0) and 32-bit offsets, so a chunk costs one address register;
-// rows outside the operand or the sub-block and k past the interval take an
-// offset past the buffer's 2^31 bytes, which loads zero.  WIDE: leading
-// dimensions whose tile reaches past those 2^31 bytes, plain addresses.
-constexpr unsigned BUF_BYTES = 0x80000000u;
+// Chunk loads: the buffer's base is the tile's first row at k0, so a chunk
+// costs one address register.  WIDE: leading dimensions whose tile reaches
+// past the buffer's 2^31 bytes, plain addresses.
 constexpr long long LD_WIDE = 1LL << 20;   // 128 rows of 2^20 complex64: 2^30 bytes
 
 template <bool KC, int ROWS, int NTH>
@@ -659,19 +438,12 @@ __global__ __launch_bounds__(TL::NTH, TL::OCC) void gemm_split_kernel(
     }
 
   const int lr = lane & 15, lk = lane >> 4;
-  int ro[SI], co[SJ];
-  bool pact[SI][SJ];
+  int ro[SI], co[SJ], ni = SI, nj = SJ;
 #pragma unroll
   for (int i = 0; i < SI; ++i) ro[i] = wm * (TM / WM) + i * 16;
 #pragma unroll
   for (int j = 0; j < SJ; ++j) co[j] = wn * (TN / WN) + j * 16;
-#pragma unroll
-  for (int i = 0; i < SI; ++i)
-#pragma unroll
-    for (int j = 0; j < SJ; ++j)
-      pact[i][j] = !TL::MAPPED ||
-                   (ro[i] < job.r1 && ro[i] + 16 > job.r0 && co[j] < job.c1 && co[j] + 16 > job.c0);
-  if constexpr (TL::MAPPED) deal_pieces(job, kit != nullptr, wave, ro, co, pact);
+  if constexpr (TL::MAPPED) deal_pieces(job, kit != nullptr, wave, ro, co, ni, nj);
   const float s_r = ((conj ^ (conj >> 1)) & 1) ? 1.f : -1.f;
 
   const KIter kr_ = job.kr;
@@ -710,29 +482,19 @@ __global__ __launch_bounds__(TL::NTH, TL::OCC) void gemm_split_kernel(
     if constexpr (TERMS == 3) __builtin_amdgcn_s_setprio(1);
 #pragma unroll
     for (int i = 0; i < SI; ++i) {
-      bool any = false, all = true;
-#pragma unroll
-      for (int j = 0; j < SJ; ++j) {
-        any = any || pact[i][j];
-        all = all && pact[i][j];
-      }
-      if (!any) continue;
+      if (TL::MAPPED && i >= ni) break;
       uint4 a_r[TERMS], a_i[TERMS];
 #pragma unroll
       for (int t = 0; t < TERMS; ++t) {
         a_r[t] = *reinterpret_cast<const uint4*>(As + (2 * t) * PA + ro[i] * BKS + la);
         a_i[t] = *reinterpret_cast<const uint4*>(As + (2 * t + 1) * PA + ro[i] * BKS + la);
       }
-      if (all) {
+      if (!TL::MAPPED || nj == SJ)
         step_products<TERMS, SJ>(a_r, a_i, b_r, b_i, s_r, cr[i], ci[i]);
-      } else if constexpr (TL::MAPPED) {
-#pragma unroll
-        for (int j = 0; j < SJ; ++j)
-          if (pact[i][j])
-            step_products<TERMS, 1>(a_r, a_i, reinterpret_cast<uint4(&)[1][TERMS]>(b_r[j]),
-                                    reinterpret_cast<uint4(&)[1][TERMS]>(b_i[j]), s_r,
-                                    reinterpret_cast<f4(&)[1]>(cr[i][j]), reinterpret_cast<f4(&)[1]>(ci[i][j]));
-      }
+      else if (nj == 1)
+        step_products<TERMS, 1>(a_r, a_i, reinterpret_cast<uint4(&)[1][TERMS]>(b_r[0]),
+                                reinterpret_cast<uint4(&)[1][TERMS]>(b_i[0]), s_r, reinterpret_cast<f4(&)[1]>(cr[i][0]),
+                                reinterpret_cast<f4(&)[1]>(ci[i][0]));
       // one row piece's operands at a time (192 more registers otherwise)
       if constexpr (TERMS == 3) __builtin_amdgcn_sched_barrier(0);
     }
@@ -749,7 +511,7 @@ __global__ __launch_bounds__(TL::NTH, TL::OCC) void gemm_split_kernel(
   for (int i = 0; i < SI; ++i)
 #pragma unroll
     for (int j = 0; j < SJ; ++j) {
-      if (!pact[i][j]) continue;
+      if (TL::MAPPED && (i >= ni || j >= nj)) continue;
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int lm = ro[i] + lk * 4 + r, ln = co[j] + lr;
@@ -791,6 +553,221 @@ __global__ __launch_bounds__(TL::NTH, TL::OCC) void gemm_split_kernel(
         }
       }
     }
+}
+
+// ---------------------------------------------------------------- FP64 GEMM
+// An FP64 MFMA takes 64 cycles for 1 KiB of operands, so the vector caches can
+// feed the matrix cores by themselves: every wave loads its operand pieces
+// straight in the MFMA layout (lane l: row or column l % 16, k = l / 16) PF
+// steps of four k ahead, nothing passes through LDS and no wave waits for
+// another.  A block is WM x WN waves of SI x SJ 16 x 16 pieces each, times up
+// to PARTS waves that take one part of K each and meet in LDS at the end.
+// A complex product is three real ones (the 3M form): p1 = sum ar br,
+// p2 = sum ai bi, p3 = sum (ar + ai)(br + bi); Re = p1 - p2, Im = p3 - p1 - p2.
+// The parts of K depend on M, N and K alone (choose_splits) and are summed in
+// their order, so every tile gives the same bits.
+// What bounds it: the matrix cores (80 ns a piece and step) and, not quite
+// beside them, the operand loads (5 us a MiB and CU with two or more waves on
+// a SIMD, 9 with one).  20480 x 2048 x 1024: 4.02 ms, 85 TFLOP/s at 8 a
+// complex multiply-add, 82% of what three products allow (through LDS tiles
+// with a barrier a step: 4.47 ms).
+template <int SI_, int SJ_, int WM_, int WN_, int PARTS_, int PF_, bool MAPPED_ = false, bool WIDE_ = false>
+struct DirectTile {
+  static constexpr int SI = SI_, SJ = SJ_, WM = WM_, WN = WN_, PARTS = PARTS_, PF = PF_;
+  static constexpr int TM = WM * SI * 16, TN = WN * SJ * 16, NTH = WM * WN * PARTS * 64;
+  static constexpr bool MAPPED = MAPPED_, WIDE = WIDE_;
+  static_assert(PARTS == 1 || WM * WN == 1, "waves along K or over the tile");
+};
+constexpr long long LD_WIDE64 = 1LL << 21;   // 64 rows of 2^21 complex128: 2^31 bytes
+
+// An operand as a wave reads it: rows (columns of B) r0 + off, lane row
+// off + l % 16.  KC: k is the contiguous index.
+template <bool KC, bool WIDE, int NP> struct DirectOperand {
+  const double2* base;   // row r0, k = 0
+  long long ld;
+  unsigned at[NP];       // byte offset of the lane's entry at the step's first k
+  int row[NP];           // WIDE: the lane's row, -1 if it is not there
+  __device__ void init(const double2* X, long long ld_, int r0, int R, const int (&off)[NP], int lo, int hi, int lr,
+                       int lk) {
+    ld = ld_;
+    base = X + (KC ? (long long)r0 * ld : (long long)r0);
+#pragma unroll
+    for (int i = 0; i < NP; ++i) {
+      const int r = off[i] + lr;
+      const bool in = r0 + r < R && r >= lo && r < hi;
+      if constexpr (WIDE) row[i] = in ? r : -1;
+      else at[i] = in ? (KC ? (unsigned)r * (unsigned)ld + lk : (unsigned)lk * (unsigned)ld + r) * 16u : BUF_BYTES;
+    }
+  }
+  // the first N pieces
+  template <int N> __device__ void load(int k0, bool in, int lk, double2 (&v)[NP]) const {
+    if constexpr (WIDE) {
+#pragma unroll
+      for (int i = 0; i < N; ++i) {
+        v[i] = double2{0.0, 0.0};
+        if (in && row[i] >= 0)
+          v[i] = base[KC ? (long long)row[i] * ld + k0 + lk : (long long)(k0 + lk) * ld + row[i]];
+      }
+    } else {
+      const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+          const_cast<double2*>(base + (KC ? (long long)k0 : (long long)k0 * ld)), 0, (int)BUF_BYTES, 0x00020000);
+#pragma unroll
+      for (int i = 0; i < N; ++i)
+        v[i] = __builtin_bit_cast(double2,
+                                  __builtin_amdgcn_raw_buffer_load_b128(rs, (int)(in ? at[i] : BUF_BYTES), 0, 0));
+    }
+  }
+};
+
+// S splits over the grid, or (PARTS > 1) a block's waves as parts of Kc each;
+// conj: bit 0 conjugates A, bit 1 conjugates B
+template <class TL, bool TA, bool TB, int TAG>
+__global__ __launch_bounds__(TL::NTH, TL::NTH > 512 ? 4 : 2) void gemm_direct_kernel(
+    int M, int N, int K, double ar, double ai, const double* __restrict__ A, long long lda, long long sa,
+    const double* __restrict__ B, long long ldb, long long sb, double br, double bi, double* __restrict__ C,
+    long long ldc, long long sc, int S, int Kc, long long sps, const int4* __restrict__ kit,
+    const int2* __restrict__ kiv, int conj) {
+  constexpr int SI = TL::SI, SJ = TL::SJ, WN = TL::WN, PF = TL::PF, E = SI * SJ * 4;
+  extern __shared__ unsigned char direct_lds[];
+  const int tid = threadIdx.x, lane = tid & 63, lr = lane & 15, lk = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int parts = TL::PARTS > 1 ? (int)(blockDim.x >> 6) : 1;
+  const int wk = TL::PARTS > 1 ? wave : 0, wmn = TL::PARTS > 1 ? 0 : wave;
+  const TileJob job = tile_job<TL::TM, TL::TN>(M, N, K, S, TL::PARTS > 1 ? K : Kc, TL::MAPPED ? kit : nullptr, kiv);
+  // the wave's pieces: the product of ni rows and nj columns of pieces at the
+  // tile offsets ro, co
+  int ro[SI], co[SJ], ni = SI, nj = SJ;
+#pragma unroll
+  for (int i = 0; i < SI; ++i) ro[i] = (wmn / WN * SI + i) * 16;
+#pragma unroll
+  for (int j = 0; j < SJ; ++j) co[j] = (wmn % WN * SJ + j) * 16;
+  if constexpr (TL::MAPPED) {
+    deal_pieces(job, kit != nullptr, wmn, ro, co, ni, nj);
+    if (ni == 0 || nj == 0) return;
+  }
+
+  DirectOperand<!TA, TL::WIDE, SI> oa;
+  DirectOperand<TB, TL::WIDE, SJ> ob;
+  oa.init(reinterpret_cast<const double2*>(A) + job.bz * sa, lda, job.m0, M, ro, job.r0, job.r1, lr, lk);
+  ob.init(reinterpret_cast<const double2*>(B) + job.bz * sb, ldb, job.n0, N, co, job.c0, job.c1, lr, lk);
+
+  d4 p1[SI][SJ], p2[SI][SJ], p3[SI][SJ];
+#pragma unroll
+  for (int i = 0; i < SI; ++i)
+#pragma unroll
+    for (int j = 0; j < SJ; ++j) p1[i][j] = p2[i][j] = p3[i][j] = d4{0, 0, 0, 0};
+  const double ca = (conj & 1) ? -1.0 : 1.0, cb = (conj & 2) ? -1.0 : 1.0;
+  const KIter kr = job.kr;
+  // the steps over the wave's intervals with NI x NJ pieces, PF of them in
+  // flight; `left` counts those loaded and not yet multiplied
+  auto multiply = [&](auto ni_, auto nj_) {
+    constexpr int NI = decltype(ni_)::value, NJ = decltype(nj_)::value;
+    int iv = 0, k = 0, kend = 0, left = 0;
+    if (kr.n > 0) {
+      const int2 I = kr.at(0);
+      k = __builtin_amdgcn_readfirstlane(I.x);
+      kend = __builtin_amdgcn_readfirstlane(I.y);
+    }
+    if (parts > 1) {
+      k = wk * Kc;
+      kend = min(kend, k + Kc);
+    }
+    double2 va[PF][SI], vb[PF][SJ];
+    auto load = [&](double2 (&a)[SI], double2 (&b)[SJ]) {
+      if constexpr (TL::MAPPED) {
+        while (k >= kend && ++iv < kr.n) {
+          const int2 I = kr.at(iv);
+          k = __builtin_amdgcn_readfirstlane(I.x);
+          kend = __builtin_amdgcn_readfirstlane(I.y);
+        }
+      }
+      if (k >= kend) return;
+      const bool in = k + lk < kend;
+      oa.template load<NI>(k, in, lk, a);
+      ob.template load<NJ>(k, in, lk, b);
+      k += 4;
+      ++left;
+    };
+#pragma unroll
+    for (int p = 0; p < PF; ++p) load(va[p], vb[p]);
+    while (left > 0) {
+#pragma unroll
+      for (int p = 0; p < PF; ++p) {
+        if (left <= 0) break;
+        double as[NI], bs[NJ];
+#pragma unroll
+        for (int i = 0; i < NI; ++i) as[i] = fma(ca, va[p][i].y, va[p][i].x);
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) bs[j] = fma(cb, vb[p][j].y, vb[p][j].x);
+#pragma unroll
+        for (int i = 0; i < NI; ++i)
+#pragma unroll
+          for (int j = 0; j < NJ; ++j) {
+            p1[i][j] = mfma(va[p][i].x, vb[p][j].x, p1[i][j]);
+            p2[i][j] = mfma(va[p][i].y, vb[p][j].y, p2[i][j]);
+            p3[i][j] = mfma(as[i], bs[j], p3[i][j]);
+          }
+        --left;
+        load(va[p], vb[p]);
+      }
+    }
+  };
+  if constexpr (TL::MAPPED) {
+    using One = std::integral_constant<int, 1>;
+    using Two = std::integral_constant<int, 2>;
+    if (ni == 2 && nj == 2) multiply(Two{}, Two{});
+    else if (ni == 2) multiply(Two{}, One{});
+    else if (nj == 2) multiply(One{}, Two{});
+    else multiply(One{}, One{});
+  } else {
+    multiply(std::integral_constant<int, SI>{}, std::integral_constant<int, SJ>{});
+  }
+  // p2 holds the product of the stored imaginary parts
+  double2 x[E];
+#pragma unroll
+  for (int i = 0; i < SI; ++i)
+#pragma unroll
+    for (int j = 0; j < SJ; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const double q1 = p1[i][j][r], q2 = ca * cb * p2[i][j][r];
+        x[(i * SJ + j) * 4 + r] = double2{q1 - q2, p3[i][j][r] - q1 - q2};
+      }
+  double2* red = reinterpret_cast<double2*>(direct_lds) + lane;   // [part][entry][lane]
+  if (parts > 1) {
+#pragma unroll
+    for (int e = 0; e < E; ++e) red[(wk * E + e) * 64] = x[e];
+    __syncthreads();
+  }
+  const bool has_beta = (br != 0.0) || (bi != 0.0);
+  double2* Cb = reinterpret_cast<double2*>(C) + job.bz * sc + job.split * sps;
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    const int i = e / 4 / SJ, j = e / 4 % SJ, r = e % 4;
+    if (i >= ni || j >= nj) continue;
+    double2 v = x[e];
+    if (parts > 1) {
+      if (e % parts != wk) continue;   // the parts' waves share the sums and stores
+      v = double2{0.0, 0.0};
+      for (int w = 0; w < parts; ++w) {
+        const double2 u = red[(w * E + e) * 64];
+        v.x += u.x;
+        v.y += u.y;
+      }
+    }
+    // row of the MFMA's result r: lane / 16 + 4 r, column lane % 16
+    const int lm = ro[i] + lk + 4 * r, ln = co[j] + lr;
+    const int gm = job.m0 + lm, gn = job.n0 + ln;
+    if (gm < M && gn < N && lm >= job.r0 && lm < job.r1 && ln >= job.c0 && ln < job.c1) {
+      double2 o{ar * v.x - ai * v.y, ar * v.y + ai * v.x};
+      if (has_beta) {
+        const double2 old = Cb[(long long)gm * ldc + gn];
+        o.x += br * old.x - bi * old.y;
+        o.y += br * old.y + bi * old.x;
+      }
+      Cb[(long long)gm * ldc + gn] = o;
+    }
+  }
 }
 
 // Deterministic split-K reduction: C = alpha * sum_s P[s] + beta * C.
@@ -851,19 +828,6 @@ __global__ void splitk_reduce_map_kernel(const T* __restrict__ P, int batch, lon
     o.y += br * old.y + bi * old.x;
   }
   *Cc = o;
-}
-
-// Number of K splits: about one workgroup per CU when the output has few
-// tiles (Gram matrices, back transformations: 16-64 tiles would leave most
-// of the 256 CUs idle), each split keeping >= 64 of K.  The partial products
-// (S M N complex) mostly stay in the last-level cache.
-inline int choose_splits(int M, int N, int K, int batch, size_t ws_bytes, size_t cbytes) {
-  const long long tiles = (long long)((M + BM - 1) / BM) * ((N + BN - 1) / BN) * batch;
-  if (batch != 1 || ws_bytes == 0 || tiles >= 256 || K < 128) return 1;
-  int S = (int)std::min<long long>((256 + tiles - 1) / tiles, K / 64);
-  S = std::min(S, 32);
-  while (S > 1 && (size_t)S * M * N * cbytes > ws_bytes) --S;
-  return std::max(S, 1);
 }
 
 // Compute mode of the complex64 GEMMs on the calling host thread (kern::set_float_mode):
@@ -988,12 +952,111 @@ void choose_split_tile(int M, int N, int K, int batch, size_t ws_bytes, int* til
   }
 }
 
-template <bool TA, bool CA, bool TB, bool CB, int TAG>
-void launch_fp64(dim3 grid, const Product<double>& p, double* C, long long ldc, long long sc, bool plain, int S, int Kc,
-                 long long sps, const int4* kit, const int2* kiv) {
-  hipLaunchKernelGGL((gemm_kernel<double, TA, CA, TB, CB, TAG>), grid, dim3(gemm_threads<double>()), 0, p.s, p.M, p.N,
-                     p.K, plain ? 1.0 : p.ar, plain ? 0.0 : p.ai, p.A, p.lda, p.sa, p.B, p.ldb, p.sb,
-                     plain ? 0.0 : p.br, plain ? 0.0 : p.bi, C, ldc, sc, S, Kc, sps, kit, kiv);
+// Number of K splits of an FP64 product: about one 64 x 64 tile per CU when the
+// output has few (Gram matrices, back transformations), each keeping >= 64 of
+// K.  ws_bytes: room for the partial products.
+inline int choose_splits(int M, int N, int K, int batch, size_t ws_bytes) {
+  const long long tiles = (long long)((M + BM - 1) / BM) * ((N + BN - 1) / BN) * batch;
+  if (batch != 1 || ws_bytes == 0 || tiles >= 256 || K < 128) return 1;
+  int S = (int)std::min<long long>((256 + tiles - 1) / tiles, K / 64);
+  S = std::min(S, 32);
+  while (S > 1 && (size_t)S * M * N * sizeof(double2) > ws_bytes) --S;
+  return std::max(S, 1);
+}
+
+using Direct0 = DirectTile<2, 2, 2, 2, 1, 6>;
+using Direct1 = DirectTile<2, 1, 2, 2, 1, 4>;
+using Direct2 = DirectTile<1, 1, 2, 2, 1, 8>;
+using Direct3 = DirectTile<2, 2, 1, 1, 8, 4>;
+using Direct4 = DirectTile<2, 1, 1, 1, 8, 4>;
+using Direct5 = DirectTile<1, 1, 1, 1, 16, 8>;
+using DirectMapped = DirectTile<2, 2, 2, 2, 1, 4, true>;
+using DirectWide = DirectTile<2, 2, 2, 2, 1, 2, true, true>;
+constexpr int N_DIRECT = 6;
+
+// Estimated time in us of an M x N x K product in S parts on a tile (infinite
+// where the tile takes no such parts), from what the busiest CU works off: 80
+// ns a piece and step on each SIMD, and the operand loads, which cost 10 us a
+// MiB and CU where k is the contiguous index (16 rows a load) and 6 where it
+// is not, about 0.6 of that in the pieces of 32 x 32 and half as much again
+// with one wave a SIMD.  Blocks of two or three waves land unevenly on the
+// SIMDs.  A second launch sums the partial products of a split grid.
+template <class TL, bool TA, bool TB> double direct_cost(int M, int N, int K, int batch, int S, bool in_block) {
+  if (in_block ? S > TL::PARTS : S > 1 && TL::PARTS > 1) return 1e30;
+  const double mn = (double)M * N * sizeof(double2);
+  const double blocks = (double)((M + TL::TM - 1) / TL::TM) * ((N + TL::TN - 1) / TL::TN) * (in_block ? 1 : S) * batch;
+  const double per_cu = std::ceil(blocks / 256.0), waves = TL::WM * TL::WN * (in_block ? S : 1);
+  const double steps = std::ceil(std::ceil((double)K / S) / 4);
+  double per_simd = std::ceil(per_cu * waves / 4.0);
+  if (waves == 2.0 || waves == 3.0) per_simd = std::max(per_simd, 2.0);
+  const double mib = per_cu * waves * steps / 1024.0;
+  const double load = mib * (TL::SI * (TA ? 6.0 : 10.0) + TL::SJ * (TB ? 10.0 : 6.0)) *
+                      (TL::SI * TL::SJ == 4 ? 0.6 : 1.0) * (per_simd > 1.0 ? 1.0 : 1.5);
+  double us = 4.5 + per_simd * steps * TL::SI * TL::SJ * 0.08 + load;
+  if (S > 1) us += in_block ? per_cu * 0.03 * S * TL::SI * TL::SJ : 4.0 + (2 * S + 1) * mn / 8e6;
+  return us;
+}
+
+// Tile of a dense FP64 product of S parts: the least estimated time, from what
+// the busiest CU works off.  Large outputs take the 64 x 64 tile (fewest
+// operand bytes per output); smaller ones take smaller tiles, which fill more
+// of the 256 CUs, with the parts of K on a block's waves instead of a second
+// launch.  Measured with 64 x 64 tiles through LDS / on these tiles: 256 x 64 x
+// 32 7.5 / 3.7 us, 64 x 32 x 256 14.1 / 5.4, 768 x 192 x 96 15.5 / 7.0, 192 x
+// 96 x 768 17.2 / 11, 462 x 256 x 256 18.4 / 8.4, 512 x 256 x 2048 43.5 / 38.8,
+// 2048 x 512 x 256 37.3 / 34.3, 5000 x 1000 x 1000 652 / 511.
+template <bool TA, bool TB>
+void choose_direct_tile(int M, int N, int K, int batch, int S, int* tile, bool* in_block) {
+  double best = 1e29;
+  *tile = 0;
+  *in_block = false;
+  for (int ib = 0; ib < 2; ++ib) {
+    if (ib && S == 1) break;
+    const double us[N_DIRECT] = {
+        direct_cost<Direct0, TA, TB>(M, N, K, batch, S, ib), direct_cost<Direct1, TA, TB>(M, N, K, batch, S, ib),
+        direct_cost<Direct2, TA, TB>(M, N, K, batch, S, ib), direct_cost<Direct3, TA, TB>(M, N, K, batch, S, ib),
+        direct_cost<Direct4, TA, TB>(M, N, K, batch, S, ib), direct_cost<Direct5, TA, TB>(M, N, K, batch, S, ib)};
+    for (int t = 0; t < N_DIRECT; ++t)
+      if (us[t] < best) {
+        best = us[t];
+        *tile = t;
+        *in_block = ib != 0;
+      }
+  }
+}
+
+// parts > 1: K in parts of Kc on the block's waves
+template <class TL, bool TA, bool TB, int TAG>
+void launch_direct_tile(const Product<double>& p, int n_items, double* C, long long ldc, long long sc, bool plain,
+                        int S, int parts, int Kc, long long sps, const int4* kit, const int2* kiv, int conj) {
+  const dim3 grid = kit ? dim3(n_items)
+                        : dim3((p.N + TL::TN - 1) / TL::TN, (p.M + TL::TM - 1) / TL::TM, S > 1 ? S : p.batch);
+  const size_t lds = parts > 1 ? (size_t)parts * TL::SI * TL::SJ * 256 * sizeof(double2) : 0;
+  if (lds > 64 * 1024) {   // per device, and cheap next to a launch that takes this much
+    HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_direct_kernel<TL, TA, TB, TAG>),
+                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+  }
+  hipLaunchKernelGGL((gemm_direct_kernel<TL, TA, TB, TAG>), grid, dim3(TL::WM * TL::WN * parts * 64), lds, p.s, p.M,
+                     p.N, p.K, plain ? 1.0 : p.ar, plain ? 0.0 : p.ai, p.A, p.lda, p.sa, p.B, p.ldb, p.sb,
+                     plain ? 0.0 : p.br, plain ? 0.0 : p.bi, C, ldc, sc, S, Kc, sps, kit, kiv, conj);
+}
+
+template <bool TA, bool TB, int TAG>
+void launch_direct(const Product<double>& p, int conj, int tile, int n_items, double* C, long long ldc, long long sc,
+                   bool plain, int S, int parts, int Kc, long long sps, const int4* kit, const int2* kiv) {
+  auto go = [&](auto tl) {
+    launch_direct_tile<decltype(tl), TA, TB, TAG>(p, n_items, C, ldc, sc, plain, S, parts, Kc, sps, kit, kiv, conj);
+  };
+  if (p.lda >= LD_WIDE64 || p.ldb >= LD_WIDE64) return go(DirectWide{});
+  if (kit) return go(DirectMapped{});
+  switch (tile) {
+    case 0: return go(Direct0{});
+    case 1: return go(Direct1{});
+    case 2: return go(Direct2{});
+    case 3: return go(Direct3{});
+    case 4: return go(Direct4{});
+    default: return go(Direct5{});
+  }
 }
 
 // TERMS 0: FP64; otherwise complex64 operands as TERMS BF16 terms.
@@ -1001,22 +1064,18 @@ template <typename T, int TERMS, int OA, int OB, int TAG>
 void launch_gemm_mode(const Product<T>& p) {
   constexpr bool TA = (OA == TDVP_OP_T || OA == TDVP_OP_C), CA = (OA == TDVP_OP_C || OA == TDVP_OP_R);
   constexpr bool TB = (OB == TDVP_OP_T || OB == TDVP_OP_C), CB = (OB == TDVP_OP_C || OB == TDVP_OP_R);
-  constexpr int KSTEP = TERMS == 0 ? BK : BKS;
+  constexpr int KSTEP = TERMS == 0 ? 16 : BKS, CONJ = (CA ? 1 : 0) | (CB ? 2 : 0);
   using c2 = typename VT<T>::c2;
   const int M = p.M, N = p.N, K = p.K, batch = p.batch;
   const long long MN = (long long)M * N;
   // S > 1 or `plain`: partial products (alpha 1, beta 0)
   auto launch = [&](int tile, int n_items, T* C, long long ldc, long long sc, bool plain, int S, int Kc, long long sps,
-                    const int4* kit, const int* kiv) {
+                    const int4* kit, const int* kiv, int parts = 1) {
     const int2* iv = reinterpret_cast<const int2*>(kiv);
-    if constexpr (TERMS == 0) {
-      (void)tile;
-      const dim3 grid = kit ? dim3(n_items) : dim3((N + BN - 1) / BN, (M + BM - 1) / BM, S > 1 ? S : batch);
-      launch_fp64<TA, CA, TB, CB, TAG>(grid, p, C, ldc, sc, plain, S, Kc, sps, kit, iv);
-    } else {
-      launch_split<TERMS, TA, TB, TAG>(p, (CA ? 1 : 0) | (CB ? 2 : 0), tile, n_items, C, ldc, sc, plain, S, Kc, sps,
-                                       kit, iv);
-    }
+    if constexpr (TERMS == 0)
+      launch_direct<TA, TB, TAG>(p, CONJ, tile, n_items, C, ldc, sc, plain, S, parts, Kc, sps, kit, iv);
+    else
+      launch_split<TERMS, TA, TB, TAG>(p, CONJ, tile, n_items, C, ldc, sc, plain, S, Kc, sps, kit, iv);
   };
   const kern::KMap* km = tl_kmap;
   if (km && km->batch == batch) {
@@ -1039,14 +1098,24 @@ void launch_gemm_mode(const Product<T>& p) {
     return;
   }
   int S, tile = 0;
-  if constexpr (TERMS == 0) S = choose_splits(M, N, K, batch, p.ws_bytes, sizeof(c2));
-  else choose_split_tile<TERMS>(M, N, K, batch, p.ws_bytes, &tile, &S);
+  bool in_block = false;
+  if constexpr (TERMS == 0) {
+    S = choose_splits(M, N, K, batch, p.ws_bytes);
+    choose_direct_tile<TA, TB>(M, N, K, batch, S, &tile, &in_block);
+    if (p.lda >= LD_WIDE64 || p.ldb >= LD_WIDE64) in_block = false;
+  } else {
+    choose_split_tile<TERMS>(M, N, K, batch, p.ws_bytes, &tile, &S);
+  }
   if (S == 1) {
     launch(tile, 0, p.C, p.ldc, p.sc, false, 1, std::max(K, 1), 0, nullptr, nullptr);
     return;
   }
   const int Kc = ((K + S - 1) / S + KSTEP - 1) / KSTEP * KSTEP;
   const int Sx = (K + Kc - 1) / Kc;
+  if (in_block) {
+    launch(tile, 0, p.C, p.ldc, p.sc, false, 1, Kc, 0, nullptr, nullptr, Sx);
+    return;
+  }
   T* P = static_cast<T*>(p.ws);
   launch(tile, 0, P, N, 0, true, Sx, Kc, MN, nullptr, nullptr);
   hipLaunchKernelGGL(splitk_reduce_kernel<T>, dim3((unsigned)((MN + 255) / 256)), dim3(256), 0, p.s, P, Sx,

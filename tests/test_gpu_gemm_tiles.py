@@ -1,7 +1,7 @@
-"""complex64 products on the BF16 matrix cores: edges of the tiles and K steps
-of every tile the dispatch picks, K splits, conjugations, leading dimensions
-past the buffer-addressed range, and operands that have no BF16 terms
-(infinities, NaN, numbers that round to an infinity)."""
+"""Products at the edges of the tiles and K steps of every tile the dispatch
+picks: FP64, and complex64 on the BF16 matrix cores; K splits, conjugations,
+leading dimensions past the buffer-addressed range, and operands that have no
+BF16 terms (infinities, NaN, numbers that round to an infinity)."""
 import numpy as np
 import pytest
 
@@ -11,6 +11,8 @@ pytestmark = pytest.mark.gpu
 # bounds a product of the operands' terms, n the products per output part and k
 # that are added up in FP32 (see test_gpu_kernels; three terms hold an FP32
 # number exactly and leave out at most 3 * 2^-26 of a product).
+# FP64 rounds each of the 3 K + 64 additions and products of the three real sums
+# of a complex product, each sum up to 2 |A||B|.
 C = {"bf16": 2.0 ** -7 + 2.0 ** -16, "bf16x3": 3.1 * 2.0 ** -16, "fp32": 2.0 ** -24}
 N_PRODUCTS = {"bf16": 2, "bf16x3": 6, "fp32": 12}
 
@@ -52,6 +54,42 @@ def test_tiles_steps_and_splits(env, prec, opa, opb, M, N, K):
     bound = (C[prec] + (N_PRODUCTS[prec] * K + 64) * 2.0 ** -24) * S + 2.0 ** -22 * ref.abs()
     err = (Y.to(torch.complex128) - ref).abs()
     assert bool((err <= bound).all()), float((err / bound).max())
+
+
+@pytest.mark.parametrize("opa,opb", [(0, 0), (1, 2), (2, 3), (3, 1)])
+@pytest.mark.parametrize("M,N,K,batch", [(1, 1, 1, 1), (16, 15, 5, 1), (17, 33, 127, 1), (64, 32, 256, 1), (97, 95, 193, 2),
+                                         (193, 95, 771, 1), (31, 470, 1030, 1), (500, 513, 514, 1), (129, 257, 2050, 1),
+                                         (2049, 511, 130, 1), (1100, 1090, 61, 1), (700, 130, 90, 3)])
+def test_fp64_tiles_and_parts(env, opa, opb, M, N, K, batch):
+    T, torch, ctx = env
+    g = torch.Generator(device="cuda").manual_seed(M + N + K)
+    rand = lambda *s: torch.randn(*s, dtype=torch.complex128, device="cuda", generator=g)  # noqa: E731
+    A = rand(batch, *((M, K) if opa in (0, 3) else (K, M)))
+    B = rand(batch, *((K, N) if opb in (0, 3) else (N, K)))
+    Y0 = rand(batch, M, N)
+    Y = Y0.clone()
+    T.tdvp_gemm(ctx, opa, opb, M, N, K, 0.5 - 2j, A, A.shape[2], M * K, B, B.shape[2], K * N, -1.0, Y, N, M * N, batch)
+    for b in range(batch):
+        a, c = _op(A[b], opa), _op(B[b], opb)
+        ref = (0.5 - 2j) * (a @ c) - Y0[b]
+        bound = (2 * (3 * K + 64) * 2.5 * (_mag(a) @ _mag(c)) + 8 * Y0[b].abs()) * 2.0 ** -53
+        assert bool(((Y[b] - ref).abs() <= bound).all())
+
+
+@pytest.mark.parametrize("opa,opb", [(0, 0), (2, 3)])
+def test_fp64_wide_leading_dimension(env, opa, opb):
+    # a leading dimension of 2^21 complex128: plain 64-bit addresses
+    T, torch, ctx = env
+    M, N, K, ld = 40, 33, 37, 1 << 21
+    g = torch.Generator(device="cuda").manual_seed(3)
+    rand = lambda *s: torch.randn(*s, dtype=torch.complex128, device="cuda", generator=g)  # noqa: E731
+    A, B = rand(*((M, K) if opa == 0 else (K, M))), rand(K, N)
+    wide = torch.empty(A.shape[0], ld, dtype=torch.complex128, device="cuda")
+    wide[:, : A.shape[1]] = A
+    Y, Y2 = (torch.empty(M, N, dtype=torch.complex128, device="cuda") for _ in range(2))
+    T.tdvp_gemm(ctx, opa, opb, M, N, K, 1.0, wide, ld, 0, B, N, 0, 0.0, Y, N, 0, 1)
+    T.tdvp_gemm(ctx, opa, opb, M, N, K, 1.0, A, A.shape[1], 0, B, N, 0, 0.0, Y2, N, 0, 1)
+    assert torch.equal(Y, Y2)
 
 
 @pytest.mark.parametrize("prec", ["fp32", "bf16", "bf16x3"])
