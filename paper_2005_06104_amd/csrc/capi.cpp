@@ -807,9 +807,6 @@ tdvp_status tdvp_heff_apply_u1(tdvp_ctx ctx, int prec, int ml, int wl, int wr, i
     const kern::KMap g1 = mc.use(e1), g2 = mc.use(e2);
     ProdMaps pm{&g1, &g2, e1.exact_flops + e2.exact_flops};
     kern::WCharges wc = wc_of(cmap_wstage(mc, ql, qr, qwl, qwr), ml, mr, wl);
-    // the stage stores only the outputs allowed by charge into cleared memory
-    kern::zfill(ctx->stream, w2, zc(0.0, 0.0), 2LL * ml * wr * mr, prec == TDVP_FP64 ? 16 : 8);
-    wc.zeros_kept = 1;
     pm.wc = &wc;
     if (prec == TDVP_FP64) heff_apply<double>(ctx, tb, ml, wl, wr, mr, L, Rt, C, Y, w1, w2, nullptr, sk, pm);
     else heff_apply<float>(ctx, tb, ml, wl, wr, mr, L, Rt, C, Y, w1, w2, nullptr, sk, pm);

@@ -976,11 +976,12 @@ constexpr int N_DIRECT = 6;
 
 // Estimated time in us of an M x N x K product in S parts on a tile (infinite
 // where the tile takes no such parts), from what the busiest CU works off: 80
-// ns a piece and step on each SIMD, and the operand loads, which cost 10 us a
-// MiB and CU where k is the contiguous index (16 rows a load) and 6 where it
-// is not, about 0.6 of that in the pieces of 32 x 32 and half as much again
-// with one wave a SIMD.  Blocks of two or three waves land unevenly on the
-// SIMDs.  A second launch sums the partial products of a split grid.
+// ns a piece and step on each SIMD, and the operand loads.  These cost 6 us a
+// MiB and CU where k is not the contiguous index, 10 where it is (a load meets
+// 16 rows), 16 where it is for both operands; half as much again with one wave
+// a SIMD (not in the last case), 0.6 of it in pieces of 32 x 32.  Blocks of two
+// or three waves land unevenly on the SIMDs.  A second launch sums the partial
+// products of a split grid.
 template <class TL, bool TA, bool TB> double direct_cost(int M, int N, int K, int batch, int S, bool in_block) {
   if (in_block ? S > TL::PARTS : S > 1 && TL::PARTS > 1) return 1e30;
   const double mn = (double)M * N * sizeof(double2);
@@ -990,8 +991,10 @@ template <class TL, bool TA, bool TB> double direct_cost(int M, int N, int K, in
   double per_simd = std::ceil(per_cu * waves / 4.0);
   if (waves == 2.0 || waves == 3.0) per_simd = std::max(per_simd, 2.0);
   const double mib = per_cu * waves * steps / 1024.0;
-  const double load = mib * (TL::SI * (TA ? 6.0 : 10.0) + TL::SJ * (TB ? 10.0 : 6.0)) *
-                      (TL::SI * TL::SJ == 4 ? 0.6 : 1.0) * (per_simd > 1.0 ? 1.0 : 1.5);
+  constexpr bool both = !TA && TB;
+  constexpr double wa = both ? 16.0 : TA ? 6.0 : 10.0, wb = both ? 16.0 : TB ? 10.0 : 6.0;
+  const double load = mib * (TL::SI * wa + TL::SJ * wb) * (TL::SI * TL::SJ == 4 ? 0.6 : 1.0) *
+                      (per_simd > 1.0 || both ? 1.0 : 1.5);
   double us = 4.5 + per_simd * steps * TL::SI * TL::SJ * 0.08 + load;
   if (S > 1) us += in_block ? per_cu * 0.03 * S * TL::SI * TL::SJ : 4.0 + (2 * S + 1) * mn / 8e6;
   return us;
@@ -1152,65 +1155,99 @@ void dispatch_b(hipStream_t s, int opb, int M, int N, int K, zc alpha, const voi
 }
 
 // ---------------------------------------------------------------- W apply
-constexpr int WQ = 64;      // q extent per block
+// Memory bound.  An MPO tensor holds about one nonzero per input channel, so an
+// input entry is read once or twice: each wave takes output channels of one row
+// p and 64 V columns (V entries a lane, 16 bytes) and reads its inputs straight
+// from memory, the coefficients through scalar loads.
+// chi = 1024, w = 20, complex64, dense: 108 us, 6.2 TB/s (through LDS, eight
+// bytes a lane: 184 us).
 constexpr int WNT = 256;
 constexpr int WMAX_CH = 256;   // channels (MPO index x physical index) of a charged stage
 
-template <typename T>
+typedef float f4u __attribute__((ext_vector_type(4), aligned(8)));
+
+template <typename T, int V, bool CHARGED>
 __global__ __launch_bounds__(WNT) void wapply_kernel(const T* __restrict__ in, T* __restrict__ out, long long nQ,
-                                                      long long isP, long long isQ, long long is1,
-                                                      long long is2, long long osP, long long osQ,
-                                                      long long os1, long long os2,
-                                                      const int* __restrict__ rowptr,
-                                                      const int* __restrict__ col,
-                                                      const double2* __restrict__ val, int n_in,
+                                                      long long isP, long long is1, long long is2, long long osP,
+                                                      long long os1, long long os2, const int* __restrict__ rowptr,
+                                                      const int* __restrict__ col, const double2* __restrict__ val,
                                                       int n_out, kern::WCharges wc) {
   using c2 = typename VT<T>::c2;
-  extern __shared__ unsigned char smem_raw[];
-  c2* lds = reinterpret_cast<c2*>(smem_raw);  // [n_in][WQ]
-  // charge difference of each column of the block and the channels' own
-  // (charged contractions only)
-  __shared__ int dq[WQ];
-  __shared__ int din_s[WMAX_CH], dout_s[WMAX_CH];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const long long p = blockIdx.y;
-  const long long q0 = (long long)blockIdx.x * WQ;
-  const c2* inb = reinterpret_cast<const c2*>(in);
-  c2* outb = reinterpret_cast<c2*>(out);
-  const bool charged = wc.ql != nullptr;
-  if (charged) {
-    for (int t = threadIdx.x; t < WQ; t += WNT) dq[t] = q0 + t < nQ ? wc.qr[q0 + t] - wc.ql[p] : 0;
-    for (int t = threadIdx.x; t < n_in; t += WNT) din_s[t] = wc.din[t];
-    for (int t = threadIdx.x; t < n_out; t += WNT) dout_s[t] = wc.dout[t];
-    __syncthreads();
+  const long long q = ((long long)blockIdx.x * 64 + (threadIdx.x & 63)) * V;
+  if (q >= nQ) return;
+  const c2* inb = reinterpret_cast<const c2*>(in) + p * isP + q;
+  c2* outb = reinterpret_cast<c2*>(out) + p * osP + q;
+  const bool whole = q + V <= nQ;
+  // charge difference of the lane's columns (charged contractions only); an
+  // output of another charge is an exact zero, stored unless the output already
+  // holds it, and an output's inputs all have its charge
+  int dq[V];
+  if constexpr (CHARGED) {
+    const int ql = wc.ql[p];
+#pragma unroll
+    for (int v = 0; v < V; ++v) dq[v] = wc.qr[q + v < nQ ? q + v : q] - ql;
   }
-  for (int idx = threadIdx.x; idx < n_in * WQ; idx += WNT) {
-    const int c = idx / WQ, q = idx % WQ;
-    c2 v;
-    v.x = T(0); v.y = T(0);
-    if (q0 + q < nQ && (!charged || din_s[c] == dq[q]))
-      v = inb[p * isP + (q0 + q) * isQ + (c >> 1) * is1 + (c & 1) * is2];
-    lds[idx] = v;
-  }
-  __syncthreads();
-  for (int idx = threadIdx.x; idx < n_out * WQ; idx += WNT) {
-    const int o = idx / WQ, q = idx % WQ;
-    if (q0 + q >= nQ) continue;
-    T sr = T(0), si = T(0);
-    // an output of another charge is an exact zero (+0, as the sum of the
-    // zero inputs would give), stored unless the output already holds it
-    const bool zero = charged && dout_s[o] != dq[q];
-    if (zero && wc.zeros_kept) continue;
-    const int e_end = zero ? rowptr[o] : rowptr[o + 1];
-    for (int e = rowptr[o]; e < e_end; ++e) {
-      const double2 w = val[e];
-      const c2 x = lds[col[e] * WQ + q];
-      sr += T(w.x) * x.x - T(w.y) * x.y;
-      si += T(w.x) * x.y + T(w.y) * x.x;
+  for (int o = blockIdx.z * (WNT / 64) + wave; o < n_out; o += gridDim.z * (WNT / 64)) {
+    bool on[V], any = false, all = whole;
+#pragma unroll
+    for (int v = 0; v < V; ++v) {
+      on[v] = (V == 1 || v == 0 || whole) && (!CHARGED || wc.dout[o] == dq[v]);
+      any = any || on[v];
+      all = all && on[v];
     }
-    c2 r;
-    r.x = sr;
-    r.y = si;
-    outb[p * osP + (q0 + q) * osQ + (o >> 1) * os1 + (o & 1) * os2] = r;
+    T sr[V], si[V];
+#pragma unroll
+    for (int v = 0; v < V; ++v) sr[v] = si[v] = T(0);
+    if (any) {
+      const int e1 = rowptr[o + 1];
+      for (int e = rowptr[o]; e < e1; ++e) {
+        const double2 w = val[e];
+        const int c = col[e];
+        const c2* x = inb + (c >> 1) * is1 + (c & 1) * is2;
+        c2 xv[V];
+        if constexpr (V == 2) {
+          if (whole) {
+            const f4u t = *reinterpret_cast<const f4u*>(x);
+            xv[0].x = t.x;
+            xv[0].y = t.y;
+            xv[1].x = t.z;
+            xv[1].y = t.w;
+          } else {
+            xv[0] = xv[1] = x[0];
+          }
+        } else {
+          xv[0] = x[0];
+        }
+#pragma unroll
+        for (int v = 0; v < V; ++v) {
+          sr[v] += T(w.x) * xv[v].x - T(w.y) * xv[v].y;
+          si[v] += T(w.x) * xv[v].y + T(w.y) * xv[v].x;
+        }
+      }
+    }
+    c2* y = outb + (o >> 1) * os1 + (o & 1) * os2;
+    const bool keep = CHARGED && wc.zeros_kept;
+    if constexpr (V == 2) {
+      if (all || (whole && !keep)) {
+        f4u t;
+        t.x = on[0] ? sr[0] : T(0);
+        t.y = on[0] ? si[0] : T(0);
+        t.z = on[1] ? sr[1] : T(0);
+        t.w = on[1] ? si[1] : T(0);
+        *reinterpret_cast<f4u*>(y) = t;
+        continue;
+      }
+    }
+#pragma unroll
+    for (int v = 0; v < V; ++v)
+      if ((v == 0 || whole) && (on[v] || !keep)) {
+        c2 r;
+        r.x = on[v] ? sr[v] : T(0);
+        r.y = on[v] ? si[v] : T(0);
+        y[v] = r;
+      }
   }
 }
 
@@ -1710,18 +1747,29 @@ void wapply(hipStream_t s, const WTable& t, const void* in, void* out, long long
             long long os1, long long os2, const WCharges* wc) {
   if (nP <= 0 || nQ <= 0) return;
   if (nP > 65535) TDVP_THROW(TDVP_ERR_ARG, "wapply: P extent too large");
-  dim3 grid((unsigned)((nQ + WQ - 1) / WQ), (unsigned)nP);
-  const size_t sh = (size_t)t.n_in_ch * WQ * sizeof(typename VT<T>::c2);
-  if (sh > 64 * 1024) TDVP_THROW(TDVP_ERR_ARG, "wapply: MPO bond dimension too large");
+  if (isQ != 1 || osQ != 1) TDVP_THROW(TDVP_ERR_ARG, "wapply: columns must be contiguous");
+  if ((size_t)t.n_in_ch * 64 * sizeof(typename VT<T>::c2) > 64 * 1024)
+    TDVP_THROW(TDVP_ERR_ARG, "wapply: MPO bond dimension too large");
   WCharges w{nullptr, nullptr, nullptr, nullptr, 0};
   if (wc) {
     if (t.n_in_ch > WMAX_CH || t.n_out_ch > WMAX_CH) TDVP_THROW(TDVP_ERR_ARG, "wapply: too many charged channels");
     if (!wc->ql || !wc->qr || !wc->din || !wc->dout) TDVP_THROW(TDVP_ERR_ARG, "wapply: incomplete charge table");
     w = *wc;
   }
-  hipLaunchKernelGGL(wapply_kernel<T>, grid, dim3(WNT), sh, s, static_cast<const T*>(in), static_cast<T*>(out),
-                     nQ, isP, isQ, is1, is2, osP, osQ, os1, os2, t.rowptr, t.col,
-                     reinterpret_cast<const double2*>(t.val), t.n_in_ch, t.n_out_ch, w);
+  // about 2048 blocks of four waves fill the device; fewer rows and columns:
+  // the output channels are dealt over the grid as well
+  constexpr int V = sizeof(T) == 8 ? 1 : 2, WAVES = WNT / 64;
+  const long long gx = (nQ + 64 * V - 1) / (64 * V);
+  const long long gz = std::max<long long>(
+      1, std::min<long long>((2048 + gx * nP - 1) / (gx * nP), (t.n_out_ch + WAVES - 1) / WAVES));
+  const dim3 grid((unsigned)gx, (unsigned)nP, (unsigned)gz);
+  auto go = [&](auto charged) {
+    hipLaunchKernelGGL((wapply_kernel<T, V, decltype(charged)::value>), grid, dim3(WNT), 0, s,
+                       static_cast<const T*>(in), static_cast<T*>(out), nQ, isP, is1, is2, osP, os1, os2, t.rowptr,
+                       t.col, reinterpret_cast<const double2*>(t.val), t.n_out_ch, w);
+  };
+  if (wc) go(std::true_type{});
+  else go(std::false_type{});
   HIP_CHECK(hipGetLastError());
 }
 template void wapply<double>(hipStream_t, const WTable&, const void*, void*, long long, long long, long long,
