@@ -85,6 +85,7 @@ void tdvp_ctx_s::destroy_workers() {
     w->destroy_maps();
     w->destroy_uploads();
     w->dfree(w->split_ws);
+    w->dfree(w->call_tables);
     if (w->stream) (void)hipStreamSynchronize(w->stream);
     if (w->hstage) (void)hipHostFree(w->hstage);
     for (hipEvent_t e : w->ev_stage)
@@ -278,9 +279,10 @@ std::vector<zc> host_W(const double* W, int wl, int wr) {
 
 namespace {
 
+// mode: the table the call contracts with (0 F, 1 B; W_host null: none)
 template <class F>
-tdvp_status kernel_call(tdvp_ctx ctx, int prec, int ml, int wl, int wr, int mr, const double* W_host, void* workspace,
-                        F&& f) {
+tdvp_status kernel_call(tdvp_ctx ctx, int prec, int ml, int wl, int wr, int mr, const double* W_host, int mode,
+                        void* workspace, F&& f) {
   if (!ctx) return TDVP_ERR_ARG;
   return guarded(ctx, [&] {
     ARG_CHECK(prec >= TDVP_FP64 && prec <= TDVP_BF16X3_FP32ACC, "unknown precision");
@@ -289,15 +291,17 @@ tdvp_status kernel_call(tdvp_ctx ctx, int prec, int ml, int wl, int wr, int mr, 
     const int cb = prec == TDVP_FP64 ? 16 : 8;
     const size_t half = (size_t)2 * ml * mr * std::max(wl, wr) * cb;
     const size_t split = (size_t)32 * ml * mr * cb;  // split-K partial products
-    DBuf ws(ctx), tab(ctx);
+    DBuf ws(ctx);
     char* w1;
     if (workspace) w1 = static_cast<char*>(workspace);
     else w1 = static_cast<char*>(ws.ensure(2 * half + split));
+    // the tables go through a pinned buffer, so the call need not wait for the
+    // stream (a pageable copy and a wait took 27 of 57 us at chi = 32)
     SiteTables tb{};
-    if (W_host) tb = upload_tables(ctx, host_W(W_host, wl, wr), wl, wr, tab);
-    kern::FloatModeScope mode(kern::float_mode_of(prec));
+    if (W_host) tb = upload_call_tables(ctx, host_W(W_host, wl, wr), wl, wr, mode);
+    kern::FloatModeScope fmode(kern::float_mode_of(prec));
     f(tb, w1, w1 + half, SplitWS{w1 + 2 * half, split});
-    if (!workspace || W_host) ctx->sync();  // keep temporaries alive until the kernels finish
+    if (!workspace) ctx->sync();  // keep the workspace alive until the kernels finish
   });
 }
 }  // namespace
@@ -352,6 +356,7 @@ void tdvp_ctx_destroy(tdvp_ctx ctx) {
   ctx->destroy_maps();
   ctx->destroy_uploads();
   ctx->dfree(ctx->split_ws);
+  ctx->dfree(ctx->call_tables);
   (void)hipStreamSynchronize(ctx->stream);
   if (ctx->hstage) (void)hipHostFree(ctx->hstage);
   for (hipEvent_t e : ctx->ev_stage)
@@ -778,7 +783,7 @@ tdvp_status tdvp_cholesky(tdvp_ctx ctx, int n, const void* G, void* L, void* Lin
 tdvp_status tdvp_heff_apply(tdvp_ctx ctx, int prec, int ml, int wl, int wr, int mr, const double* W_host,
                             const void* L, const void* Rt, const void* C, void* Y, void* workspace) {
   if (!W_host) return TDVP_ERR_ARG;
-  return kernel_call(ctx, prec, ml, wl, wr, mr, W_host, workspace,
+  return kernel_call(ctx, prec, ml, wl, wr, mr, W_host, 0, workspace,
                      [&](const SiteTables& tb, void* w1, void* w2, SplitWS sk) {
     if (prec == TDVP_FP64) heff_apply<double>(ctx, tb, ml, wl, wr, mr, L, Rt, C, Y, w1, w2, nullptr, sk);
     else heff_apply<float>(ctx, tb, ml, wl, wr, mr, L, Rt, C, Y, w1, w2, nullptr, sk);
@@ -789,7 +794,7 @@ tdvp_status tdvp_heff_apply_u1(tdvp_ctx ctx, int prec, int ml, int wl, int wr, i
                                const int32_t* charges_l, const int32_t* charges_r, const int32_t* qw_l,
                                const int32_t* qw_r, const void* L, const void* Rt, const void* C, void* Y) {
   if (!W_host || !charges_l || !charges_r || !qw_l || !qw_r) return TDVP_ERR_ARG;
-  return kernel_call(ctx, prec, ml, wl, wr, mr, W_host, nullptr,
+  return kernel_call(ctx, prec, ml, wl, wr, mr, W_host, 0, nullptr,
                      [&](const SiteTables& tb, void* w1, void* w2, SplitWS sk) {
     const std::vector<int> ql(charges_l, charges_l + ml), qr(charges_r, charges_r + mr);
     const std::vector<int> qwl(qw_l, qw_l + wl), qwr(qw_r, qw_r + wr);
@@ -815,7 +820,7 @@ tdvp_status tdvp_heff_apply_u1(tdvp_ctx ctx, int prec, int ml, int wl, int wr, i
 
 tdvp_status tdvp_keff_apply(tdvp_ctx ctx, int prec, int ml, int w, int mr, const void* L, const void* Rt,
                             const void* X, void* Y, void* workspace) {
-  return kernel_call(ctx, prec, ml, w, w, mr, nullptr, workspace, [&](const SiteTables&, void* w1, void*, SplitWS sk) {
+  return kernel_call(ctx, prec, ml, w, w, mr, nullptr, 0, workspace, [&](const SiteTables&, void* w1, void*, SplitWS sk) {
     if (prec == TDVP_FP64) keff_apply<double>(ctx, ml, w, mr, L, Rt, X, Y, w1, sk);
     else keff_apply<float>(ctx, ml, w, mr, L, Rt, X, Y, w1, sk);
   });
@@ -824,7 +829,7 @@ tdvp_status tdvp_keff_apply(tdvp_ctx ctx, int prec, int ml, int w, int mr, const
 tdvp_status tdvp_env_left(tdvp_ctx ctx, int prec, int ml, int wl, int wr, int mr, const double* W_host,
                           const void* L, const void* A, void* Lout, void* workspace) {
   if (!W_host) return TDVP_ERR_ARG;
-  return kernel_call(ctx, prec, ml, wl, wr, mr, W_host, workspace,
+  return kernel_call(ctx, prec, ml, wl, wr, mr, W_host, 0, workspace,
                      [&](const SiteTables& tb, void* w1, void* w2, SplitWS sk) {
     if (prec == TDVP_FP64) env_left<double>(ctx, tb, ml, wl, wr, mr, L, A, Lout, w1, w2, sk);
     else env_left<float>(ctx, tb, ml, wl, wr, mr, L, A, Lout, w1, w2, sk);
@@ -834,7 +839,7 @@ tdvp_status tdvp_env_left(tdvp_ctx ctx, int prec, int ml, int wl, int wr, int mr
 tdvp_status tdvp_env_right(tdvp_ctx ctx, int prec, int ml, int wl, int wr, int mr, const double* W_host,
                            const void* Rt, const void* B, void* Rout, void* workspace) {
   if (!W_host) return TDVP_ERR_ARG;
-  return kernel_call(ctx, prec, ml, wl, wr, mr, W_host, workspace,
+  return kernel_call(ctx, prec, ml, wl, wr, mr, W_host, 1, workspace,
                      [&](const SiteTables& tb, void* w1, void* w2, SplitWS sk) {
     if (prec == TDVP_FP64) env_right<double>(ctx, tb, ml, wl, wr, mr, Rt, B, Rout, w1, w2, sk);
     else env_right<float>(ctx, tb, ml, wl, wr, mr, Rt, B, Rout, w1, w2, sk);

@@ -60,6 +60,11 @@ struct tdvp_ctx_s {
     if (!split_ws) split_ws = dalloc(SPLIT_WS_BYTES);
     return split_ws;
   }
+  // MPO tables of the kernel-level calls: grown on demand (at most the tables
+  // of a 32 x 32 MPO tensor), freed with the context.  The stream orders a
+  // call's upload after the kernels that read the one before.
+  void* call_tables = nullptr;
+  size_t call_tables_cap = 0;
   // Pinned host staging for the small results the host branches on (Lanczos
   // coefficients, eigenvalues, check flags): one DMA copy instead of a staged
   // pageable one.  Allocated on first use, freed with the context.

@@ -389,17 +389,21 @@ kern::WTable resolve(const char* base, const TableOffsets& o) {
 
 }  // namespace
 
-SiteTables upload_tables(tdvp_ctx_s* ctx, const std::vector<zc>& W, int wl, int wr, DBuf& buf) {
+SiteTables upload_call_tables(tdvp_ctx_s* ctx, const std::vector<zc>& W, int wl, int wr, int mode) {
   TableBlob blob;
-  TableOffsets f = add_table(blob, W, wl, wr, 0), b = add_table(blob, W, wl, wr, 1), h = add_table(blob, W, wl, wr, 2);
-  buf.ensure(blob.bytes.size());
-  upload(ctx, buf.p, blob.bytes.data(), blob.bytes.size());
-  HIP_CHECK(hipStreamSynchronize(ctx->stream));
-  const char* base = static_cast<const char*>(buf.p);
-  SiteTables t;
-  t.F = resolve(base, f);
-  t.B = resolve(base, b);
-  t.BH = resolve(base, h);
+  const TableOffsets o = add_table(blob, W, wl, wr, mode);
+  if (ctx->call_tables_cap < blob.bytes.size()) {
+    ctx->dfree(ctx->call_tables);
+    ctx->call_tables = nullptr;
+    ctx->call_tables_cap = 0;
+    const size_t cap = std::max<size_t>(blob.bytes.size(), 16384);
+    ctx->call_tables = ctx->dalloc(cap);
+    ctx->call_tables_cap = cap;
+  }
+  ctx->upload_async(ctx->call_tables, blob.bytes.data(), blob.bytes.size());
+  const char* base = static_cast<const char*>(ctx->call_tables);
+  SiteTables t{};
+  (mode == 0 ? t.F : t.B) = resolve(base, o);
   t.nnz = site_nnz(W);
   return t;
 }

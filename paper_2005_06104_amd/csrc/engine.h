@@ -281,9 +281,11 @@ void env_left(tdvp_ctx_s* ctx, const SiteTables& tb, int ml, int wl, int wr, int
 template <typename T>
 void env_right(tdvp_ctx_s* ctx, const SiteTables& tb, int ml, int wl, int wr, int mr, const void* Rt,
                const void* B, void* Rout, void* ws1, void* ws2, SplitWS sk = {}, ProdMaps pm = {});
-// CSR tables for a single host W (kernel-level calls); keeps the device copy in `buf`
-SiteTables upload_tables(tdvp_ctx_s* ctx, const std::vector<zc>& W, int wl, int wr, DBuf& buf);
-// The same tables written into caller-provided device memory (cap bytes at
+// One CSR table (mode 0: F, 1: B) of a single host W for a kernel-level call, in
+// the context's buffer for them: valid until the next such call's, in stream
+// order; does not wait for the stream
+SiteTables upload_call_tables(tdvp_ctx_s* ctx, const std::vector<zc>& W, int wl, int wr, int mode);
+// All three tables of a single host W written into caller-provided device memory (cap bytes at
 // dst, allocates nothing on the device): returns the bytes they take; when
 // that exceeds cap nothing is written and *out is left as it was.
 size_t write_tables(tdvp_ctx_s* ctx, const std::vector<zc>& W, int wl, int wr, void* dst, size_t cap,

@@ -164,28 +164,30 @@ HostMPO build_host_mpo(int N, const tdvp_term* terms, int n_terms, zc c0, zc c1)
 //   BH: out (alpha, s)  <- in (beta, s'),  coef conj(W[alpha,beta,s',s])
 void build_site_csr(const std::vector<zc>& W, int wl, int wr, int mode, std::vector<int>& rowptr,
                     std::vector<int>& col, std::vector<zc>& val) {
+  // counted, then filled: entries of a row in the order (alpha, beta, s', s)
   const int n_out = (mode == 0 ? wr : wl) * 2;
-  std::vector<std::vector<std::pair<int, zc>>> rows(n_out);
-  for (int a = 0; a < wl; ++a)
-    for (int b = 0; b < wr; ++b)
-      for (int sp = 0; sp < 2; ++sp)
-        for (int s = 0; s < 2; ++s) {
-          const zc w = W[(((size_t)a * wr + b) * 2 + sp) * 2 + s];
-          if (w == zc(0.0, 0.0)) continue;
-          if (mode == 0) rows[b * 2 + sp].emplace_back(a * 2 + s, w);
-          else if (mode == 1) rows[a * 2 + sp].emplace_back(b * 2 + s, w);
-          else rows[a * 2 + s].emplace_back(b * 2 + sp, std::conj(w));
-        }
+  auto each = [&](auto&& f) {
+    for (int a = 0; a < wl; ++a)
+      for (int b = 0; b < wr; ++b)
+        for (int sp = 0; sp < 2; ++sp)
+          for (int s = 0; s < 2; ++s) {
+            const zc w = W[(((size_t)a * wr + b) * 2 + sp) * 2 + s];
+            if (w == zc(0.0, 0.0)) continue;
+            if (mode == 0) f(b * 2 + sp, a * 2 + s, w);
+            else if (mode == 1) f(a * 2 + sp, b * 2 + s, w);
+            else f(a * 2 + s, b * 2 + sp, std::conj(w));
+          }
+  };
   rowptr.assign(n_out + 1, 0);
-  col.clear();
-  val.clear();
-  for (int o = 0; o < n_out; ++o) {
-    for (const auto& e : rows[o]) {
-      col.push_back(e.first);
-      val.push_back(e.second);
-    }
-    rowptr[o + 1] = (int)col.size();
-  }
+  each([&](int row, int, zc) { ++rowptr[row + 1]; });
+  for (int o = 0; o < n_out; ++o) rowptr[o + 1] += rowptr[o];
+  col.resize(rowptr[n_out]);
+  val.resize(rowptr[n_out]);
+  std::vector<int> at(rowptr.begin(), rowptr.end() - 1);
+  each([&](int row, int c, zc w) {
+    col[at[row]] = c;
+    val[at[row]++] = w;
+  });
 }
 
 long long site_nnz(const std::vector<zc>& W) {
