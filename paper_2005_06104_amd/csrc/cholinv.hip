@@ -1,19 +1,25 @@
 // Cholesky factorisation G = L L^H of a Hermitian positive definite n x n
 // matrix (n <= 512, row-major complex128) together with L^-1, in one
-// cooperative launch with one workgroup per 16 x 16 block (i, k), k <= i, of
-// the lower triangle (tiled right-looking order, each update applied as soon
-// as its operands exist):
+// cooperative launch over the 16 x 16 blocks (i, k), k <= i, of the lower
+// triangle (tiled right-looking order, each update applied as soon as its
+// operands exist):
 //     L_ik = (G_ik - sum_{j<k} L_ij L_kj^H) (L_kk^-1)^H           k < i,
 //     L_ii = chol(G_ii - sum_{j<i} L_ij L_ij^H),  with L_ii^-1,
 //     Linv_ik = -L_ii^-1 sum_{j=k}^{i-1} L_ij Linv_jk              k < i.
+// The chain along the diagonal is what is sequential, and a block handed from
+// one workgroup to another costs two to three microseconds (write back, flag,
+// poll, fetch).  So one workgroup per matrix runs the whole chain out of LDS,
+// the diagonal blocks and those below them: while one of its waves factorises
+// and inverts block (i, i), two others bring block row i + 1 up to date with
+// L_{i+1,i-1}, and one writes out the step before.  The other blocks have a
+// workgroup each; those of (i, i) and (i, i - 1) hand the chain their sums over
+// j < i - 2, early enough for it not to wait.  n = 300: 273 us (each
+// diagonal block in a workgroup of its own: 335 us).
 // A block is published with a flag once written; a workgroup waits only for
 // blocks of lower column index (or, for L^-1, of lower row index in its own
-// column) and for diagonal blocks, so the waits form chains that end.  Only
-// the diagonal chain (one factorisation and inversion of a 16 x 16 block and
-// two block products per block row) is sequential: small blocks keep its
-// column steps few and short.  Every wait is bounded;
-// one that runs out makes the call report failure.  The factorisation
-// reports failure when a pivot is not positive and finite.
+// column) and for diagonal blocks, so the waits form chains that end.  Every
+// wait is bounded; one that runs out makes the call report failure.  The
+// factorisation reports failure when a pivot is not positive and finite.
 // Block-diagonal matrices (the Gram matrices of charged tensors, whose
 // charge sectors are contiguous) are factorised sector by sector in the same
 // launch: each sector has its own workgroups and flags, and the blocks
@@ -27,7 +33,8 @@
 namespace {
 
 constexpr int CB = 16;            // block size
-constexpr int CNT = 256;          // threads per workgroup
+constexpr int CNT = 256;          // threads of a block's workgroup
+constexpr int CNTD = CNT + 64;    // of the diagonal chain's, and of the launch
 constexpr int CMAXB = 32;         // block rows at most
 constexpr int CENT = CB * CB / CNT;   // tile entries per thread
 constexpr int CPR = CNT / CB;         // threads per tile row
@@ -36,7 +43,7 @@ static_assert(CENT >= 1 && CB * CB == CENT * CNT && NPART >= 1, "tile mapping");
 constexpr int CFLAG = 16;         // one 64-byte line per flag
 constexpr unsigned CSPIN = 1u << 22;
 constexpr int CMAXSEC = 64;       // sectors per launch
-constexpr int CMAXWG = 1024;      // workgroups per launch (all co-resident)
+constexpr int CMAXWG = 768;       // workgroups per launch (all co-resident: three of five waves on each of 256 CUs)
 constexpr size_t CSEC_FLAGS = 2 * CMAXB * CMAXB * CFLAG;   // flag words per sector
 
 struct CholArgs {
@@ -233,8 +240,156 @@ __device__ void diag_chol_inv(double2 (*tS)[CB + 1], double2 (*tY)[CB + 1], int 
   }
 }
 
-__global__ __launch_bounds__(CNT) void cholinv_kernel(CholArgs args) {
+// workgroup barrier for LDS alone: stores to memory stay in flight
+__device__ inline void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// The steps of single waves.  Lane l holds the entries e = l + 64 q of a tile.
+constexpr int WENT = CB * CB / 64;
+
+// wait_flags for one wave and one flag
+__device__ bool wave_wait(const Sec& a, const unsigned* f) {
+  unsigned polls = 0;
+  while (__hip_atomic_load(f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0u) {
+    if (__hip_atomic_load(a.info, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 2 || ++polls > CSPIN) {
+      __hip_atomic_store(a.info, 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      return false;
+    }
+    __builtin_amdgcn_s_sleep(1);
+  }
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+  return true;
+}
+__device__ void wave_load(double2 (&v)[WENT], const double2* M, int ld, int r0, int rows, int c0, int cols, int lane) {
+#pragma unroll
+  for (int q = 0; q < WENT; ++q) {
+    const int r = (lane + 64 * q) / CB, c = lane % CB;
+    v[q] = (r < rows && c < cols) ? M[(size_t)(r0 + r) * ld + c0 + c] : double2{0.0, 0.0};
+  }
+}
+__device__ void wave_store(const double2 (*t)[CB + 1], double2* M, int ld, int r0, int rows, int c0, int cols,
+                           int lane) {
+#pragma unroll
+  for (int q = 0; q < WENT; ++q) {
+    const int r = (lane + 64 * q) / CB, c = lane % CB;
+    if (r < rows && c < cols) M[(size_t)(r0 + r) * ld + c0 + c] = t[r][c];
+  }
+}
+__device__ void wave_to_tile(const double2 (&v)[WENT], double2 (*t)[CB + 1], int lane) {
+#pragma unroll
+  for (int q = 0; q < WENT; ++q) t[(lane + 64 * q) / CB][lane % CB] = v[q];
+}
+// v -= X Y^H
+__device__ void wave_sub(double2 (&v)[WENT], const double2 (*X)[CB + 1], const double2 (*Y)[CB + 1], int lane) {
+#pragma unroll 4
+  for (int k = 0; k < CB; ++k)
+#pragma unroll
+    for (int q = 0; q < WENT; ++q) {
+      const double2 p = cmc(X[(lane + 64 * q) / CB][k], Y[lane % CB][k]);
+      v[q].x += -1.0 * p.x;
+      v[q].y += -1.0 * p.y;
+    }
+}
+
+struct ChainTiles {
+  double2 (*S)[CB + 1];    // the diagonal block, then its factor
+  double2 (*Y)[CB + 1];    // the factor's inverse
+  double2 (*C)[CB + 1];    // L_{i+1,i}
+  double2 (*A)[CB + 1];    // block (i + 1, i), up to date but for column i
+  double2 (*B)[CB + 1];    // block (i + 1, i + 1), up to date but for column i
+  double2 (*X1)[CB + 1];   // L_{i+1,i-1}, one copy per wave that uses it
+  double2 (*X2)[CB + 1];
+};
+
+// The chain along the diagonal of one matrix, all CNTD threads.
+__device__ void diagonal_chain(const Sec& a, const ChainTiles& t, int* s_ok, int* s_fail) {
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  const int nb = (a.n + CB - 1) / CB, ld = a.ld;
+  if (tid == 0) {
+    *s_ok = 1;
+    *s_fail = 0;
+  }
+  if (tid < CNT) load_tile(t.S, a.G, ld, 0, bsize(a, 0), 0, bsize(a, 0));
+  lds_barrier();
+  for (int i = 0; i < nb; ++i) {
+    const int r = i + 1, mi = bsize(a, i), ri = i * CB, rr = r * CB;
+    const bool more = r < nb;
+    const int mr = more ? bsize(a, r) : 0;
+    if (wave == 0) {
+      diag_chol_inv(t.S, t.Y, mi, s_fail);
+    } else if ((wave == 1 || wave == 2) && more) {
+      // wave 1: block (r, i), wave 2: block (r, r), from their workgroups' sums
+      // over j < r - 2 (none for r < 3), with column j = i - 1 added here
+      const bool dia = wave == 2;
+      const double2 (*x)[CB + 1] = dia ? t.X2 : t.X1;
+      bool ok = r < 3 || wave_wait(a, dia ? flag_at(a.fi, r, r) : flag_at(a.fl, i, r));
+      if (ok) {
+        double2 v[WENT];
+        wave_load(v, r < 3 ? a.G : a.L, ld, rr, mr, dia ? rr : ri, dia ? mr : mi, lane);
+        if (i >= 1) {
+          ok = wave_wait(a, flag_at(a.fl, r, i - 1));
+          if (ok) {
+            double2 xv[WENT];
+            wave_load(xv, a.L, ld, rr, mr, ri - CB, CB, lane);
+            wave_to_tile(xv, dia ? t.X2 : t.X1, lane);
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            wave_sub(v, x, dia ? x : t.C, lane);
+          }
+        }
+        wave_to_tile(v, dia ? t.B : t.A, lane);
+      }
+      if (!ok && lane == 0) *s_ok = 0;
+    } else if (wave == 4 && i > 0) {
+      // this wave wrote the blocks of the step before
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+      if (lane == 0) {
+        __hip_atomic_store(flag_at(a.fl, i - 1, i - 1), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(flag_at(a.fl, i, i - 1), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+    }
+    lds_barrier();
+    if (*s_ok == 0) return;
+    if (tid == 0 && *s_fail) __hip_atomic_store(a.info, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    // L_ri = A (L_ii^-1)^H
+    if (wave == 4) {
+      wave_store(t.S, a.L, ld, ri, mi, ri, mi, lane);
+      wave_store(t.Y, a.Li, ld, ri, mi, ri, mi, lane);
+    } else if (more) {
+      double2 acc[CENT];
+#pragma unroll
+      for (int q = 0; q < CENT; ++q) acc[q] = double2{0.0, 0.0};
+      tile_mma<true>(acc, t.A, t.Y, 1.0);
+      acc_to_tile(acc, t.C);
+    }
+    lds_barrier();
+    // the next diagonal block: B - L_ri L_ri^H
+    if (more) {
+      if (wave == 4) {
+        wave_store(t.C, a.L, ld, rr, mr, ri, mi, lane);
+      } else {
+        double2 acc[CENT];
+        tile_to_acc(t.B, acc);
+        tile_mma<true>(acc, t.C, t.C, -1.0);
+        acc_to_tile(acc, t.S);
+      }
+    }
+    lds_barrier();
+  }
+  if (wave == 4) {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+    if (lane == 0)
+      __hip_atomic_store(flag_at(a.fl, nb - 1, nb - 1), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+}
+
+__global__ __launch_bounds__(CNTD, 4) void cholinv_kernel(CholArgs args) {
   __shared__ double2 tS[CB][CB + 1], tX[CB][CB + 1], tY[CB][CB + 1];
+  __shared__ double2 tA[CB][CB + 1], tB[CB][CB + 1], tC[CB][CB + 1], tX2[CB][CB + 1];
   __shared__ int s_ok, s_fail;
   int sec = 0;
   while (sec + 1 < args.nsec && args.wg0[sec + 1] <= (int)blockIdx.x) ++sec;
@@ -251,50 +406,60 @@ __global__ __launch_bounds__(CNT) void cholinv_kernel(CholArgs args) {
     a.n = args.size[sec];
     a.ld = args.ld;
   }
+  if (wg == 0) {   // block (0, 0) and the chain
+    const ChainTiles t{tS, tY, tC, tA, tB, tX, tX2};
+    diagonal_chain(a, t, &s_ok, &s_fail);
+    return;
+  }
+  if (threadIdx.x >= CNT) return;
   int i = 0;
   while ((i + 1) * (i + 2) / 2 <= wg) ++i;
   const int k = wg - i * (i + 1) / 2;
   const int n = a.ld, mi = bsize(a, i), mk = bsize(a, k), ri = i * CB, rk = k * CB;
   double2 acc[CENT];
 
-  // ---- S = G_ik - sum_{j<k} L_ij L_kj^H (blocks j < k are full)
-  load_tile(tS, a.G, n, ri, mi, rk, mk);
-  __syncthreads();
-  tile_to_acc(tS, acc);
-  for (int j = 0; j < k; ++j) {
-    if (!wait_flags(a, flag_at(a.fl, i, j), flag_at(a.fl, k, j), &s_ok)) return;
-    load_tile(tX, a.L, n, ri, mi, j * CB, CB);                     // L_ij
-    if (i != k) load_tile(tY, a.L, n, rk, mk, j * CB, CB);         // L_kj
+  // ---- S = G_ik - sum_j L_ij L_kj^H over j < k (blocks j < k are full), for
+  // the blocks of the chain over j < i - 2
+  const bool chain = k + 1 >= i;
+  const int jn = chain ? i - 2 : k;
+  if (!chain || jn > 0) {
+    load_tile(tS, a.G, n, ri, mi, rk, mk);
     __syncthreads();
-    tile_mma<true>(acc, tX, i == k ? tX : tY, -1.0);
-    __syncthreads();
+    tile_to_acc(tS, acc);
+    for (int j = 0; j < jn; ++j) {
+      if (!wait_flags(a, flag_at(a.fl, i, j), flag_at(a.fl, k, j), &s_ok)) return;
+      load_tile(tX, a.L, n, ri, mi, j * CB, CB);                     // L_ij
+      if (i != k) load_tile(tY, a.L, n, rk, mk, j * CB, CB);         // L_kj
+      __syncthreads();
+      tile_mma<true>(acc, tX, i == k ? tX : tY, -1.0);
+      __syncthreads();
+    }
   }
-
-  if (i == k) {
-    // ---- diagonal block: L_ii and L_ii^-1
+  if (chain) {
+    if (jn > 0) {   // handed over in the block's place in L
+      acc_to_tile(acc, tS);
+      __syncthreads();
+      store_tile(tS, a.L, n, ri, mi, rk, mk);
+      publish(i == k ? flag_at(a.fi, i, i) : flag_at(a.fl, k, i));
+    }
+    if (i == k) return;
+    if (!wait_flags(a, flag_at(a.fl, i, k), flag_at(a.fl, k, k), &s_ok)) return;
+    load_tile(tX, a.L, n, ri, mi, rk, mk);
+    load_tile(tY, a.Li, n, rk, mk, rk, mk);
+    __syncthreads();
+  } else {
+    // ---- L_ik = S (L_kk^-1)^H, kept in tX
+    if (!wait_flags(a, flag_at(a.fl, k, k), flag_at(a.fl, k, k), &s_ok)) return;
     acc_to_tile(acc, tS);
-    if (threadIdx.x == 0) s_fail = 0;
+    load_tile(tY, a.Li, n, rk, mk, rk, mk);                          // L_kk^-1
     __syncthreads();
-    diag_chol_inv(tS, tY, mi, &s_fail);
+    for (int q = 0; q < CENT; ++q) acc[q] = double2{0.0, 0.0};
+    tile_mma<true>(acc, tS, tY, 1.0);
+    acc_to_tile(acc, tX);
     __syncthreads();
-    store_tile(tS, a.L, n, ri, mi, ri, mi);
-    store_tile(tY, a.Li, n, ri, mi, ri, mi);
-    if (s_fail && threadIdx.x == 0) __hip_atomic_store(a.info, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    publish(flag_at(a.fl, i, i));
-    return;
+    store_tile(tX, a.L, n, ri, mi, rk, mk);
+    publish(flag_at(a.fl, i, k));
   }
-
-  // ---- L_ik = S (L_kk^-1)^H, kept in tX
-  if (!wait_flags(a, flag_at(a.fl, k, k), flag_at(a.fl, k, k), &s_ok)) return;
-  acc_to_tile(acc, tS);
-  load_tile(tY, a.Li, n, rk, mk, rk, mk);                            // L_kk^-1
-  __syncthreads();
-  for (int q = 0; q < CENT; ++q) acc[q] = double2{0.0, 0.0};
-  tile_mma<true>(acc, tS, tY, 1.0);
-  acc_to_tile(acc, tX);
-  __syncthreads();
-  store_tile(tX, a.L, n, ri, mi, rk, mk);
-  publish(flag_at(a.fl, i, k));
   for (int e = threadIdx.x; e < CB * CB; e += CNT) {                   // block (k, i) of L^-1
     const int y = e / CB, x = e % CB;
     if (y < mk && x < mi) a.Li[(size_t)(rk + y) * n + ri + x] = double2{0.0, 0.0};
@@ -379,7 +544,7 @@ hipError_t cholinv_blocks(hipStream_t s, const void* G, int ld, const int* off, 
                        first && !keep_info ? a.info : nullptr);
     void* args[] = {&a};
     const hipError_t e = hipLaunchCooperativeKernel(reinterpret_cast<const void*>(cholinv_kernel), dim3(wg),
-                                                    dim3(CNT), args, 0, s);
+                                                    dim3(CNTD), args, 0, s);
     if (e != hipSuccess) return e;
     first = false;
     q0 = q;
