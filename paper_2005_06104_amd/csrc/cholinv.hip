@@ -29,6 +29,7 @@
 #include <algorithm>
 
 #include "common.h"
+#include "wave.h"
 
 namespace {
 
@@ -39,7 +40,7 @@ constexpr int CMAXB = 32;         // block rows at most
 constexpr int CENT = CB * CB / CNT;   // tile entries per thread
 constexpr int CPR = CNT / CB;         // threads per tile row
 constexpr int NPART = 64 / CB;        // lanes per row in the one-wave steps
-static_assert(CENT >= 1 && CB * CB == CENT * CNT && NPART >= 1, "tile mapping");
+static_assert(CENT >= 1 && CB * CB == CENT * CNT && CB == 16 && NPART == 4, "tile mapping");
 constexpr int CFLAG = 16;         // one 64-byte line per flag
 constexpr unsigned CSPIN = 1u << 22;
 constexpr int CMAXSEC = 64;       // sectors per launch
@@ -151,93 +152,108 @@ __device__ void tile_to_acc(const double2 (*t)[CB + 1], double2 acc[CENT]) {
 
 // Wave 0 factorises the mi x mi block in tS (the lower part; the strict upper
 // part holds the matrix) in place and forms its inverse in tY; *s_fail
-// becomes 1 when a pivot is not positive and finite.  The lanes of one wave
-// see each other's LDS stores in program order, so the steps need no
-// workgroup barrier.
-__device__ void diag_chol_inv(double2 (*tS)[CB + 1], double2 (*tY)[CB + 1], int mi, int* s_fail) {
-  if (threadIdx.x < 64) {
-    const int lane = threadIdx.x;
-    int bad = 0;
-    // left-looking: column c of L from the dot products of the rows r >= c
-    // with row c over the finished columns (row r on the NPART lanes
-    // r + CB p, each adding every NPART-th term)
-    const int rr = lane % CB, part = lane / CB;
-    for (int c = 0; c < mi; ++c) {
-      double2 t{0.0, 0.0};
-      if (rr >= c && rr < mi)
-        for (int k = part; k < c; k += NPART) {
-          const double2 p = cmc(tS[rr][k], tS[c][k]);
-          t.x += p.x;
-          t.y += p.y;
-        }
+// becomes 1 when a pivot is not positive and finite.
+// Left-looking, row rr on the NPART lanes rr + CB p, each with the columns k =
+// p mod NPART in registers: column c of L from the dot products of the rows
+// with row c (broadcast within the row of lanes), every lane adding its
+// NPART-th of the terms.  The inverse follows a row behind by forward
+// substitution, column j on the lanes j + CB p, in the shadow of the square
+// root and division of the next pivot, which are most of the chain.
+// FULL: mi = CB, the usual case, without the bounds.
+struct DiagState {
+  double2 l[CB / NPART];   // L[rr][p + NPART m]
+  double2 y[CB / NPART];   // L^-1[j + p + NPART m][j], j = rr
+  double il;               // 1 / L[rr][rr]
+  int bad;
+};
+template <int C>
+__device__ inline void diag_column(double2 (*tS)[CB + 1], DiagState& s, int rr, int part) {
+  const double2 v = tS[rr][C];
+  double2 t{0.0, 0.0};
 #pragma unroll
-      for (int o = CB; o < 64; o <<= 1) {
-        t.x += __shfl_xor(t.x, o);
-        t.y += __shfl_xor(t.y, o);
-      }
-      const double d = tS[c][c].x - __shfl(t.x, c);
-      const bool good = d > 0.0 && isfinite(d);
-      bad |= good ? 0 : 1;
-      const double l = good ? sqrt(d) : 1.0, il = 1.0 / l;
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-      if (part == 0 && rr > c && rr < mi) {
-        const double2 v = tS[rr][c];
-        tS[rr][c] = double2{(v.x - t.x) * il, (v.y - t.y) * il};
-      }
-      if (lane == c) tS[c][c] = double2{l, 0.0};
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    }
-    // zero above the diagonal and outside the block
-    for (int e = lane; e < CB * CB; e += 64) {
-      const int r = e / CB, c = e % CB;
-      if (c > r || r >= mi || c >= mi) tS[r][c] = double2{0.0, 0.0};
-      tY[r][c] = double2{0.0, 0.0};
-    }
+  for (int m = 0; NPART * m < C; ++m) {
+    const double2 lc{wave::row_bcast<C>(s.l[m].x), wave::row_bcast<C>(s.l[m].y)};
+    t.x += fma(s.l[m].x, lc.x, s.l[m].y * lc.y);   // zero where k >= C
+    t.y += fma(s.l[m].y, lc.x, -(s.l[m].x * lc.y));
+  }
+  t.x = wave::rows_sum(t.x);
+  t.y = wave::rows_sum(t.y);
+  const double d = wave::row_bcast<C>(v.x - t.x);
+  const bool good = d > 0.0 && isfinite(d);
+  s.bad |= good ? 0 : 1;
+  const double l = good ? sqrt(d) : 1.0, il = 1.0 / l;
+  double2 x{(v.x - t.x) * il, (v.y - t.y) * il};
+  if (rr == C) {
+    x = double2{l, 0.0};
+    s.il = il;
+  }
+  if (rr < C) x = double2{0.0, 0.0};
+  if (part == C % NPART) {
+    s.l[C / NPART] = x;
+    tS[rr][C] = x;
+  }
+}
+// row R of L^-1: x_R (column j < R) = -(sum_{q=j}^{R-1} L[R][q] x_q) / L[R][R]
+template <int R>
+__device__ inline void diag_inverse_row(const double2 (*tS)[CB + 1], double2 (*tY)[CB + 1], DiagState& s, int j,
+                                        int part) {
+  double2 t{0.0, 0.0};
+#pragma unroll
+  for (int m = 0; NPART * m < R; ++m) {
+    const int q = j + part + NPART * m;
+    const double2 l = tS[R][q < CB ? q : CB - 1];
+    const double px = fma(l.x, s.y[m].x, -(l.y * s.y[m].y)), py = fma(l.y, s.y[m].x, l.x * s.y[m].y);
+    t.x += q < R ? px : 0.0;
+    t.y += q < R ? py : 0.0;
+  }
+  t.x = wave::rows_sum(t.x);
+  t.y = wave::rows_sum(t.y);
+  const double ir = wave::row_bcast<R>(s.il);
+  double2 x{-t.x * ir, -t.y * ir};
+  if (j == R) x = double2{ir, 0.0};
+  if (j > R) x = double2{0.0, 0.0};
+#pragma unroll
+  for (int m = 0; m < CB / NPART; ++m)
+    if (R - j - part == NPART * m) s.y[m] = x;
+  if (part == 0) tY[R][j] = x;
+}
+template <bool FULL, int C>
+__device__ inline void diag_steps(double2 (*tS)[CB + 1], double2 (*tY)[CB + 1], DiagState& s, int mi, int rr,
+                                  int part) {
+  if constexpr (C <= CB) {
+    // column C and row C - 1 of the inverse (it reads row C - 1 of L, which
+    // column C - 1 completed)
+    if constexpr (C < CB)
+      if (FULL || C < mi) diag_column<C>(tS, s, rr, part);
+    if constexpr (C > 0)
+      if (FULL || C - 1 < mi) diag_inverse_row<C - 1>(tS, tY, s, rr, part);
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    // L^-1 by forward substitution, column j on the NPART lanes j + CB p
-    // (each adds every NPART-th term; shuffles join them)
-    {
-      const int j = lane % CB, part = lane / CB;
-      const bool act = j < mi;
-      double2 xj = double2{0.0, 0.0};
-      if (act && part == 0) {
-        xj = double2{1.0 / tS[j][j].x, 0.0};
-        tY[j][j] = xj;
-      }
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-      for (int r = 1; r < mi; ++r) {
-        // x_r (column j, r > j) = -(sum_{s=j}^{r-1} L[r][s] x_s) / L[r][r]
-        double2 t{0.0, 0.0};
-        if (act && r > j)
-          for (int q = j + part; q < r; q += NPART) {
-            const double2 p = cm(tS[r][q], tY[q][j]);
-            t.x += p.x;
-            t.y += p.y;
-          }
-#pragma unroll
-        for (int o = CB; o < 64; o <<= 1) {
-          t.x += __shfl_xor(t.x, o);
-          t.y += __shfl_xor(t.y, o);
-        }
-        if (act && r > j && part == 0) {
-          const double ir = 1.0 / tS[r][r].x;
-          tY[r][j] = double2{-t.x * ir, -t.y * ir};
-        }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-      }
-    }
-    if (lane == 0) *s_fail = bad;
+    diag_steps<FULL, C + 1>(tS, tY, s, mi, rr, part);
   }
+}
+template <bool FULL>
+__device__ inline void diag_chol_inv_as(double2 (*tS)[CB + 1], double2 (*tY)[CB + 1], int mi, int lane, int* s_fail) {
+  DiagState s;
+#pragma unroll
+  for (int m = 0; m < CB / NPART; ++m) s.l[m] = s.y[m] = double2{0.0, 0.0};
+  s.il = 1.0;
+  s.bad = 0;
+  if (!FULL) {   // rows past the block
+    for (int e = lane; e < CB * CB; e += 64)
+      if (e / CB >= mi || e % CB >= mi) tS[e / CB][e % CB] = tY[e / CB][e % CB] = double2{0.0, 0.0};
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  }
+  diag_steps<FULL, 0>(tS, tY, s, mi, lane % CB, lane / CB);
+  if (lane == 0) *s_fail = s.bad;
+}
+__device__ void diag_chol_inv(double2 (*tS)[CB + 1], double2 (*tY)[CB + 1], int mi, int* s_fail) {
+  const int lane = threadIdx.x & 63;
+  if (mi == CB) diag_chol_inv_as<true>(tS, tY, mi, lane, s_fail);
+  else diag_chol_inv_as<false>(tS, tY, mi, lane, s_fail);
 }
 
 // workgroup barrier for LDS alone: stores to memory stay in flight

@@ -25,6 +25,28 @@ __device__ inline double lane_of(double v, int l) {
   return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
 }
 
+// lane C of each row of 16, in all lanes of the row
+template <int C>
+__device__ inline double row_bcast(double v) {
+  return dpp_mov<0x150 + C>(v);   // row_newbcast
+}
+
+// sum of the four lanes l, l ^ 16, l ^ 32, l ^ 48, rows paired by 16 first
+__device__ inline double rows_sum(double v) {
+  const unsigned long long b = (unsigned long long)__double_as_longlong(v);
+  const unsigned lo = (unsigned)b, hi = (unsigned)(b >> 32);
+  auto l = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+  auto h = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+  v = __longlong_as_double((long long)(((unsigned long long)h[0] << 32) | l[0])) +
+      __longlong_as_double((long long)(((unsigned long long)h[1] << 32) | l[1]));
+  const unsigned long long c = (unsigned long long)__double_as_longlong(v);
+  const unsigned lo2 = (unsigned)c, hi2 = (unsigned)(c >> 32);
+  l = __builtin_amdgcn_permlane32_swap(lo2, lo2, false, false);
+  h = __builtin_amdgcn_permlane32_swap(hi2, hi2, false, false);
+  return __longlong_as_double((long long)(((unsigned long long)h[0] << 32) | l[0])) +
+         __longlong_as_double((long long)(((unsigned long long)h[1] << 32) | l[1]));
+}
+
 // op over the 16 lanes of each row (every lane gets its row's result)
 template <class Op>
 __device__ inline double row16(double v, Op op) {
