@@ -9,12 +9,12 @@
 // The chain along the diagonal is what is sequential, and a block handed from
 // one workgroup to another costs two to three microseconds (write back, flag,
 // poll, fetch).  So one workgroup per matrix runs the whole chain out of LDS,
-// the diagonal blocks and those below them: while one of its waves factorises
-// and inverts block (i, i), two others bring block row i + 1 up to date with
+// the diagonal blocks and those below them: while two of its waves factorise
+// and invert block (i, i), two others bring block row i + 1 up to date with
 // L_{i+1,i-1}, and one writes out the step before.  The other blocks have a
 // workgroup each; those of (i, i) and (i, i - 1) hand the chain their sums over
-// j < i - 2, early enough for it not to wait.  n = 300: 273 us (each
-// diagonal block in a workgroup of its own: 335 us).
+// j < i - 2, early enough for it not to wait.  n = 300: 160 us, 8.2 us a block row (each
+// diagonal block in a workgroup of its own, LDS and shuffles: 335 us).
 // A block is published with a flag once written; a workgroup waits only for
 // blocks of lower column index (or, for L^-1, of lower row index in its own
 // column) and for diagonal blocks, so the waits form chains that end.  Every
@@ -150,110 +150,122 @@ __device__ void tile_to_acc(const double2 (*t)[CB + 1], double2 acc[CENT]) {
   for (int q = 0; q < CENT; ++q) acc[q] = t[r][c0 + CPR * q];
 }
 
-// Wave 0 factorises the mi x mi block in tS (the lower part; the strict upper
-// part holds the matrix) in place and forms its inverse in tY; *s_fail
-// becomes 1 when a pivot is not positive and finite.
-// Left-looking, row rr on the NPART lanes rr + CB p, each with the columns k =
-// p mod NPART in registers: column c of L from the dot products of the rows
-// with row c (broadcast within the row of lanes), every lane adding its
-// NPART-th of the terms.  The inverse follows a row behind by forward
-// substitution, column j on the lanes j + CB p, in the shadow of the square
-// root and division of the next pivot, which are most of the chain.
-// FULL: mi = CB, the usual case, without the bounds.
-struct DiagState {
-  double2 l[CB / NPART];   // L[rr][p + NPART m]
-  double2 y[CB / NPART];   // L^-1[j + p + NPART m][j], j = rr
-  double il;               // 1 / L[rr][rr]
-  int bad;
+// The mi x mi diagonal block in tS (the lower part; the strict upper part holds
+// the matrix) is factorised in place by one wave; *s_fail becomes 1 when a pivot
+// is not positive and finite.  Left-looking, row rr on the NPART lanes rr + CB p,
+// each with the columns k = p mod NPART in registers: column c of L from the dot
+// products of the rows with row c (broadcast within the row of lanes), every
+// lane adding its NPART-th of the terms.  Another wave forms the inverse in tY a
+// row behind by forward substitution, column j on the lanes j + CB p; the first
+// tells it in *done how many columns are there (a wave's LDS accesses keep their
+// order).  A wave issues an instruction every four to five cycles, and the two
+// are about 80 each per column: in one wave they took 8.7 us a block, in two
+// 6.1.  FULL: mi = CB, the usual case, without the bounds.
+struct DiagShare {
+  double il[CB];   // 1 / L[c][c]
+  int done;        // columns of L that are in tS; 0 at the start
 };
 template <int C>
-__device__ inline void diag_column(double2 (*tS)[CB + 1], DiagState& s, int rr, int part) {
+__device__ inline void diag_column(double2 (*tS)[CB + 1], DiagShare* sh, double2 (&lr)[CB / NPART], int& bad, int rr,
+                                   int part) {
   const double2 v = tS[rr][C];
   double2 t{0.0, 0.0};
 #pragma unroll
   for (int m = 0; NPART * m < C; ++m) {
-    const double2 lc{wave::row_bcast<C>(s.l[m].x), wave::row_bcast<C>(s.l[m].y)};
-    t.x += fma(s.l[m].x, lc.x, s.l[m].y * lc.y);   // zero where k >= C
-    t.y += fma(s.l[m].y, lc.x, -(s.l[m].x * lc.y));
+    const double2 lc{wave::row_bcast<C>(lr[m].x), wave::row_bcast<C>(lr[m].y)};
+    t.x += fma(lr[m].x, lc.x, lr[m].y * lc.y);   // zero where k >= C
+    t.y += fma(lr[m].y, lc.x, -(lr[m].x * lc.y));
   }
   t.x = wave::rows_sum(t.x);
   t.y = wave::rows_sum(t.y);
   const double d = wave::row_bcast<C>(v.x - t.x);
   const bool good = d > 0.0 && isfinite(d);
-  s.bad |= good ? 0 : 1;
+  bad |= good ? 0 : 1;
   const double l = good ? sqrt(d) : 1.0, il = 1.0 / l;
   double2 x{(v.x - t.x) * il, (v.y - t.y) * il};
-  if (rr == C) {
-    x = double2{l, 0.0};
-    s.il = il;
-  }
+  if (rr == C) x = double2{l, 0.0};
   if (rr < C) x = double2{0.0, 0.0};
   if (part == C % NPART) {
-    s.l[C / NPART] = x;
+    lr[C / NPART] = x;   // L[rr][p + NPART m]
     tS[rr][C] = x;
+  }
+  asm volatile("" ::: "memory");
+  if (rr == 0 && part == 0) {
+    sh->il[C] = il;
+    asm volatile("" ::: "memory");
+    __hip_atomic_store(&sh->done, C + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  }
+  asm volatile("" ::: "memory");
+}
+template <bool FULL, int C>
+__device__ inline void diag_columns(double2 (*tS)[CB + 1], DiagShare* sh, double2 (&lr)[CB / NPART], int& bad, int mi,
+                                    int rr, int part) {
+  if constexpr (C < CB) {
+    if (FULL || C < mi) diag_column<C>(tS, sh, lr, bad, rr, part);
+    diag_columns<FULL, C + 1>(tS, sh, lr, bad, mi, rr, part);
   }
 }
 // row R of L^-1: x_R (column j < R) = -(sum_{q=j}^{R-1} L[R][q] x_q) / L[R][R]
-template <int R>
-__device__ inline void diag_inverse_row(const double2 (*tS)[CB + 1], double2 (*tY)[CB + 1], DiagState& s, int j,
-                                        int part) {
-  double2 t{0.0, 0.0};
+template <bool FULL, int R>
+__device__ inline void diag_inverse_rows(const double2 (*tS)[CB + 1], double2 (*tY)[CB + 1], DiagShare* sh,
+                                         double2 (&y)[CB / NPART], int mi, int j, int part) {
+  if constexpr (R < CB) {
+    if (FULL || R < mi) {
+      while (__hip_atomic_load(&sh->done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) <= R) {
+      }
+      asm volatile("" ::: "memory");
+      double2 t{0.0, 0.0};
 #pragma unroll
-  for (int m = 0; NPART * m < R; ++m) {
-    const int q = j + part + NPART * m;
-    const double2 l = tS[R][q < CB ? q : CB - 1];
-    const double px = fma(l.x, s.y[m].x, -(l.y * s.y[m].y)), py = fma(l.y, s.y[m].x, l.x * s.y[m].y);
-    t.x += q < R ? px : 0.0;
-    t.y += q < R ? py : 0.0;
-  }
-  t.x = wave::rows_sum(t.x);
-  t.y = wave::rows_sum(t.y);
-  const double ir = wave::row_bcast<R>(s.il);
-  double2 x{-t.x * ir, -t.y * ir};
-  if (j == R) x = double2{ir, 0.0};
-  if (j > R) x = double2{0.0, 0.0};
+      for (int m = 0; NPART * m < R; ++m) {
+        const int q = j + part + NPART * m;
+        const double2 l = tS[R][q < CB ? q : CB - 1];
+        const double px = fma(l.x, y[m].x, -(l.y * y[m].y)), py = fma(l.y, y[m].x, l.x * y[m].y);
+        t.x += q < R ? px : 0.0;
+        t.y += q < R ? py : 0.0;
+      }
+      t.x = wave::rows_sum(t.x);
+      t.y = wave::rows_sum(t.y);
+      const double ir = sh->il[R];
+      double2 x{-t.x * ir, -t.y * ir};
+      if (j == R) x = double2{ir, 0.0};
+      if (j > R) x = double2{0.0, 0.0};
 #pragma unroll
-  for (int m = 0; m < CB / NPART; ++m)
-    if (R - j - part == NPART * m) s.y[m] = x;
-  if (part == 0) tY[R][j] = x;
-}
-template <bool FULL, int C>
-__device__ inline void diag_steps(double2 (*tS)[CB + 1], double2 (*tY)[CB + 1], DiagState& s, int mi, int rr,
-                                  int part) {
-  if constexpr (C <= CB) {
-    // column C and row C - 1 of the inverse (it reads row C - 1 of L, which
-    // column C - 1 completed)
-    if constexpr (C < CB)
-      if (FULL || C < mi) diag_column<C>(tS, s, rr, part);
-    if constexpr (C > 0)
-      if (FULL || C - 1 < mi) diag_inverse_row<C - 1>(tS, tY, s, rr, part);
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    diag_steps<FULL, C + 1>(tS, tY, s, mi, rr, part);
+      for (int m = 0; m < CB / NPART; ++m)
+        if (R - j - part == NPART * m) y[m] = x;   // L^-1[j + p + NPART m][j]
+      if (part == 0) tY[R][j] = x;
+    }
+    diag_inverse_rows<FULL, R + 1>(tS, tY, sh, y, mi, j, part);
   }
 }
-template <bool FULL>
-__device__ inline void diag_chol_inv_as(double2 (*tS)[CB + 1], double2 (*tY)[CB + 1], int mi, int lane, int* s_fail) {
-  DiagState s;
-#pragma unroll
-  for (int m = 0; m < CB / NPART; ++m) s.l[m] = s.y[m] = double2{0.0, 0.0};
-  s.il = 1.0;
-  s.bad = 0;
-  if (!FULL) {   // rows past the block
-    for (int e = lane; e < CB * CB; e += 64)
-      if (e / CB >= mi || e % CB >= mi) tS[e / CB][e % CB] = tY[e / CB][e % CB] = double2{0.0, 0.0};
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-  }
-  diag_steps<FULL, 0>(tS, tY, s, mi, lane % CB, lane / CB);
-  if (lane == 0) *s_fail = s.bad;
+// entries past the block
+__device__ inline void diag_clear(double2 (*t)[CB + 1], int mi, int lane) {
+  for (int e = lane; e < CB * CB; e += 64)
+    if (e / CB >= mi || e % CB >= mi) t[e / CB][e % CB] = double2{0.0, 0.0};
+  asm volatile("" ::: "memory");
 }
-__device__ void diag_chol_inv(double2 (*tS)[CB + 1], double2 (*tY)[CB + 1], int mi, int* s_fail) {
-  const int lane = threadIdx.x & 63;
-  if (mi == CB) diag_chol_inv_as<true>(tS, tY, mi, lane, s_fail);
-  else diag_chol_inv_as<false>(tS, tY, mi, lane, s_fail);
+__device__ void diag_factor(double2 (*tS)[CB + 1], int mi, DiagShare* sh, int* s_fail, int lane) {
+  double2 lr[CB / NPART];
+#pragma unroll
+  for (int m = 0; m < CB / NPART; ++m) lr[m] = double2{0.0, 0.0};
+  int bad = 0;
+  if (mi == CB) {
+    diag_columns<true, 0>(tS, sh, lr, bad, mi, lane % CB, lane / CB);
+  } else {
+    diag_clear(tS, mi, lane);
+    diag_columns<false, 0>(tS, sh, lr, bad, mi, lane % CB, lane / CB);
+  }
+  if (lane == 0) *s_fail = bad;
+}
+__device__ void diag_invert(const double2 (*tS)[CB + 1], double2 (*tY)[CB + 1], int mi, DiagShare* sh, int lane) {
+  double2 y[CB / NPART];
+#pragma unroll
+  for (int m = 0; m < CB / NPART; ++m) y[m] = double2{0.0, 0.0};
+  if (mi == CB) {
+    diag_inverse_rows<true, 0>(tS, tY, sh, y, mi, lane % CB, lane / CB);
+  } else {
+    diag_clear(tY, mi, lane);
+    diag_inverse_rows<false, 0>(tS, tY, sh, y, mi, lane % CB, lane / CB);
+  }
 }
 
 // workgroup barrier for LDS alone: stores to memory stay in flight
@@ -321,12 +333,13 @@ struct ChainTiles {
 };
 
 // The chain along the diagonal of one matrix, all CNTD threads.
-__device__ void diagonal_chain(const Sec& a, const ChainTiles& t, int* s_ok, int* s_fail) {
+__device__ void diagonal_chain(const Sec& a, const ChainTiles& t, DiagShare* sh, int* s_ok, int* s_fail) {
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int nb = (a.n + CB - 1) / CB, ld = a.ld;
   if (tid == 0) {
     *s_ok = 1;
     *s_fail = 0;
+    sh->done = 0;
   }
   if (tid < CNT) load_tile(t.S, a.G, ld, 0, bsize(a, 0), 0, bsize(a, 0));
   lds_barrier();
@@ -335,7 +348,9 @@ __device__ void diagonal_chain(const Sec& a, const ChainTiles& t, int* s_ok, int
     const bool more = r < nb;
     const int mr = more ? bsize(a, r) : 0;
     if (wave == 0) {
-      diag_chol_inv(t.S, t.Y, mi, s_fail);
+      diag_factor(t.S, mi, sh, s_fail, lane);
+    } else if (wave == 3) {
+      diag_invert(t.S, t.Y, mi, sh, lane);
     } else if ((wave == 1 || wave == 2) && more) {
       // wave 1: block (r, i), wave 2: block (r, r), from their workgroups' sums
       // over j < r - 2 (none for r < 3), with column j = i - 1 added here
@@ -370,6 +385,7 @@ __device__ void diagonal_chain(const Sec& a, const ChainTiles& t, int* s_ok, int
     }
     lds_barrier();
     if (*s_ok == 0) return;
+    if (tid == 0) sh->done = 0;
     if (tid == 0 && *s_fail) __hip_atomic_store(a.info, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     // L_ri = A (L_ii^-1)^H
     if (wave == 4) {
@@ -406,6 +422,7 @@ __device__ void diagonal_chain(const Sec& a, const ChainTiles& t, int* s_ok, int
 __global__ __launch_bounds__(CNTD, 4) void cholinv_kernel(CholArgs args) {
   __shared__ double2 tS[CB][CB + 1], tX[CB][CB + 1], tY[CB][CB + 1];
   __shared__ double2 tA[CB][CB + 1], tB[CB][CB + 1], tC[CB][CB + 1], tX2[CB][CB + 1];
+  __shared__ DiagShare diag;
   __shared__ int s_ok, s_fail;
   int sec = 0;
   while (sec + 1 < args.nsec && args.wg0[sec + 1] <= (int)blockIdx.x) ++sec;
@@ -424,7 +441,7 @@ __global__ __launch_bounds__(CNTD, 4) void cholinv_kernel(CholArgs args) {
   }
   if (wg == 0) {   // block (0, 0) and the chain
     const ChainTiles t{tS, tY, tC, tA, tB, tX, tX2};
-    diagonal_chain(a, t, &s_ok, &s_fail);
+    diagonal_chain(a, t, &diag, &s_ok, &s_fail);
     return;
   }
   if (threadIdx.x >= CNT) return;
