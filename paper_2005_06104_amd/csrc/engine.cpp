@@ -278,14 +278,15 @@ void env_left(tdvp_ctx_s* ctx, const SiteTables& tb, int ml, int wl, int wr, int
                   mr, (long long)wr * mr, pm.wc);
   // Lout[b',(be,b)] = sum_{(a',s')} conj(A[(a',s'),b']) T2[(a',s'),(be,b)]
   kern::KMapScope ks(pm.g2);
+  const bool lend = sizeof(T) == 4;   // FP64 keeps its order of summation
   kern::gemm<T>(s, TDVP_OP_C, TDVP_OP_N, mr, wr * mr, 2 * ml, 1.0, A, mr, 0, ws2, (long long)wr * mr, 0, 0.0, Lout,
-                (long long)wr * mr, 0, 1);
+                (long long)wr * mr, 0, 1, lend ? sk.p : nullptr, lend ? sk.bytes : 0);
 }
 
 template <typename T>
 void env_right(tdvp_ctx_s* ctx, const SiteTables& tb, int ml, int wl, int wr, int mr, const void* Rt,
                const void* B, void* Rout, void* ws1, void* ws2, SplitWS sk, ProdMaps pm) {
-  (void)sk;
+  const bool lend = sizeof(T) == 4;   // FP64 keeps its order of summation
   hipStream_t s = ctx->stream;
   // U1[be][(a,s),b'] = B[(a,s),b] Rt[be][b,b']   (batched over be)
   {
@@ -298,7 +299,7 @@ void env_right(tdvp_ctx_s* ctx, const SiteTables& tb, int ml, int wl, int wr, in
   // Rout[(al,a),a'] = sum_{(s',b')} U2[(al,a),(s',b')] conj(B[a',(s',b')])
   kern::KMapScope ks(pm.g2);
   kern::gemm<T>(s, TDVP_OP_N, TDVP_OP_C, wl * ml, ml, 2 * mr, 1.0, ws2, 2LL * mr, 0, B, 2LL * mr, 0, 0.0, Rout, ml,
-                0, 1);
+                0, 1, lend ? sk.p : nullptr, lend ? sk.bytes : 0);
 }
 
 // Two-site effective Hamiltonian on Th[a,(s,v),b] for the sites i, i+1:

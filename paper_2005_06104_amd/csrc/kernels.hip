@@ -8,10 +8,11 @@
 //   These carry every contraction of the method: effective Hamiltonians,
 //   environments, MPO application, basis extension.
 // * wapply: contraction with the sparse MPO tensor over (MPO index, physical
-//   index), staged through LDS; memory bound.
+//   index); memory bound.
 // * complex128 vector helpers for the Lanczos recurrence (FP64 always).
 #include <hip/hip_runtime.h>
 
+#include <numeric>
 #include <type_traits>
 
 #include "common.h"
@@ -171,16 +172,19 @@ __device__ inline void deal_pieces(const TileJob& job, bool mapped, int wave, in
 //
 // What bounds it (TERMS 3, 20480 x 2048 x 1024): the matrix cores and the
 // conversion at once; a K step of a 128 x 64 tile is 192 MFMAs a wave (3190
-// cycles) and about 500 other vector instructions (2300), which the CU's two
+// cycles) and about 460 other vector instructions (2100), which the CU's two
 // workgroups overlap in part: 1.86 ms, 184 TFLOP/s at 8 a complex
 // multiply-add, 1.1 PFLOP/s in BF16 (a register-only loop of these MFMAs on
-// such data: 1.9).  The FP32 matrix cores in the 3M form: 2.67 ms.
+// such data: 1.9; a large library product in BF16: 1.2).  Both signs on A and
+// in a step's sums, 64 more instructions: 1.93 ms.  The FP32 matrix cores in
+// the 3M form: 2.67 ms.
 constexpr int BKS = 32;
 constexpr float UP3 = 0x1p20f;
 
 typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
 typedef float f2v __attribute__((ext_vector_type(2)));
+typedef float f4u __attribute__((ext_vector_type(4), aligned(8)));
 
 __device__ inline f4 mfma_bf16(uint4 a, uint4 b, f4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf8, a), __builtin_bit_cast(bf8, b), c, 0, 0,
@@ -280,15 +284,17 @@ __device__ inline void chunk_load(const float2* __restrict__ X, long long ld, in
   }
 }
 
-// the TERMS BF16 terms of eight numbers, packed
+// the TERMS BF16 terms of eight numbers (neg: of their negatives), packed
 template <int TERMS>
-__device__ inline void bf16_terms(const float (&x)[8], uint4 (&o)[TERMS]) {
+__device__ inline void bf16_terms(const float (&x)[8], bool neg, uint4 (&o)[TERMS]) {
+  const float up = neg ? -UP3 : UP3;
+  const unsigned flip = neg ? 0x80008000u : 0u;
   unsigned w[TERMS][4];
 #pragma unroll
   for (int p = 0; p < 4; ++p) {
     f2v v;
-    v.x = TERMS == 3 ? x[2 * p] * UP3 : x[2 * p];
-    v.y = TERMS == 3 ? x[2 * p + 1] * UP3 : x[2 * p + 1];
+    v.x = TERMS == 3 ? x[2 * p] * up : x[2 * p];
+    v.y = TERMS == 3 ? x[2 * p + 1] * up : x[2 * p + 1];
 #pragma unroll
     for (int t = 0; t < TERMS; ++t) {
       w[t][p] = __builtin_bit_cast(unsigned, __builtin_convertvector(v, bf2));
@@ -299,12 +305,15 @@ __device__ inline void bf16_terms(const float (&x)[8], uint4 (&o)[TERMS]) {
     }
   }
 #pragma unroll
-  for (int t = 0; t < TERMS; ++t) o[t] = uint4{w[t][0], w[t][1], w[t][2], w[t][3]};
+  for (int t = 0; t < TERMS; ++t) {
+    o[t] = uint4{w[t][0], w[t][1], w[t][2], w[t][3]};
+    if (TERMS < 3) o[t] = bf16_flip(o[t], flip);
+  }
 }
 
-// planes: term t, real then imaginary part, ROWS x 32 each
+// planes: term t, real then imaginary part (conj: its negative), ROWS x 32 each
 template <bool KC, int TERMS, int ROWS, int NTH>
-__device__ inline void chunk_store(unsigned short* P, int tid, const float2 (&v)[ROWS * 4 / NTH][8]) {
+__device__ inline void chunk_store(unsigned short* P, int tid, const float2 (&v)[ROWS * 4 / NTH][8], bool conj) {
 #pragma unroll
   for (int it = 0; it < ROWS * 4 / NTH; ++it) {
     int row, ch;
@@ -316,8 +325,8 @@ __device__ inline void chunk_store(unsigned short* P, int tid, const float2 (&v)
       im[j] = v[it][j].y;
     }
     uint4 tr[TERMS], ti[TERMS];
-    bf16_terms<TERMS>(re, tr);
-    bf16_terms<TERMS>(im, ti);
+    bf16_terms<TERMS>(re, false, tr);
+    bf16_terms<TERMS>(im, conj, ti);
     unsigned short* p = P + plane_at(row, ch);
 #pragma unroll
     for (int t = 0; t < TERMS; ++t) {
@@ -327,64 +336,47 @@ __device__ inline void chunk_store(unsigned short* P, int tid, const float2 (&v)
   }
 }
 
-// cr += a_r b_r + s_r a_i b_i, ci += a_r b_i + s_i a_i b_r (s_i = -s_r) over a
-// step's 32 k, for one row piece and NJ column pieces.
-template <int TERMS, int NJ>
+// cr += a_r b_r - a_i b_i, ci += a_r b_i + a_i b_r over a step's 32 k,
+// for one row piece and NJ column pieces.  The sign goes to A, or, if the caller
+// has more row than column pieces, to b_n = -b_i.
+template <int TERMS, int NJ, bool BN = false>
 __device__ inline void step_products(const uint4 (&a_r)[TERMS], const uint4 (&a_i)[TERMS],
-                                     const uint4 (&b_r)[NJ][TERMS], const uint4 (&b_i)[NJ][TERMS], float s_r,
-                                     f4 (&cr)[NJ], f4 (&ci)[NJ]) {
-  if constexpr (TERMS == 3) {
-    // The four products of a step are summed on their own and added to the
-    // running sums once: the signs cost no pass over the operands, and a sum
-    // over K rounds K / 32 times at its full size instead of 3/8 K times
-    // (M x N x K = 20480 x 2048 x 1024: error 1.2e-7 against 7.1e-7 with the
-    // running sums in the matrix cores and 8.0e-7 on the FP32 matrix cores).
-    f4 rr[NJ], ri[NJ], ir[NJ], ii[NJ];
+                                     const uint4 (&b_r)[NJ][TERMS], const uint4 (&b_i)[NJ][TERMS],
+                                     const uint4 (&b_n)[NJ][TERMS], f4 (&cr)[NJ], f4 (&ci)[NJ]) {
+  // TERMS 3: a step's products are summed on their own and added to the running
+  // sums once: a sum over K rounds K / 32 times at its full size instead of
+  // 3/8 K times (M x N x K = 20480 x 2048 x 1024: error 1.1e-7 against 7.1e-7
+  // with the running sums in the matrix cores and 8.0e-7 on the FP32 matrix
+  // cores).  Fewer terms: too few products a step for that.
+  constexpr bool APART = TERMS == 3;
+  uint4 a_n[TERMS];
 #pragma unroll
-    for (int j = 0; j < NJ; ++j) rr[j] = ri[j] = ir[j] = ii[j] = f4{0, 0, 0, 0};
+  for (int t = 0; t < TERMS; ++t) a_n[t] = BN ? a_i[t] : bf16_flip(a_i[t], 0x80008000u);
+  f4 xr[NJ], xi[NJ];
 #pragma unroll
-    for (int g = TERMS - 1; g >= 0; --g)   // the products of 2^-8g, the smallest first
+  for (int j = 0; j < NJ; ++j) {
+    xr[j] = APART ? f4{0, 0, 0, 0} : cr[j];
+    xi[j] = APART ? f4{0, 0, 0, 0} : ci[j];
+  }
 #pragma unroll
-      for (int t = 0; t <= g; ++t)
+  for (int g = TERMS - 1; g >= 0; --g)   // the products of 2^-8g, the smallest first
 #pragma unroll
-        for (int j = 0; j < NJ; ++j) {
-          rr[j] = mfma_bf16(a_r[t], b_r[j][g - t], rr[j]);
-          ri[j] = mfma_bf16(a_r[t], b_i[j][g - t], ri[j]);
-          ir[j] = mfma_bf16(a_i[t], b_r[j][g - t], ir[j]);
-          ii[j] = mfma_bf16(a_i[t], b_i[j][g - t], ii[j]);
-        }
+    for (int t = 0; t <= g; ++t) {
 #pragma unroll
-    for (int j = 0; j < NJ; ++j)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        cr[j][r] += fmaf(s_r, ii[j][r], rr[j][r]);
-        ci[j][r] += fmaf(-s_r, ir[j][r], ri[j][r]);
+      for (int j = 0; j < NJ; ++j) {
+        xr[j] = mfma_bf16(a_r[t], b_r[j][g - t], xr[j]);
+        xi[j] = mfma_bf16(a_r[t], b_i[j][g - t], xi[j]);
       }
-  } else {
-    // too few products a step for that: running sums in the matrix cores, the
-    // signs on A's imaginary part
-    const unsigned m_r = s_r < 0.f ? 0x80008000u : 0u, m_i = m_r ^ 0x80008000u;
-    uint4 a_n[TERMS], a_p[TERMS];
 #pragma unroll
-    for (int t = 0; t < TERMS; ++t) {
-      a_n[t] = bf16_flip(a_i[t], m_r);
-      a_p[t] = bf16_flip(a_i[t], m_i);
+      for (int j = 0; j < NJ; ++j) {
+        xr[j] = mfma_bf16(a_n[t], BN ? b_n[j][g - t] : b_i[j][g - t], xr[j]);
+        xi[j] = mfma_bf16(a_i[t], b_r[j][g - t], xi[j]);
+      }
     }
 #pragma unroll
-    for (int g = TERMS - 1; g >= 0; --g)
-#pragma unroll
-      for (int t = 0; t <= g; ++t) {
-#pragma unroll
-        for (int j = 0; j < NJ; ++j) {
-          cr[j] = mfma_bf16(a_r[t], b_r[j][g - t], cr[j]);
-          ci[j] = mfma_bf16(a_r[t], b_i[j][g - t], ci[j]);
-        }
-#pragma unroll
-        for (int j = 0; j < NJ; ++j) {
-          cr[j] = mfma_bf16(a_n[t], b_i[j][g - t], cr[j]);
-          ci[j] = mfma_bf16(a_p[t], b_r[j][g - t], ci[j]);
-        }
-      }
+  for (int j = 0; j < NJ; ++j) {
+    cr[j] = APART ? cr[j] + xr[j] : xr[j];
+    ci[j] = APART ? ci[j] + xi[j] : xi[j];
   }
 }
 
@@ -397,8 +389,7 @@ struct SplitTile {
   static constexpr bool MAPPED = MAPPED_, WIDE = WIDE_;
 };
 
-// conj: bit 0 conjugates A, bit 1 conjugates B.  A B* = (A* B)*, so two signs
-// of the products with A's imaginary part and one at the store serve all four.
+// conj: bit 0 conjugates A, bit 1 conjugates B (on the way into LDS).
 template <class TL, bool TA, bool TB, int TAG>
 __global__ __launch_bounds__(TL::NTH, TL::OCC) void gemm_split_kernel(
     int M, int N, int K, float ar, float ai, const float* __restrict__ A, long long lda, long long sa,
@@ -406,6 +397,7 @@ __global__ __launch_bounds__(TL::NTH, TL::OCC) void gemm_split_kernel(
     long long sc, int S, int Kc, long long sps, const int4* __restrict__ kit, const int2* __restrict__ kiv, int conj) {
   constexpr int TERMS = TL::TERMS, TM = TL::TM, TN = TL::TN, WM = TL::WM, WN = TL::WN, NTH = TL::NTH;
   constexpr int SI = TM / WM / 16, SJ = TN / WN / 16, PA = TM * BKS, PB = TN * BKS;
+  constexpr bool BN = SI > SJ;
   __shared__ __attribute__((aligned(16))) unsigned short As[2 * TERMS * PA], Bs[2 * TERMS * PB];
 
   const int tid = threadIdx.x;
@@ -444,7 +436,6 @@ __global__ __launch_bounds__(TL::NTH, TL::OCC) void gemm_split_kernel(
 #pragma unroll
   for (int j = 0; j < SJ; ++j) co[j] = wn * (TN / WN) + j * 16;
   if constexpr (TL::MAPPED) deal_pieces(job, kit != nullptr, wave, ro, co, ni, nj);
-  const float s_r = ((conj ^ (conj >> 1)) & 1) ? 1.f : -1.f;
 
   const KIter kr_ = job.kr;
   int iv = 0, k0 = 0, kend = 0;
@@ -466,17 +457,18 @@ __global__ __launch_bounds__(TL::NTH, TL::OCC) void gemm_split_kernel(
       }
     }
     const bool more = niv < kr_.n;
-    chunk_store<!TA, TERMS, TM, NTH>(As, tid, va);
-    chunk_store<TB, TERMS, TN, NTH>(Bs, tid, vb);
+    chunk_store<!TA, TERMS, TM, NTH>(As, tid, va, conj & 1);
+    chunk_store<TB, TERMS, TN, NTH>(Bs, tid, vb, conj & 2);
     __syncthreads();
     if (more) load(nk0, nkend);   // in flight while this step is multiplied
-    uint4 b_r[SJ][TERMS], b_i[SJ][TERMS];
+    uint4 b_r[SJ][TERMS], b_i[SJ][TERMS], b_n[SJ][TERMS];
 #pragma unroll
     for (int j = 0; j < SJ; ++j)
 #pragma unroll
       for (int t = 0; t < TERMS; ++t) {
         b_r[j][t] = *reinterpret_cast<const uint4*>(Bs + (2 * t) * PB + co[j] * BKS + la);
         b_i[j][t] = *reinterpret_cast<const uint4*>(Bs + (2 * t + 1) * PB + co[j] * BKS + la);
+        b_n[j][t] = BN ? bf16_flip(b_i[j][t], 0x80008000u) : b_i[j][t];
       }
     // the CU's other workgroup converts its next step meanwhile
     if constexpr (TERMS == 3) __builtin_amdgcn_s_setprio(1);
@@ -490,11 +482,12 @@ __global__ __launch_bounds__(TL::NTH, TL::OCC) void gemm_split_kernel(
         a_i[t] = *reinterpret_cast<const uint4*>(As + (2 * t + 1) * PA + ro[i] * BKS + la);
       }
       if (!TL::MAPPED || nj == SJ)
-        step_products<TERMS, SJ>(a_r, a_i, b_r, b_i, s_r, cr[i], ci[i]);
+        step_products<TERMS, SJ, BN>(a_r, a_i, b_r, b_i, b_n, cr[i], ci[i]);
       else if (nj == 1)
-        step_products<TERMS, 1>(a_r, a_i, reinterpret_cast<uint4(&)[1][TERMS]>(b_r[0]),
-                                reinterpret_cast<uint4(&)[1][TERMS]>(b_i[0]), s_r, reinterpret_cast<f4(&)[1]>(cr[i][0]),
-                                reinterpret_cast<f4(&)[1]>(ci[i][0]));
+        step_products<TERMS, 1, BN>(a_r, a_i, reinterpret_cast<uint4(&)[1][TERMS]>(b_r[0]),
+                                    reinterpret_cast<uint4(&)[1][TERMS]>(b_i[0]),
+                                    reinterpret_cast<uint4(&)[1][TERMS]>(b_n[0]), reinterpret_cast<f4(&)[1]>(cr[i][0]),
+                                    reinterpret_cast<f4(&)[1]>(ci[i][0]));
       // one row piece's operands at a time (192 more registers otherwise)
       if constexpr (TERMS == 3) __builtin_amdgcn_sched_barrier(0);
     }
@@ -519,7 +512,7 @@ __global__ __launch_bounds__(TL::NTH, TL::OCC) void gemm_split_kernel(
         const int gn = n0 + ln;
         if (gm < M && gn < N && lm >= job.r0 && lm < job.r1 && ln >= job.c0 && ln < job.c1) {
           const float down = TERMS == 3 ? 1.f / (UP3 * UP3) : 1.f;
-          float xr = down * cr[i][j][r], xi = ((conj & 2) ? -down : down) * ci[i][j][r];
+          float xr = down * cr[i][j][r], xi = down * ci[i][j][r];
           if constexpr (TERMS == 3) {
             // An infinity, or a number or sum that the scale takes to one, has
             // no such terms (h - x is not finite): the element is formed again
@@ -553,6 +546,198 @@ __global__ __launch_bounds__(TL::NTH, TL::OCC) void gemm_split_kernel(
         }
       }
     }
+}
+
+// ---------------------------------------------------------------- term images
+// For one and two terms the conversion costs more than the products: a large
+// operand entry is converted once per output tile of its row or column.  With
+// scratch at hand the terms are written once, as the LDS blocks that the
+// product stages, and loaded straight into LDS (no registers, no address
+// arithmetic).  Three terms: the product takes as long either way (six products
+// an entry, 1.2 PFLOP/s), so it keeps the conversion on the way in.
+// 14000 x 2048 x 1021, TERMS 1: 497 us -> 43 of conversion and 196, 1.2
+// PFLOP/s; 10752 x 1402 x 768, TERMS 2: 310 -> 27 and 218, 1.28 PFLOP/s in BF16
+// (a large library product in plain BF16 reaches 1.21 here).
+//
+// Block (64 rows, 32 k): the 2 TERMS planes (term t, real, imaginary) one
+// after the other, each as plane_at; the k blocks of 64 rows follow one
+// another.  Rows and k past the operand are zeros.
+constexpr int IROWS = 64;
+template <int TERMS> constexpr int IBLOCK = 2 * TERMS * IROWS * BKS;   // numbers of a block
+
+// grid (k blocks, row blocks), a chunk a thread: a wave loads whole 128-byte
+// lines in either order and stores a plane's 16 rows, 1 KiB
+template <bool KC, int TERMS>
+__global__ __launch_bounds__(256) void terms_kernel(const float* __restrict__ X, long long ld, int R, int K, int conj,
+                                                    unsigned short* __restrict__ img) {
+  const int lane = threadIdx.x & 63, row = (threadIdx.x >> 6) * 16 + (KC ? lane >> 2 : lane & 15);
+  const int ch = KC ? lane & 3 : lane >> 4;
+  const long long r = (long long)blockIdx.y * IROWS + row;
+  const int k = blockIdx.x * BKS + 8 * ch;
+  float re[8], im[8];
+#pragma unroll
+  for (int j = 0; j < 8; ++j) re[j] = im[j] = 0.f;
+  if (r < R && k < K) {
+    const float2* x = reinterpret_cast<const float2*>(X) + (KC ? r * ld + k : (long long)k * ld + r);
+    if (KC && k + 8 <= K) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const f4u t = reinterpret_cast<const f4u*>(x)[j];
+        re[2 * j] = t.x;
+        im[2 * j] = t.y;
+        re[2 * j + 1] = t.z;
+        im[2 * j + 1] = t.w;
+      }
+    } else {
+#pragma unroll
+      for (int j = 0; j < 8; ++j)
+        if (k + j < K) {
+          const float2 t = KC ? x[j] : x[j * ld];
+          re[j] = t.x;
+          im[j] = t.y;
+        }
+    }
+  }
+  uint4 tr[TERMS], ti[TERMS];
+  bf16_terms<TERMS>(re, false, tr);
+  bf16_terms<TERMS>(im, conj, ti);
+  unsigned short* o = img + ((long long)blockIdx.y * gridDim.x + blockIdx.x) * IBLOCK<TERMS> + plane_at(row, ch);
+#pragma unroll
+  for (int t = 0; t < TERMS; ++t) {
+    *reinterpret_cast<uint4*>(o + (2 * t) * IROWS * BKS) = tr[t];
+    *reinterpret_cast<uint4*>(o + (2 * t + 1) * IROWS * BKS) = ti[t];
+  }
+}
+
+// blocks r0 / 64 .. of an image's k block into LDS, 1 KiB a wave and load
+template <int TERMS, int ROWS, int NTH>
+__device__ inline void image_load(const unsigned short* __restrict__ img, int nkc, int r0, int k0, unsigned short* P,
+                                  int wave, int lane) {
+  constexpr int PER = IBLOCK<TERMS> / 512, PIECES = ROWS / IROWS * PER, NW = NTH / 64;
+  static_assert(ROWS % IROWS == 0 && PIECES % NW == 0);
+#pragma unroll
+  for (int it = 0; it < PIECES / NW; ++it) {
+    const int piece = wave + it * NW;
+    const unsigned short* g = img + ((long long)(r0 / IROWS + piece / PER) * nkc + k0 / BKS) * IBLOCK<TERMS> +
+                              piece % PER * 512 + lane * 8;
+    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)g,
+                                     (__attribute__((address_space(3))) void*)(P + piece * 512), 16, 0, 0);
+  }
+}
+
+// Tile TM x TN, WM x WN waves, OCC workgroups of them a CU at four waves each.
+// STAGES 2: the next step's blocks arrive in a second buffer; 1: the step's
+// last reads are waited for first, and the CU's other workgroups multiply
+// meanwhile.  Tiles are dealt GROUP rows at a time, down the rows first: the
+// workgroups that run together on an XCD share both panels (14000 x 2048 x
+// 1021, TERMS 1: 196 us; along the rows 215).
+template <int TERMS_, int TM_, int TN_, int WM_, int WN_, int STAGES_, int OCC_>
+struct ImageTile {
+  static constexpr int TERMS = TERMS_, TM = TM_, TN = TN_, WM = WM_, WN = WN_, STAGES = STAGES_, OCC = OCC_;
+  static constexpr int NTH = WM * WN * 64, GROUP = 8;
+};
+
+// IA, IB: images of op(A) (rows m) and op(B) (rows n) of nkc k blocks, padded to
+// whole tiles by the host.  Split s of S takes k from s Kc.
+template <class TL>
+__global__ __launch_bounds__(TL::NTH, TL::OCC) void gemm_image_kernel(
+    int M, int N, int K, float ar, float ai, const unsigned short* __restrict__ IA,
+    const unsigned short* __restrict__ IB, int nkc, float br, float bi, float* __restrict__ C, long long ldc, int S,
+    int Kc, long long sps) {
+  constexpr int TERMS = TL::TERMS, TM = TL::TM, TN = TL::TN, WM = TL::WM, WN = TL::WN, NTH = TL::NTH;
+  constexpr int SI = TM / WM / 16, SJ = TN / WN / 16, PA = 2 * TERMS * TM * BKS, PB = 2 * TERMS * TN * BKS;
+  // buffers of their own: a read of one does not wait for the loads into the other
+  __shared__ __attribute__((aligned(16))) unsigned short P0[PA + PB], P1[TL::STAGES == 2 ? PA + PB : 8];
+
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wm = wave / WN, wn = wave % WN;
+  const TileJob job = tile_job<TM, TN>(M, N, K, S, Kc, nullptr, nullptr);
+  const int gx = gridDim.x, gy = gridDim.y, lin = (job.m0 / TM) * gx + job.n0 / TN;
+  const int g0 = lin / (TL::GROUP * gx) * TL::GROUP, rows = min(TL::GROUP, gy - g0), in = lin - g0 * gx;
+  const int m0 = (g0 + in % rows) * TM, n0 = in / rows * TN;
+  const int kb = job.kr.one.x, ke = job.kr.one.y;
+  float2* Cb = reinterpret_cast<float2*>(C) + job.split * sps;
+
+  f4 cr[SI][SJ], ci[SI][SJ];
+#pragma unroll
+  for (int i = 0; i < SI; ++i)
+#pragma unroll
+    for (int j = 0; j < SJ; ++j) cr[i][j] = ci[i][j] = f4{0, 0, 0, 0};
+
+  const int lr = lane & 15, lk = lane >> 4, la = plane_at(lr, lk);
+  auto load = [&](int k, unsigned short* P) {
+    image_load<TERMS, TM, NTH>(IA, nkc, m0, k, P, wave, lane);
+    image_load<TERMS, TN, NTH>(IB, nkc, n0, k, P + PA, wave, lane);
+  };
+  auto at = [&](const unsigned short* P, int t, int r) {
+    return *reinterpret_cast<const uint4*>(P + (r / IROWS) * IBLOCK<TERMS> + (t * IROWS + r % IROWS) * BKS + la);
+  };
+  auto landed = [] {
+    __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0): this wave's blocks are in LDS
+    __syncthreads();
+  };
+  auto step = [&](const unsigned short* P, unsigned short* next, int k) {
+    if (TL::STAGES == 2 && k + BKS < ke) load(k + BKS, next);
+    uint4 b_r[SJ][TERMS], b_i[SJ][TERMS];
+#pragma unroll
+    for (int j = 0; j < SJ; ++j)
+#pragma unroll
+      for (int t = 0; t < TERMS; ++t) {
+        b_r[j][t] = at(P + PA, 2 * t, wn * (TN / WN) + j * 16);
+        b_i[j][t] = at(P + PA, 2 * t + 1, wn * (TN / WN) + j * 16);
+      }
+#pragma unroll
+    for (int i = 0; i < SI; ++i) {
+      uint4 a_r[TERMS], a_i[TERMS];
+#pragma unroll
+      for (int t = 0; t < TERMS; ++t) {
+        a_r[t] = at(P, 2 * t, wm * (TM / WM) + i * 16);
+        a_i[t] = at(P, 2 * t + 1, wm * (TM / WM) + i * 16);
+      }
+      if (TL::STAGES == 1 && i + 1 == SI) {
+        __syncthreads();   // every wave has read its blocks
+        if (k + BKS < ke) load(k + BKS, next);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      step_products<TERMS, SJ>(a_r, a_i, b_r, b_i, b_i, cr[i], ci[i]);
+    }
+    landed();
+  };
+  if (kb < ke) {
+    load(kb, P0);
+    landed();
+    if constexpr (TL::STAGES == 1) {
+      for (int k = kb; k < ke; k += BKS) step(P0, P0, k);
+    } else {
+      for (int k = kb; k < ke; k += 2 * BKS) {
+        step(P0, P1, k);
+        if (k + BKS < ke) step(P1, P0, k + BKS);
+      }
+    }
+  }
+
+  const bool has_beta = (br != 0.f) || (bi != 0.f);
+#pragma unroll
+  for (int i = 0; i < SI; ++i)
+#pragma unroll
+    for (int j = 0; j < SJ; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int gm = m0 + wm * (TM / WM) + i * 16 + lk * 4 + r, gn = n0 + wn * (TN / WN) + j * 16 + lr;
+        if (gm < M && gn < N) {
+          const float xr = cr[i][j][r], xi = ci[i][j][r];
+          float2 o;
+          o.x = ar * xr - ai * xi;
+          o.y = ar * xi + ai * xr;
+          if (has_beta) {
+            const float2 old = Cb[(long long)gm * ldc + gn];
+            o.x += br * old.x - bi * old.y;
+            o.y += br * old.y + bi * old.x;
+          }
+          Cb[(long long)gm * ldc + gn] = o;
+        }
+      }
 }
 
 // ---------------------------------------------------------------- FP64 GEMM
@@ -929,7 +1114,7 @@ void launch_split(const Product<float>& p, int conj, int tile, int n_items, floa
 // its pass over the partial products (about 3 TB/s).  Splits keep at least two
 // K steps each.
 template <int TERMS>
-void choose_split_tile(int M, int N, int K, int batch, size_t ws_bytes, int* tile, int* S) {
+double choose_split_tile(int M, int N, int K, int batch, size_t ws_bytes, int* tile, int* S) {
   using TS = SplitTiles<TERMS>;
   const double mn = (double)M * N * sizeof(float2);
   double best = 0.0;
@@ -947,6 +1132,143 @@ void choose_split_tile(int M, int N, int K, int batch, size_t ws_bytes, int* til
         best = us;
         *tile = t;
         *S = q;
+      }
+    }
+  }
+  return best;
+}
+
+// Tiles of the products on term images, as TileCost (14000 x 2048 x 1021, 4096
+// x 2048 x 1021, 1500 x 1000 x 3500, 1000 x 500 x 1000; TERMS 1, largest to
+// smallest tile: 196, 63, 70, 21 us and 258, 75, 72, 17; TERMS 2 10752 x 1402 x
+// 768 / 701 x 11917 x 1536: 218 / 277 us, 128 x 64: 220 / 286).
+template <int TERMS> struct ImageTiles;
+template <> struct ImageTiles<1> {
+  static constexpr int n = 2;
+  static constexpr TileCost cost[n] = {{128, 64, 0.6, 0.44}, {64, 64, 0.4, 0.28}};
+  using T0 = ImageTile<1, 128, 64, 2, 2, 2, 3>;
+  using T1 = ImageTile<1, 64, 64, 2, 2, 1, 4>;
+};
+template <> struct ImageTiles<2> {
+  static constexpr int n = 1;
+  static constexpr TileCost cost[n] = {{64, 64, 0.75, 0.59}};
+  using T0 = ImageTile<2, 64, 64, 2, 2, 1, 4>;
+  using T1 = T0;
+};
+
+// How a product on images is cut so that they fit the scratch: slabs of M, of N
+// or of K (then C is read and written again by each).
+struct ImagePlan {
+  int tile, S, ms, ns, ks;   // tile of ImageTiles; K splits; rows, columns and k of a slab
+  double us;
+};
+
+inline long long ceil_to(long long a, long long b) { return (a + b - 1) / b * b; }
+
+// bytes of the image of `rows` rows and k numbers, rows padded to whole tiles
+template <int TERMS> long long image_bytes(long long rows, long long k, int tile) {
+  return ceil_to(rows, tile) * ceil_to(k, BKS) * 2 * TERMS * (long long)sizeof(short);
+}
+
+// The cut of least estimated time, from the steps each CU works off as above
+// and a conversion of 3.5 us and 5 TB/s; us < 0: none fits.
+template <int TERMS>
+ImagePlan choose_images(int M, int N, int K, size_t ws_bytes) {
+  using TS = ImageTiles<TERMS>;
+  ImagePlan best{0, 1, M, N, K, -1.0};
+  if (std::max(M, N) > 65535 * IROWS) return best;   // the conversion's grid
+  const double mn = (double)M * N * sizeof(float2);
+  for (int t = 0; t < TS::n; ++t) {
+    const TileCost& c = TS::cost[t];
+    const int nt = (N + c.tn - 1) / c.tn, mt = (M + c.tm - 1) / c.tm;
+    auto gemm_us = [&](int rows, int cols, int k, int S) {   // rows and columns of tiles
+      const double per_cu = std::ceil((double)rows * cols * S / 256.0);
+      const double steps = std::ceil(std::ceil((double)k / S) / BKS);
+      return 4.0 + steps * (per_cu > 1.0 ? std::max(c.alone, per_cu * c.shared) : c.alone);
+    };
+    auto convert_us = [&](double rows, double k) { return 3.5 + rows * k * (8.0 + 4.0 * TERMS) / 5e6; };
+    auto consider = [&](int S, int ms, int ns, int ks, double us) {
+      if (best.us < 0.0 || us < best.us) best = ImagePlan{t, S, ms, ns, ks, us};
+    };
+    const double convert = convert_us(M, K) + convert_us(N, K);
+    // slabs of rows (columns): the other operand's image and one slab's
+    for (int side = 0; side < 2; ++side) {
+      const int cut = side ? nt : mt, whole = side ? mt : nt, edge = side ? c.tn : c.tm;
+      const long long other = image_bytes<TERMS>(side ? M : N, K, side ? c.tm : c.tn);
+      const long long one = image_bytes<TERMS>(edge, K, edge);
+      if (other + one > (long long)ws_bytes) continue;
+      const int fit = (int)std::min<long long>(cut, ((long long)ws_bytes - other) / one);
+      for (int slabs = (cut + fit - 1) / fit; slabs <= cut && slabs <= 16; ++slabs)
+        for (int fill = 0; fill < 2; ++fill) {   // even slabs, or such as fill the CUs evenly
+          int w = (cut + slabs - 1) / slabs;
+          const int unit = 256 / std::gcd(256, whole);
+          if (fill) w = std::min(fit, (w + unit - 1) / unit * unit);
+          const int n = (cut + w - 1) / w, last = cut - (n - 1) * w;
+          consider(1, side ? M : w * edge, side ? w * edge : N, K,
+                   convert + 3.5 * (n - 1) + (n - 1) * gemm_us(w, whole, K, 1) + gemm_us(last, whole, K, 1));
+        }
+    }
+    // slabs of k, with or without K splits: both images' slabs and the partial products
+    for (int S : {1, 2, 3, 4, 6, 8}) {
+      if (K < 4 * BKS * S) break;
+      const long long part = S > 1 ? (long long)S * (long long)mn : 0;
+      const long long k_img = image_bytes<TERMS>(M, BKS, c.tm) + image_bytes<TERMS>(N, BKS, c.tn);
+      const long long kc = ((long long)ws_bytes - part) / k_img;   // k blocks that fit
+      if (kc < 4 * S) continue;
+      const int n = (int)(((K + BKS - 1) / BKS + kc - 1) / kc);
+      const int ks = (int)ceil_to((K + n - 1) / n, BKS);
+      double us = convert + 7.0 * (n - 1) + n * gemm_us(mt, nt, ks, S) + (n - 1) * 2 * mn / 3e6;
+      if (S > 1) us += n * (4.0 + (2 * S + 1) * mn / 3e6);
+      consider(S, M, N, ks, us);
+    }
+  }
+  return best;
+}
+
+template <int TERMS>
+void launch_images(const Product<float>& p, bool ta, bool tb, int conj, const ImagePlan& g) {
+  using TS = ImageTiles<TERMS>;
+  const TileCost& c = TS::cost[g.tile];
+  const long long mn = (long long)p.M * p.N;
+  auto convert = [&](bool kc, const float* X, long long ld, int R, int K, int pad, int cj, unsigned short* img) {
+    const dim3 grid((K + BKS - 1) / BKS, (unsigned)(ceil_to(R, pad) / IROWS));
+    if (kc) hipLaunchKernelGGL((terms_kernel<true, TERMS>), grid, dim3(256), 0, p.s, X, ld, R, K, cj, img);
+    else hipLaunchKernelGGL((terms_kernel<false, TERMS>), grid, dim3(256), 0, p.s, X, ld, R, K, cj, img);
+  };
+  for (long long k0 = 0; k0 < p.K; k0 += g.ks) {
+    const int K = (int)std::min<long long>(g.ks, p.K - k0), nkc = (K + BKS - 1) / BKS;
+    const int Kc = (int)ceil_to((K + g.S - 1) / g.S, BKS), S = (K + Kc - 1) / Kc;
+    unsigned short* ia = static_cast<unsigned short*>(p.ws);
+    unsigned short* ib = ia + image_bytes<TERMS>(g.ms, K, c.tm) / 2;
+    float* part = reinterpret_cast<float*>(ib + image_bytes<TERMS>(g.ns, K, c.tn) / 2);
+    const float br = k0 ? 1.f : p.br, bi = k0 ? 0.f : p.bi;
+    // rows m0 .. of A, columns n0 .. of B; at most one of the two is cut
+    auto a_rows = [&](long long m0, int M) {
+      convert(!ta, p.A + 2 * (ta ? k0 * p.lda + m0 : m0 * p.lda + k0), p.lda, M, K, c.tm, conj & 1, ia);
+    };
+    if (g.ms >= p.M) a_rows(0, p.M);
+    for (long long n0 = 0; n0 < p.N; n0 += g.ns) {
+      const int N = (int)std::min<long long>(g.ns, p.N - n0);
+      convert(tb, p.B + 2 * (tb ? n0 * p.ldb + k0 : k0 * p.ldb + n0), p.ldb, N, K, c.tn, conj & 2, ib);
+      for (long long m0 = 0; m0 < p.M; m0 += g.ms) {
+        const int M = (int)std::min<long long>(g.ms, p.M - m0);
+        if (g.ms < p.M) a_rows(m0, M);
+        const dim3 grid((N + c.tn - 1) / c.tn, (M + c.tm - 1) / c.tm, S);
+        float* C = p.C + 2 * (m0 * p.ldc + n0);
+        auto product = [&](auto tl) {
+          using TL = decltype(tl);
+          if (S == 1)
+            hipLaunchKernelGGL((gemm_image_kernel<TL>), grid, dim3(TL::NTH), 0, p.s, M, N, K, p.ar, p.ai, ia, ib, nkc, br,
+                               bi, C, p.ldc, 1, Kc, 0LL);
+          else
+            hipLaunchKernelGGL((gemm_image_kernel<TL>), grid, dim3(TL::NTH), 0, p.s, M, N, K, 1.f, 0.f, ia, ib, nkc, 0.f,
+                               0.f, part, (long long)N, S, Kc, mn);
+        };
+        if (g.tile == 0) product(typename TS::T0{});
+        else product(typename TS::T1{});
+        if (S > 1)
+          hipLaunchKernelGGL(splitk_reduce_kernel<float>, dim3((unsigned)((mn + 255) / 256)), dim3(256), 0, p.s, part, S,
+                             (long long)M, (long long)N, p.ar, p.ai, br, bi, C, p.ldc);
       }
     }
   }
@@ -1107,7 +1429,22 @@ void launch_gemm_mode(const Product<T>& p) {
     choose_direct_tile<TA, TB>(M, N, K, batch, S, &tile, &in_block);
     if (p.lda >= LD_WIDE64 || p.ldb >= LD_WIDE64) in_block = false;
   } else {
-    choose_split_tile<TERMS>(M, N, K, batch, p.ws_bytes, &tile, &S);
+    const double us = choose_split_tile<TERMS>(M, N, K, batch, p.ws_bytes, &tile, &S);
+    // on term images where those take less time: large products, and long ones
+    // whose few tiles repeat the conversion one after the other
+    if constexpr (TERMS < 3) {
+      Product<float> q = p;
+      const size_t skip = (256 - reinterpret_cast<uintptr_t>(p.ws) % 256) % 256;
+      if (batch == 1 && K > 0 && p.ws && p.ws_bytes > skip) {
+        q.ws = static_cast<char*>(p.ws) + skip;
+        q.ws_bytes -= skip;
+        const ImagePlan g = choose_images<TERMS>(M, N, K, q.ws_bytes);
+        if (g.us > 0.0 && g.us < us) {
+          launch_images<TERMS>(q, TA, TB, CONJ, g);
+          return;
+        }
+      }
+    }
   }
   if (S == 1) {
     launch(tile, 0, p.C, p.ldc, p.sc, false, 1, std::max(K, 1), 0, nullptr, nullptr);
@@ -1164,7 +1501,6 @@ void dispatch_b(hipStream_t s, int opb, int M, int N, int K, zc alpha, const voi
 constexpr int WNT = 256;
 constexpr int WMAX_CH = 256;   // channels (MPO index x physical index) of a charged stage
 
-typedef float f4u __attribute__((ext_vector_type(4), aligned(8)));
 
 template <typename T, int V, bool CHARGED>
 __global__ __launch_bounds__(WNT) void wapply_kernel(const T* __restrict__ in, T* __restrict__ out, long long nQ,
