@@ -11,6 +11,8 @@
 // becomes H_k^H A H_k = A - v w^H - w v^H with x = tau A v,
 // w = x - (tau/2)(x^H v) v.  Q = H_0 H_1 ... H_{n-2} is accumulated row by row.
 //
+// Two kernels: tridiag_row_kernel where every row has a wave of its own (n <= 512,
+// unless many charge blocks share the launch), tridiag_kernel elsewhere.
 // A library call per column costs a few microseconds of dispatch on this GPU,
 // so the whole reduction is one launch: G workgroups keep the matrix rows
 // (row r on workgroup r % G) and the matching rows of Q in LDS and exchange
@@ -26,6 +28,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "common.h"
 #include "wave.h"
@@ -43,6 +46,7 @@ constexpr int TD_LDS_BIG = 4096;
 constexpr int TD_NMAX_BIG = 1024;
 constexpr int TD_G_BIG = 256;
 constexpr int TD_ROWS = 128;        // rows per workgroup at most
+constexpr int TD_ROWBUF = 4;        // buffers of published pivot rows
 constexpr unsigned SPIN_LIMIT = 1u << 22;
 
 struct TdArgs {
@@ -50,9 +54,9 @@ struct TdArgs {
   double2* Q;         // n x n out, row-major
   double* D;          // n out
   double* E;          // n-1 out
-  // tagged words (four per complex, zero at launch), two buffers each:
+  // tagged words (four per complex, zero at launch):
   unsigned long long* xv;     // published x = tau A v, 2 x n
-  unsigned long long* prow;   // published pivot row, 2 x n
+  unsigned long long* prow;   // published pivot row, TD_ROWBUF x n (2 in use by tridiag_kernel)
   int* err;                   // 0 at launch; 1 when a wait ran out
   int n, G, R;
 };
@@ -369,6 +373,293 @@ __global__ __launch_bounds__(TNT) void tridiag_kernel(TdBatch batch) {
   }
 }
 
+// n <= 512 with at most one row per wave.  What bounds it: a column's x is
+// published when the one before is complete, which takes a write and a read
+// past the XCDs' L2 (about 1.4 us together) and what a wave does in between.
+// So the rows of A and Q and the column's vectors are in registers, entry c of
+// each on lane c % 64 of register q (the last of TD_NQ, so that the registers
+// still in use are known at compile time: phase Q0 runs the columns with k + 1
+// in register Q0), and every wave forms w, the next pivot row and its reflector
+// for itself: one barrier between the arrival of x and the publication of the
+// next.  The pivot row comes a column ahead: its owner publishes row k + 2 while
+// it waits for column k, without that column's update, which its readers make
+// up for while they wait for column k + 1.  Row buffers alternate between four,
+// since a row is read a column after its publication.
+// n = 512: 1285 us, 2.5 a column (tridiag_kernel, rows in LDS, four barriers a
+// column: 2340 and 4.6); eight rows in half as many workgroups: 2390.
+constexpr int TD_NQ = TD_NMAX / 64;
+
+__device__ inline double2 lane_of2(double2 v, int l) { return double2{wave::lane_of(v.x, l), wave::lane_of(v.y, l)}; }
+__device__ inline double sum64(double v) {
+  return wave::rows_sum(wave::row16(v, [](double x, double y) { return x + y; }));
+}
+// the registers hold their values here: what is to be done in the shadow of a
+// wait is not moved behind it
+template <int N> __device__ inline void settle(double2 (&x)[N], int from) {
+#pragma unroll
+  for (int q = 0; q < N; ++q)
+    if (q >= from) asm volatile("" : "+v"(x[q].x), "+v"(x[q].y));
+}
+
+// Publish v under tag t in three words, `step` apart: 43, 43 and 42 bits of the
+// 128 above a tag of 21.
+constexpr int TD_TAG = 21;
+__device__ inline void put_packed(unsigned long long* w, double2 v, unsigned t, int step) {
+  const unsigned long long x = (unsigned long long)__double_as_longlong(v.x);
+  const unsigned long long y = (unsigned long long)__double_as_longlong(v.y);
+  __hip_atomic_store(w, x << TD_TAG | t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __hip_atomic_store(w + step, (y << 21 | x >> 43) << TD_TAG | t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __hip_atomic_store(w + 2 * step, y >> 22 << TD_TAG | t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// M published entries a thread, from column c on in steps of the workgroup: the
+// words as they are now (columns past the last read the last one).  Word i of
+// column c at i n + c, so that a wave's load takes four lines: every workgroup
+// reads every entry past its L2, and those requests are what the exchange waits
+// for (n = 512: four words side by side 1620 us, apart 1515).
+template <int M> struct TdWords {
+  unsigned long long u[M][3];
+  const unsigned long long* at[M];
+  int step;
+  __device__ inline void point(const unsigned long long* w, int c, int n) {
+    step = n;
+#pragma unroll
+    for (int m = 0; m < M; ++m) at[m] = w + min(c + m * TNT, n - 1);
+  }
+  __device__ inline void read() {
+#pragma unroll
+    for (int m = 0; m < M; ++m)
+#pragma unroll
+      for (int i = 0; i < 3; ++i) u[m][i] = __hip_atomic_load(at[m] + i * step, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  __device__ inline bool have(unsigned t) const {
+    bool all = true;
+#pragma unroll
+    for (int m = 0; m < M; ++m)
+#pragma unroll
+      for (int i = 0; i < 3; ++i) all = all && ((unsigned)u[m][i] & ((1u << TD_TAG) - 1)) == t;
+    return all;
+  }
+  // until all carry tag t; false when the wait ran out
+  __device__ inline bool await(unsigned t, int* err) {
+    for (unsigned polls = 0; !have(t);) {
+      ++polls;
+      if (polls > SPIN_LIMIT ||
+          ((polls & 63u) == 0 && __hip_atomic_load(err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0)) {
+        __hip_atomic_store(err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        return false;
+      }
+      read();
+    }
+    return true;
+  }
+  __device__ inline void store(double2* x, int c, int n) const {
+#pragma unroll
+    for (int m = 0; m < M; ++m)
+      if (c + m * TNT < n) {
+        const unsigned long long p = u[m][1] >> TD_TAG;   // 21 bits of x, 22 of y
+        x[c + m * TNT] = double2{__longlong_as_double((long long)(u[m][0] >> TD_TAG | p << 43)),
+                                 __longlong_as_double((long long)(p >> 21 | (u[m][2] >> TD_TAG) << 22))};
+      }
+  }
+};
+
+__global__ __launch_bounds__(TNT, 1) void tridiag_row_kernel(TdBatch batch) {
+  __shared__ double2 sx[TD_NMAX], sr[TD_NMAX];   // the gathered x and row, zero from n on
+  __shared__ int s_fail;
+  int sec = 0;
+  while (sec + 1 < batch.nsec && batch.wg0[sec + 1] <= (int)blockIdx.x) ++sec;
+  const TdArgs a = batch.sec[sec];
+  const int n = a.n, G = a.G, g = (int)blockIdx.x - batch.wg0[sec], tid = threadIdx.x;
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int qb = TD_NQ - (n + 63) / 64;          // first register in use
+  const int r = g + wave * G;                    // the wave's row
+  const bool own = r < n;
+  const int lc = lane - 64 * qb;                 // column of register q: lc + 64 q
+
+  double2 A[TD_NQ], Q[TD_NQ], v[TD_NQ], vp[TD_NQ], w[TD_NQ], row[TD_NQ];
+  double xn2 = 0.0;
+#pragma unroll
+  for (int q = 0; q < TD_NQ; ++q) {
+    const int c = lc + 64 * q;
+    const bool in = c >= 0 && c < n;
+    A[q] = in && own ? a.H[(size_t)r * n + c] : double2{0.0, 0.0};
+    Q[q] = double2{own && r == c ? 1.0 : 0.0, 0.0};
+    row[q] = in ? a.H[c] : double2{0.0, 0.0};
+    v[q] = vp[q] = w[q] = double2{0.0, 0.0};
+    if (c >= 2) xn2 += row[q].x * row[q].x + row[q].y * row[q].y;
+  }
+  xn2 = sum64(xn2);
+  for (int c = tid; c < TD_NMAX; c += TNT) sx[c] = sr[c] = double2{0.0, 0.0};
+  if (tid == 0) {
+    s_fail = 0;
+    if (g == 0) a.D[0] = a.H[0].x;
+  }
+  __syncthreads();
+
+  bool alive = true;
+  auto phase = [&](auto first) {
+    constexpr int Q0 = decltype(first)::value;
+    constexpr int M = (64 * (TD_NQ - Q0) + TNT - 1) / TNT;   // columns a thread gathers (G <= TNT)
+    const int c0 = 64 * (Q0 - qb);
+    for (int k = max(c0 - 1, 0); k + 1 < min(n, c0 + 64) && alive; ++k) {
+      // ---- reflector k from the pivot row; x = tau A v, published
+      const int l1 = (k + 1) & 63, cq = lc + 64 * Q0;   // the lane of column k + 1; column of register Q0
+      const Reflector hr = reflector(lane_of2(row[Q0], l1), xn2);
+      const double2 tau = hr.tau, sc = hr.sc;
+      double2 s{0.0, 0.0};
+#pragma unroll
+      for (int q = Q0; q < TD_NQ; ++q) {
+        v[q] = cmul(double2{row[q].x, -row[q].y}, sc);
+        if (q == Q0) {
+          v[q].x = cq > k + 1 ? v[q].x : cq == k + 1 ? 1.0 : 0.0;
+          v[q].y = cq > k + 1 ? v[q].y : 0.0;
+        }
+        const double2 p = cmul(A[q], v[q]);
+        s.x += p.x;
+        s.y += p.y;
+      }
+      s.x = sum64(s.x);
+      s.y = sum64(s.y);
+      const unsigned tag = (unsigned)k + 1u;
+      unsigned long long* xvp = a.xv + (size_t)(k & 1) * 4 * n;
+      if (own && lane == 0 && (r >= k + 1 || r >= n - G))
+        put_packed(xvp + r, r >= k + 1 ? cmul(tau, s) : double2{0.0, 0.0}, tag, n);
+
+      // ---- while the others' x arrives: row k + 1, published during column k - 1
+      TdWords<M> words;
+      if (k > 0) {
+        words.point(a.prow + (size_t)((k + 1) & (TD_ROWBUF - 1)) * 4 * n, k + 1 + tid, n);
+        words.read();
+      }
+      // row k + 2 as it stands, for the next column
+      if (own && r == k + 2) {
+        unsigned long long* rowp = a.prow + (size_t)(r & (TD_ROWBUF - 1)) * 4 * n;
+#pragma unroll
+        for (int q = Q0; q < TD_NQ; ++q) {
+          const int c = lc + 64 * q;
+          if (c >= k + 2 && c < n) put_packed(rowp + c, A[q], (unsigned)r, n);
+        }
+      }
+      if (g == 0 && tid == 0) a.E[k] = hr.beta;
+      // Q <- Q H_k = Q - tau (Q v) v^H
+      double2 sq{0.0, 0.0};
+#pragma unroll
+      for (int q = Q0; q < TD_NQ; ++q) {
+        const double2 p = cmul(Q[q], v[q]);
+        sq.x += p.x;
+        sq.y += p.y;
+      }
+      sq = cmul(tau, double2{sum64(sq.x), sum64(sq.y)});
+#pragma unroll
+      for (int q = Q0; q < TD_NQ; ++q) {
+        const double2 d = cmulc(sq, v[q]);
+        Q[q].x -= d.x;
+        Q[q].y -= d.y;
+      }
+      settle(Q, Q0);
+      if (k == 0) {
+        for (int c = tid + 1; c < n; c += TNT) sr[c] = a.H[(size_t)n + c];
+      } else {
+        if (!words.await(tag, a.err)) s_fail = 1;
+        words.store(sr, k + 1 + tid, n);
+      }
+      // x from row k + 1 on, and at least one entry of every workgroup: none gets
+      // so far ahead of another that it overwrites what that one has yet to read
+      const int xc = min(k + 1, n - G) + tid;
+      __syncthreads();
+      // a first look at x any earlier mostly finds it incomplete, and the second
+      // comes a round trip later (before the barrier: 1490 us at n = 512; after the
+      // row's update: 1370; here: 1285)
+      words.point(xvp, xc, n);
+      words.read();
+      {   // the update of column k - 1
+        const double2 v1 = lane_of2(vp[Q0], l1), w1 = lane_of2(w[Q0], l1);
+#pragma unroll
+        for (int q = Q0; q < TD_NQ; ++q) {
+          const double2 t = sr[lc + 64 * q];
+          const double2 d1 = cmulc(v1, w[q]), d2 = cmulc(w1, vp[q]);
+          row[q] = double2{t.x - (d1.x + d2.x), t.y - (d1.y + d2.y)};
+          vp[q] = v[q];
+        }
+      }
+      settle(row, Q0);
+      settle(vp, Q0);
+      // ---- x
+      if (!words.await(tag, a.err)) s_fail = 1;
+      words.store(sx, xc, n);
+      __syncthreads();
+      if (s_fail) alive = false;
+
+      // ---- w = x - (tau / 2)(x^H v) v; the next pivot row and its norm beyond column k + 2
+      double2 t{0.0, 0.0};
+#pragma unroll
+      for (int q = Q0; q < TD_NQ; ++q) {
+        w[q] = sx[lc + 64 * q];
+        if (q == Q0) {
+          w[q].x = cq > k ? w[q].x : 0.0;
+          w[q].y = cq > k ? w[q].y : 0.0;
+        }
+        const double2 p = cmulc(v[q], w[q]);
+        t.x += p.x;
+        t.y += p.y;
+      }
+      const double2 a2x = cmul(tau, double2{sum64(t.x), sum64(t.y)});
+      const double2 a2{-0.5 * a2x.x, -0.5 * a2x.y};
+#pragma unroll
+      for (int q = Q0; q < TD_NQ; ++q) {
+        const double2 tv = cmul(a2, v[q]);
+        w[q].x += tv.x;
+        w[q].y += tv.y;
+      }
+      const double2 w1 = lane_of2(w[Q0], l1);   // v_{k+1} = 1
+      xn2 = 0.0;
+#pragma unroll
+      for (int q = Q0; q < TD_NQ; ++q) {
+        const double2 d = cmulc(w1, v[q]);
+        row[q].x -= w[q].x + d.x;
+        row[q].y -= d.y - w[q].y;
+        const double2 p{row[q].x * row[q].x, row[q].y * row[q].y};
+        xn2 += q > Q0 + 1 || lc + 64 * q >= k + 3 ? p.x + p.y : 0.0;
+      }
+      xn2 = sum64(xn2);
+      if (g == 0 && tid == l1) a.D[k + 1] = row[Q0].x;
+      // ---- A <- A - v w^H - w v^H on rows not finished
+      if (own && r >= k + 2) {
+        double2 vr{0.0, 0.0}, wr{0.0, 0.0};
+        const int qr = qb + (r >> 6);
+#pragma unroll
+        for (int q = Q0; q < TD_NQ; ++q)
+          if (q == qr) {
+            vr = lane_of2(v[q], r & 63);
+            wr = lane_of2(w[q], r & 63);
+          }
+#pragma unroll
+        for (int q = Q0; q < TD_NQ; ++q) {
+          const double2 d1 = cmulc(vr, w[q]), d2 = cmulc(wr, v[q]);
+          A[q].x -= d1.x + d2.x;
+          A[q].y -= d1.y + d2.y;
+        }
+      }
+    }
+  };
+  if (qb <= 0) phase(std::integral_constant<int, 0>());
+  if (qb <= 1) phase(std::integral_constant<int, 1>());
+  if (qb <= 2) phase(std::integral_constant<int, 2>());
+  if (qb <= 3) phase(std::integral_constant<int, 3>());
+  if (qb <= 4) phase(std::integral_constant<int, 4>());
+  if (qb <= 5) phase(std::integral_constant<int, 5>());
+  if (qb <= 6) phase(std::integral_constant<int, 6>());
+  phase(std::integral_constant<int, 7>());
+
+  if (alive && own)
+#pragma unroll
+    for (int q = 0; q < TD_NQ; ++q) {
+      const int c = lc + 64 * q;
+      if (c >= 0 && c < n) a.Q[(size_t)r * n + c] = Q[q];
+    }
+}
+
 // rows[j][m] = Z[m][n-1-j] as complex, Z column-major real (eigenvector j'
 // contiguous): the eigenvectors of the tridiagonal matrix in descending order
 __global__ void zrows_from_real_kernel(double2* __restrict__ out, const double* __restrict__ Z, int n) {
@@ -529,7 +820,7 @@ int tridiag_groups(int n) {
 
 size_t tridiag_scratch_bytes(int n) {
   const int G = tridiag_groups(n);
-  return G == 0 ? 0 : sizeof(unsigned long long) * 4 * 4 * (size_t)n + 256;
+  return G == 0 ? 0 : sizeof(unsigned long long) * 4 * (2 + TD_ROWBUF) * (size_t)n + 256;
 }
 
 hipError_t tridiag(hipStream_t s, const void* H, int n, void* Q, double* D, double* E, void* scratch, int* err) {
@@ -568,7 +859,7 @@ hipError_t tridiag_batched(hipStream_t s, const TdSector* sec, int nsec, int* er
     int mx = 1;
     for (int i = i0; i < std::min(nsec, i0 + TD_RESET_MAX); ++i) {
       r.w[r.n] = static_cast<unsigned*>(sec[i].scratch);
-      r.nw[r.n] = 2 * 4 * 4 * sec[i].n;   // 32-bit halves of the tagged words
+      r.nw[r.n] = 2 * 4 * (2 + TD_ROWBUF) * sec[i].n;   // 32-bit halves of the tagged words
       mx = std::max(mx, r.nw[r.n]);
       ++r.n;
     }
@@ -609,6 +900,7 @@ hipError_t tridiag_batched(hipStream_t s, const TdSector* sec, int nsec, int* er
       }
       TdBatch b{};
       int wg = 0;
+      bool one_row = !big;   // a wave for every row
       for (size_t j = 0; j < grp.size(); ++j) {
         const TdSector& x = sec[grp[j]];
         TdArgs& a = b.sec[j];
@@ -624,12 +916,14 @@ hipError_t tridiag_batched(hipStream_t s, const TdSector* sec, int nsec, int* er
         a.R = (x.n + G[j] - 1) / G[j];
         b.wg0[j] = wg;
         wg += G[j];
+        one_row = one_row && a.R <= TNT / 64;
       }
       b.wg0[grp.size()] = wg;
       b.nsec = (int)grp.size();
       void* args[] = {&b};
       const void* kfn = big ? reinterpret_cast<const void*>(tridiag_kernel<TD_NMAX_BIG, TD_LDS_BIG, false>)
-                            : reinterpret_cast<const void*>(tridiag_kernel<TD_NMAX, TD_LDS, true>);
+                    : one_row ? reinterpret_cast<const void*>(tridiag_row_kernel)
+                              : reinterpret_cast<const void*>(tridiag_kernel<TD_NMAX, TD_LDS, true>);
       const hipError_t e = hipLaunchCooperativeKernel(kfn, dim3(wg), dim3(TNT), args, (unsigned)lds, s);
       if (e != hipSuccess) return e;
     }
