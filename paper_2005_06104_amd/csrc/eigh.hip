@@ -390,7 +390,10 @@ __global__ __launch_bounds__(TNT) void tridiag_kernel(TdBatch batch) {
 constexpr int TD_NQ = TD_NMAX / 64;
 
 __device__ inline double2 lane_of2(double2 v, int l) { return double2{wave::lane_of(v.x, l), wave::lane_of(v.y, l)}; }
+// sum over the wave, the same bits on every lane (a product is rounded before it
+// is added: contracted, a lane's own would not be)
 __device__ inline double sum64(double v) {
+  asm("" : "+v"(v));
   return wave::rows_sum(wave::row16(v, [](double x, double y) { return x + y; }));
 }
 // the registers hold their values here: what is to be done in the shadow of a

@@ -178,9 +178,10 @@ __global__ __launch_bounds__(1024) void dc_init_kernel(const DcInitBatch bt) {
 
 // ---------------------------------------------------------------- level kernels
 // Preparation, one workgroup per node: z, sign, sort by merging the two
-// sorted children, deflation: small z entries in parallel, then one thread
-// walks the remaining entries in sorted order (the pair tests precomputed,
-// recomputed only after a rotation changed the left entry).
+// sorted children, deflation: small z entries and the tests of neighbouring
+// pairs in parallel; one thread visits only the pairs that deflate (with the
+// test recomputed where a rotation changed the left entry), since a thread's
+// walk over every entry took 146 us of an eigendecomposition at n = 512, now 26.
 __global__ __launch_bounds__(DC_PREP_NT) void dc_prep_kernel(const DcBatch bt) {
   if ((int)blockIdx.y >= bt.n) return;
   const DcArgs a = bt.a[blockIdx.y];
@@ -188,10 +189,10 @@ __global__ __launch_bounds__(DC_PREP_NT) void dc_prep_kernel(const DcBatch bt) {
   __shared__ double s_ds[DC_PMAX], s_zs[DC_PMAX];
   __shared__ int s_nd[DC_PMAX], s_inv[DC_PMAX];
   __shared__ double s_max[DC_PREP_NT / 64];
-  __shared__ int s_lst[DC_PMAX], s_pd[DC_PMAX];
+  __shared__ int s_lst[DC_PMAX], s_keep[DC_PMAX];
+  __shared__ unsigned long long s_pd[DC_PREP_NT / 64];
   __shared__ double s_pc[DC_PMAX], s_ps[DC_PMAX], s_pt[DC_PMAX];
   __shared__ int s_wcnt[DC_PREP_NT / 64];
-  __shared__ int s_K;
   const int b = blockIdx.x, s = a.s, h = s / 2, P = a.P, tid = threadIdx.x;
   const int base = b * s;
   const double coupling = a.E[base + h - 1];
@@ -248,6 +249,7 @@ __global__ __launch_bounds__(DC_PREP_NT) void dc_prep_kernel(const DcBatch bt) {
   __syncthreads();
   // the test of each neighbouring pair with the values before any rotation;
   // it stands unless the left entry has just received a rotation
+  bool pair = false;
   if (tid + 1 < L) {
     const int p = s_lst[tid], q = s_lst[tid + 1];
     const double sv = s_zs[p], cv = s_zs[q];
@@ -256,31 +258,24 @@ __global__ __launch_bounds__(DC_PREP_NT) void dc_prep_kernel(const DcBatch bt) {
     s_pc[tid] = c;
     s_ps[tid] = sn;
     s_pt[tid] = ta;
-    s_pd[tid] = fabs((s_ds[q] - s_ds[p]) * c * sn) <= tol ? 1 : 0;
+    pair = fabs((s_ds[q] - s_ds[p]) * c * sn) <= tol;
   }
+  const unsigned long long pairs = __ballot(pair);
+  if (lane == 0) s_pd[wv] = pairs;
+  s_keep[tid] = tid < L;
   __syncthreads();
   if (tid == 0) {
-    int K = 0, m = 0;
-    bool rotated = false;
-    int pj = L > 0 ? s_lst[0] : -1;
-    for (int k = 1; k < L; ++k) {
-      const int j = s_lst[k];
-      double c, sn, ta;
-      bool defl;
-      if (!rotated) {
-        c = s_pc[k - 1];
-        sn = s_ps[k - 1];
-        ta = s_pt[k - 1];
-        defl = s_pd[k - 1] != 0;
-      } else {
-        const double sv = s_zs[pj], cv = s_zs[j];
-        ta = hypot(cv, sv);
-        c = cv / ta;
-        sn = -sv / ta;
-        defl = fabs((s_ds[j] - s_ds[pj]) * c * sn) <= tol;
-      }
-      if (defl) {
+    int m = 0;
+    for (int k = 0; k + 1 < L; ++k) {
+      int w = k >> 6;
+      unsigned long long bits = s_pd[w] >> (k & 63) << (k & 63);
+      while (bits == 0 && ++w < DC_PREP_NT / 64) bits = s_pd[w];
+      if (bits == 0) break;
+      k = 64 * w + __ffsll((long long)bits) - 1;
+      double c = s_pc[k], sn = s_ps[k], ta = s_pt[k];
+      while (true) {
         // rotate (pj, j): z_pj -> 0, z_j -> ta; pj keeps the mixed pole
+        const int pj = s_lst[k], j = s_lst[k + 1];
         s_zs[j] = ta;
         s_zs[pj] = 0.0;
         a.rp[base + m] = pj;
@@ -291,28 +286,37 @@ __global__ __launch_bounds__(DC_PREP_NT) void dc_prep_kernel(const DcBatch bt) {
         const double dp = s_ds[pj], dj = s_ds[j];
         s_ds[pj] = dp * c * c + dj * sn * sn;
         s_ds[j] = dp * sn * sn + dj * c * c;
-        rotated = true;
-      } else {
-        s_nd[K] = pj;
-        s_inv[pj] = K;
-        ++K;
-        rotated = false;
+        s_keep[k] = 0;
+        if (++k + 1 >= L) break;
+        const int q = s_lst[k + 1];
+        const double sv = s_zs[j], cv = s_zs[q];
+        ta = hypot(cv, sv);
+        c = cv / ta;
+        sn = -sv / ta;
+        if (!(fabs((s_ds[q] - s_ds[j]) * c * sn) <= tol)) break;   // entry k stays
       }
-      pj = j;
     }
-    if (pj >= 0) {
-      s_nd[K] = pj;
-      s_inv[pj] = K;
-      ++K;
-    }
-    s_K = K;
-    a.cnt[2 * b] = K;
     a.cnt[2 * b + 1] = m;
     a.par[2 * b] = sgn;
     a.par[2 * b + 1] = r;
   }
   __syncthreads();
-  const int K = s_K;
+  // what is left, compacted again
+  const bool kept = s_keep[tid] != 0;
+  const unsigned long long kbal = __ballot(kept);
+  if (lane == 0) s_wcnt[wv] = __popcll(kbal);
+  __syncthreads();
+  int koff = __popcll(kbal & ((1ull << lane) - 1)), K = 0;
+  for (int w = 0; w < DC_PREP_NT / 64; ++w) {
+    if (w < wv) koff += s_wcnt[w];
+    K += s_wcnt[w];
+  }
+  if (kept) {
+    s_nd[koff] = s_lst[tid];
+    s_inv[s_lst[tid]] = koff;
+  }
+  if (tid == 0) a.cnt[2 * b] = K;
+  __syncthreads();
   for (int j = tid; j < s; j += DC_PREP_NT) {
     a.ds[base + j] = s_ds[j];
     a.ndinv[base + j] = s_inv[j];
@@ -579,14 +583,28 @@ __global__ void dc_finish_kernel(const DcFinishBatch bt) {
 
 // ---------------------------------------------------------------- small levels
 // Levels with nodes of 2 .. DC_LEAF entries, all in one launch: one workgroup
-// per block of DC_LEAF leaves, everything in LDS, one thread per entry, root or
-// node (the same steps as the level kernels, with the sums over a node's at
-// most DC_LEAF poles taken serially by one thread).  On return d holds each
-// block's eigenvalues (ascending) and Z its diagonal block of eigenvectors
-// (the rest of Z is the identity's zeros).
+// per block of DC_LEAF leaves, everything in LDS, a row of 16 lanes per entry
+// or root and a lane per pole (the same steps as the level kernels).  A chain
+// of FP64 divisions and roots: with the poles one after the other in a thread
+// 68 us, a lane each 28.  On return d holds each block's eigenvalues
+// (ascending) and Z its diagonal block of eigenvectors (the rest of Z is the
+// identity's zeros).
 constexpr int DC_LEAF = 16;
 constexpr int DC_LNT = 256;
-static_assert(DC_LNT >= DC_LEAF * 2, "leaf kernel thread count");
+static_assert(DC_LNT == DC_LEAF * DC_LEAF && DC_LEAF == 16, "a row of 16 lanes per entry");
+
+// Sum over a row of 16 lanes, the same bits on each: a product among the terms is
+// rounded first (contracted into the first sum, a lane's own product would be
+// exact and its neighbour's rounded, and the lanes of a root would part ways).
+__device__ inline double row_sum(double v) {
+  asm("" : "+v"(v));
+  return wave::row16(v, [](double x, double y) { return x + y; });
+}
+// what a wave's lanes have written to LDS is there for its other lanes
+__device__ inline void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+  __builtin_amdgcn_wave_barrier();
+}
 
 __global__ __launch_bounds__(DC_LNT) void dc_leaf_kernel(const DcLeafBatch bt) {
   if ((int)blockIdx.y >= bt.n) return;
@@ -603,7 +621,8 @@ __global__ __launch_bounds__(DC_LNT) void dc_leaf_kernel(const DcLeafBatch bt) {
   __shared__ int s_perm[DC_LEAF], s_inv[DC_LEAF], s_nd[DC_LEAF], s_rp[DC_LEAF], s_rq[DC_LEAF], s_orig[DC_LEAF];
   __shared__ int s_col[DC_LEAF];
   __shared__ int s_K[DC_LEAF], s_m[DC_LEAF];
-  __shared__ double s_sgn[DC_LEAF], s_r[DC_LEAF];
+  __shared__ double s_sgn[DC_LEAF], s_r[DC_LEAF], s_pc[DC_LEAF], s_ps[DC_LEAF], s_pt[DC_LEAF];
+  __shared__ unsigned s_drop[DC_LEAF];
   const int tid = threadIdx.x, g0 = blockIdx.x * S0;
   constexpr double EPS = 2.220446049250313e-16;
   for (int e = tid; e < S0 * S0; e += DC_LNT) sZ[e / S0][e % S0] = (e / S0 == e % S0) ? 1.0 : 0.0;
@@ -643,171 +662,192 @@ __global__ __launch_bounds__(DC_LNT) void dc_leaf_kernel(const DcLeafBatch bt) {
       s_inv[base + rank] = -1;
     }
     __syncthreads();
-    // ---- deflation, one thread per node (at most DC_LEAF entries)
-    if (tid < nn) {
-      const int base = tid * s;
-      const double r = s_r[tid];
+    // ---- deflation: the tests in parallel, the pairs that deflate by one thread a node
+    if (tid < 64) {
+      const bool in = tid < S0;
+      const int b = in ? tid / s : 0, base = b * s, end = base + s;
+      const double r = s_r[b];
       double dm = 0.0;
-      for (int j = 0; j < s; ++j) dm = fmax(dm, fabs(s_ds[base + j]));
+      for (int j = base; j < end; ++j) dm = fmax(dm, fabs(s_ds[j]));
       const double tol = 8.0 * EPS * fmax(dm, r);
-      int K = 0, m = 0, pj = -1;
-      for (int j = 0; j < s; ++j) {
-        if (!(r * fabs(s_zs[base + j]) > tol)) continue;   // z entry deflated
-        if (pj < 0) {
-          pj = j;
-          continue;
+      const bool live = in && r * fabs(s_zs[in ? tid : 0]) > tol;
+      const unsigned lives = (unsigned)__ballot(live);
+      // the next live entry of the node
+      const unsigned after = in ? (lives >> (tid + 1) << (tid + 1)) & ((1u << end) - 1) : 0u;
+      const int nxt = __ffs((int)after) - 1;
+      double c = 0.0, sn = 0.0, ta = 0.0;
+      bool pair = false;
+      if (live && nxt >= 0) {
+        const double sv = s_zs[tid], cv = s_zs[nxt];
+        ta = hypot(cv, sv);
+        c = cv / ta;
+        sn = -sv / ta;
+        pair = fabs((s_ds[nxt] - s_ds[tid]) * c * sn) <= tol;
+      }
+      const unsigned pairs = (unsigned)__ballot(pair);
+      if (in) {
+        s_pc[tid] = c;
+        s_ps[tid] = sn;
+        s_pt[tid] = ta;
+      }
+      wave_lds_fence();
+      unsigned keep = lives;
+      if (in && tid == base) {
+        const unsigned mine = ((1u << end) - 1) & ~((1u << base) - 1);
+        unsigned todo = pairs & mine, drop = 0;
+        int m = 0;
+        while (todo) {
+          int pj = __ffs((int)todo) - 1;
+          double cc = s_pc[pj], cs = s_ps[pj], ct = s_pt[pj];
+          while (true) {
+            const int j = __ffs((int)(lives >> (pj + 1) << (pj + 1) & mine)) - 1;
+            s_zs[j] = ct;
+            s_zs[pj] = 0.0;
+            s_rp[base + m] = pj - base;
+            s_rq[base + m] = j - base;
+            s_rc[base + m] = cc;
+            s_rs[base + m] = cs;
+            ++m;
+            const double dp = s_ds[pj], dj = s_ds[j];
+            s_ds[pj] = dp * cc * cc + dj * cs * cs;
+            s_ds[j] = dp * cs * cs + dj * cc * cc;
+            drop |= 1u << pj;
+            pj = j;
+            const int q = __ffs((int)(lives >> (pj + 1) << (pj + 1) & mine)) - 1;
+            if (q < 0) break;
+            const double sv = s_zs[pj], cv = s_zs[q];
+            ct = hypot(cv, sv);
+            cc = cv / ct;
+            cs = -sv / ct;
+            if (!(fabs((s_ds[q] - s_ds[pj]) * cc * cs) <= tol)) break;   // entry pj stays
+          }
+          todo &= ~((2u << pj) - 1);
         }
-        const double sv = s_zs[base + pj], cv = s_zs[base + j];
-        const double ta = hypot(cv, sv);
-        const double c = cv / ta, sn = -sv / ta;
-        if (fabs((s_ds[base + j] - s_ds[base + pj]) * c * sn) <= tol) {
-          s_zs[base + j] = ta;
-          s_zs[base + pj] = 0.0;
-          s_rp[base + m] = pj;
-          s_rq[base + m] = j;
-          s_rc[base + m] = c;
-          s_rs[base + m] = sn;
-          ++m;
-          const double dp = s_ds[base + pj], dj = s_ds[base + j];
-          s_ds[base + pj] = dp * c * c + dj * sn * sn;
-          s_ds[base + j] = dp * sn * sn + dj * c * c;
-        } else {
-          s_nd[base + K] = pj;
-          s_inv[base + pj] = K;
-          ++K;
+        s_m[b] = m;
+        s_drop[b] = drop;
+      }
+      wave_lds_fence();
+      if (in) {
+        keep &= ~s_drop[b];
+        const unsigned mine = ((1u << end) - 1) & ~((1u << base) - 1);
+        if (tid == base) s_K[b] = __popc(keep & mine);
+        if (keep >> tid & 1) {
+          const int i = __popc(keep & mine & ((1u << tid) - 1));
+          s_nd[base + i] = tid - base;
+          s_inv[tid] = i;
+          s_dk[base + i] = s_ds[tid];
+          s_zk[base + i] = s_zs[tid];
         }
-        pj = j;
       }
-      if (pj >= 0) {
-        s_nd[base + K] = pj;
-        s_inv[base + pj] = K;
-        ++K;
-      }
-      for (int i = 0; i < K; ++i) {
-        s_dk[base + i] = s_ds[base + s_nd[base + i]];
-        s_zk[base + i] = s_zs[base + s_nd[base + i]];
-      }
-      s_K[tid] = K;
-      s_m[tid] = m;
     }
     __syncthreads();
-    // ---- secular roots, one thread per (node, root)
-    if (tid < S0) {
-      const int b = tid / s, i = tid % s, base = b * s;
-      const int K = s_K[b];
-      if (i < K) {
-        const double r = s_r[b];
-        const double* dk = s_dk + base;
-        const double* zk = s_zk + base;
-        double zsum = 0.0;
-        for (int j = 0; j < K; ++j) zsum += zk[j] * zk[j];
-        const bool last = i + 1 == K;
-        const double lo_abs = dk[i];
-        const double hi_abs = last ? dk[i] + r * zsum : dk[i + 1];
-        const double mid = 0.5 * (lo_abs + hi_abs);
-        double fm = 0.0;
-        for (int j = 0; j < K; ++j) fm += zk[j] * zk[j] / (dk[j] - mid);
-        fm = 1.0 + r * fm;
-        const int o = (!last && fm <= 0.0) ? i + 1 : i;
-        const double dorg = dk[o];
-        double lo, hi;
-        if (o == i) {
-          lo = 0.0;
-          hi = last ? r * zsum : mid - dorg;
-        } else {
-          lo = mid - dorg;
-          hi = 0.0;
-        }
-        double tau = 0.5 * (lo + hi);
-        for (int it = 0; it < DC_SECULAR_MAXIT; ++it) {
-          double f = 0.0, fp = 0.0, fa = 0.0;
-          for (int j = 0; j < K; ++j) {
-            const double q = 1.0 / ((dk[j] - dorg) - tau);
-            const double tt = zk[j] * zk[j] * q;
-            f += tt;
-            fp += tt * q;
-            fa += fabs(tt);
-          }
-          f = 1.0 + r * f;
-          fp = r * fp;
-          fa = 1.0 + r * fa;
-          if (fabs(f) <= 8.0 * EPS * fa) break;
-          if (f > 0.0) hi = tau;
-          else lo = tau;
-          if (hi - lo <= 2.0 * EPS * fmax(fabs(lo), fabs(hi))) break;
-          double tn = tau - tau * f / (f + tau * fp);
-          if (!(isfinite(tn) && tn > lo && tn < hi)) tn = 0.5 * (lo + hi);
-          if (fabs(tn - tau) <= 2.0 * EPS * fabs(tau)) {
-            tau = tn;
-            break;
-          }
+    const int ent = tid >> 4, ln = tid & 15;            // the row's entry, the lane's pole
+    const bool on = ent < S0;
+    const int nb = on ? ent / s : 0, ne = on ? ent % s : 0, nbase = nb * s;
+    const int K = on ? s_K[nb] : 0;
+    const double sgn = s_sgn[nb], r = s_r[nb];
+    const double* dk = s_dk + nbase;
+    const double* zk = s_zk + nbase;
+    // ---- secular roots, a row each
+    if (ne < K) {
+      const int i = ne;
+      double dj = ln < K ? dk[ln] : 1e300;   // no pole: zero weight far away
+      const double z2 = ln < K ? zk[ln] * zk[ln] : 0.0;
+      const double zsum = row_sum(z2);
+      const bool last = i + 1 == K;
+      const double lo_abs = dk[i];
+      const double hi_abs = last ? dk[i] + r * zsum : dk[i + 1];
+      const double mid = 0.5 * (lo_abs + hi_abs);
+      const double fm = 1.0 + r * row_sum(z2 / (dj - mid));
+      const int o = (!last && fm <= 0.0) ? i + 1 : i;
+      const double dorg = dk[o];
+      dj -= dorg;
+      double lo, hi;
+      if (o == i) {
+        lo = 0.0;
+        hi = last ? r * zsum : mid - dorg;
+      } else {
+        lo = mid - dorg;
+        hi = 0.0;
+      }
+      double tau = 0.5 * (lo + hi);
+      for (int it = 0; it < DC_SECULAR_MAXIT; ++it) {
+        const double q = 1.0 / (dj - tau), tt = z2 * q;
+        const double f = 1.0 + r * row_sum(tt);
+        const double fp = r * row_sum(tt * q);
+        const double fa = 1.0 + r * row_sum(fabs(tt));
+        if (fabs(f) <= 8.0 * EPS * fa) break;
+        if (f > 0.0) hi = tau;
+        else lo = tau;
+        if (hi - lo <= 2.0 * EPS * fmax(fabs(lo), fabs(hi))) break;
+        double tn = tau - tau * f / (f + tau * fp);
+        if (!(isfinite(tn) && tn > lo && tn < hi)) tn = 0.5 * (lo + hi);
+        if (fabs(tn - tau) <= 2.0 * EPS * fabs(tau)) {
           tau = tn;
+          break;
         }
-        s_orig[base + i] = o;
-        s_tau[base + i] = tau;
+        tau = tn;
+      }
+      if (ln == 0) {
+        s_orig[nbase + i] = o;
+        s_tau[nbase + i] = tau;
       }
     }
     __syncthreads();
     // ---- zhat_j (j < K) and the final column of every sorted position
-    if (tid < S0) {
-      const int b = tid / s, j = tid % s, base = b * s;
-      const int K = s_K[b];
-      const double sgn = s_sgn[b], r = s_r[b];
-      const double* dk = s_dk + base;
-      if (j < K) {
-        const double dj = dk[j];
-        double p = 1.0;
-        for (int i = 0; i < K; ++i) {
-          const double num = (dk[s_orig[base + i]] - dj) + s_tau[base + i];
-          p *= i == j ? num / r : num / (dk[i] - dj);
-        }
-        s_zhat[base + j] = copysign(sqrt(fabs(p)), s_zk[base + j]);
+    {
+      const int j = ne;
+      const int org = ln < K ? s_orig[nbase + ln] : 0;
+      const double ta = ln < K ? s_tau[nbase + ln] : 0.0;
+      double p = 1.0;
+      if (j < K && ln < K) {
+        const double num = (dk[org] - dk[j]) + ta;
+        p = ln == j ? num / r : num / (dk[ln] - dk[j]);
       }
+      p = wave::row16(p, [](double x, double y) { return x * y; });
+      if (j < K && ln == 0) s_zhat[nbase + j] = copysign(sqrt(fabs(p)), zk[j]);
       auto value = [&](int q) {
-        const int ri = s_inv[base + q];
-        const double l = ri >= 0 ? dk[s_orig[base + ri]] + s_tau[base + ri] : s_ds[base + q];
+        const int ri = s_inv[nbase + q];
+        const double l = ri >= 0 ? dk[s_orig[nbase + ri]] + s_tau[nbase + ri] : s_ds[nbase + q];
         return sgn * l;
       };
-      const double vj = value(j);
-      int c = 0;
-      for (int q = 0; q < s; ++q) {
-        const double vq = value(q);
-        c += (vq < vj || (vq == vj && q < j)) ? 1 : 0;
+      bool less = false;
+      double vj = 0.0;
+      if (on) {
+        vj = value(j);
+        if (ln < s) {
+          const double vq = value(ln);
+          less = vq < vj || (vq == vj && ln < j);
+        }
       }
-      s_col[base + j] = c;
-      sdn[base + c] = vj;
+      const int c = __popcll(__ballot(less) >> (tid & 48) & 0xffff);
+      if (on && ln == 0) {
+        s_col[nbase + j] = c;
+        sdn[nbase + c] = vj;
+      }
     }
     __syncthreads();
     // ---- eigenvector columns (rotations undone), scattered into the node block of M
-    if (tid < S0) {
-      const int b = tid / s, p = tid % s, base = b * s;
-      double* y = sY[tid];
-      for (int q = 0; q < s; ++q) y[q] = 0.0;
-      const int ri = s_inv[base + p];
-      if (ri < 0) {
-        y[p] = 1.0;
-      } else {
-        const int K = s_K[b];
-        const double* dk = s_dk + base;
-        const double dorg = dk[s_orig[base + ri]], ta = s_tau[base + ri];
-        double nrm = 0.0;
-        for (int j = 0; j < K; ++j) {
-          const double v = s_zhat[base + j] / ((dk[j] - dorg) - ta);
-          y[s_nd[base + j]] = v;
-          nrm += v * v;
+    {
+      const int p = ne, ri = on ? s_inv[nbase + p] : -1;
+      double* y = sY[ent];
+      if (on && ln < s) y[ln] = ri < 0 && ln == p ? 1.0 : 0.0;
+      wave_lds_fence();
+      double v = 0.0;
+      if (ri >= 0 && ln < K) v = s_zhat[nbase + ln] / ((dk[ln] - dk[s_orig[nbase + ri]]) - s_tau[nbase + ri]);
+      const double nrm = row_sum(v * v);
+      if (ri >= 0 && ln < K) y[s_nd[nbase + ln]] = v * (1.0 / sqrt(nrm));
+      wave_lds_fence();
+      if (on && ln == 0)
+        for (int t = s_m[nb] - 1; t >= 0; --t) {
+          const int pp = s_rp[nbase + t], qq = s_rq[nbase + t];
+          const double c = s_rc[nbase + t], sn = s_rs[nbase + t];
+          const double yp = y[pp], yq = y[qq];
+          y[pp] = c * yp - sn * yq;
+          y[qq] = sn * yp + c * yq;
         }
-        const double inv = 1.0 / sqrt(nrm);
-        for (int j = 0; j < K; ++j) y[s_nd[base + j]] *= inv;
-      }
-      for (int t = s_m[b] - 1; t >= 0; --t) {
-        const int pp = s_rp[base + t], qq = s_rq[base + t];
-        const double c = s_rc[base + t], sn = s_rs[base + t];
-        const double yp = y[pp], yq = y[qq];
-        y[pp] = c * yp - sn * yq;
-        y[qq] = sn * yp + c * yq;
-      }
-      const int col = s_col[base + p];
-      for (int q = 0; q < s; ++q) sM[base + s_perm[base + q]][base + col] = y[q];
+      wave_lds_fence();
+      if (on && ln < s) sM[nbase + s_perm[nbase + ln]][nbase + s_col[nbase + p]] = y[ln];
     }
     __syncthreads();
     // ---- Zn = blockdiag(children) M on each node block
