@@ -295,10 +295,12 @@ tdvp_status kernel_call(tdvp_ctx ctx, int prec, int ml, int wl, int wr, int mr, 
     char* w1;
     if (workspace) w1 = static_cast<char*>(workspace);
     else w1 = static_cast<char*>(ws.ensure(2 * half + split));
-    // the tables go through a pinned buffer, so the call need not wait for the
-    // stream (a pageable copy and a wait took 27 of 57 us at chi = 32)
+    // the tables go with the launch or, large ones, through a pinned buffer, so
+    // the call need not wait for the stream (a pageable copy and a wait took 27
+    // of 57 us at chi = 32, a copy without the wait 7 of 21.5)
     SiteTables tb{};
-    if (W_host) tb = upload_call_tables(ctx, host_W(W_host, wl, wr), wl, wr, mode);
+    kern::WInline small;
+    if (W_host) tb = upload_call_tables(ctx, host_W(W_host, wl, wr), wl, wr, mode, &small);
     kern::FloatModeScope fmode(kern::float_mode_of(prec));
     f(tb, w1, w1 + half, SplitWS{w1 + 2 * half, split});
     if (!workspace) ctx->sync();  // keep the workspace alive until the kernels finish

@@ -347,11 +347,19 @@ void gemm_nn_ws(hipStream_t s, int M, int N, int K, zc alpha, const void* A, lon
 // Sparse MPO contraction over two channel indices (MPO index, physical index):
 // out[p, q, o1, o2] = sum_e val[e] * in[p, q, i1(e), i2(e)] for the CSR rows
 // o = o1*2 + o2; all eight strides in elements of the precision.
+// A table small enough for a kernel's arguments (4 KiB with the others)
+struct alignas(16) WInline {
+  static constexpr int MAX_OUT = 64, MAX_NNZ = 160;
+  double val[2 * MAX_NNZ];
+  int rowptr[MAX_OUT + 1];
+  int col[MAX_NNZ];
+};
 struct WTable {
   const int* rowptr;      // device, n_out_ch + 1
   const int* col;         // device, in-channel index i1*2 + i2
   const double* val;      // device, complex128 coefficients
   int n_in_ch, n_out_ch;
+  const WInline* inl;     // host, or null: goes with the launch instead of the three above
 };
 // Charges of the sparse-MPO stage of a charged contraction (device arrays):
 // element (p, q) of the stage pairs bra row p (charge ql[p]) with ket column

@@ -376,8 +376,12 @@ TableOffsets add_table(TableBlob& blob, const std::vector<zc>& W, int wl, int wr
   build_site_csr(W, wl, wr, mode, rp, col, val);
   TableOffsets o;
   o.rp = blob.add(rp.data(), rp.size() * sizeof(int));
-  o.col = blob.add(col.data(), std::max<size_t>(1, col.size()) * sizeof(int));
-  o.val = blob.add(val.data(), std::max<size_t>(1, val.size()) * sizeof(zc));
+  if (col.empty()) {   // an empty tensor still has addresses
+    col.push_back(0);
+    val.push_back(zc(0.0, 0.0));
+  }
+  o.col = blob.add(col.data(), col.size() * sizeof(int));
+  o.val = blob.add(val.data(), val.size() * sizeof(zc));
   o.n_in = (mode == 0 ? wl : wr) * 2;
   o.n_out = (mode == 0 ? wr : wl) * 2;
   return o;
@@ -390,9 +394,22 @@ kern::WTable resolve(const char* base, const TableOffsets& o) {
 
 }  // namespace
 
-SiteTables upload_call_tables(tdvp_ctx_s* ctx, const std::vector<zc>& W, int wl, int wr, int mode) {
+SiteTables upload_call_tables(tdvp_ctx_s* ctx, const std::vector<zc>& W, int wl, int wr, int mode,
+                              kern::WInline* small) {
   TableBlob blob;
   const TableOffsets o = add_table(blob, W, wl, wr, mode);
+  SiteTables t{};
+  t.nnz = site_nnz(W);
+  kern::WTable& w = mode == 0 ? t.F : t.B;
+  w = resolve(blob.bytes.data(), o);
+  const int nnz = w.rowptr[w.n_out_ch];
+  if (w.n_out_ch <= kern::WInline::MAX_OUT && nnz <= kern::WInline::MAX_NNZ) {
+    std::copy_n(w.rowptr, w.n_out_ch + 1, small->rowptr);
+    std::copy_n(w.col, nnz, small->col);
+    std::copy_n(w.val, 2 * (size_t)nnz, small->val);
+    w = kern::WTable{nullptr, nullptr, nullptr, w.n_in_ch, w.n_out_ch, small};
+    return t;
+  }
   if (ctx->call_tables_cap < blob.bytes.size()) {
     ctx->dfree(ctx->call_tables);
     ctx->call_tables = nullptr;
@@ -402,10 +419,7 @@ SiteTables upload_call_tables(tdvp_ctx_s* ctx, const std::vector<zc>& W, int wl,
     ctx->call_tables_cap = cap;
   }
   ctx->upload_async(ctx->call_tables, blob.bytes.data(), blob.bytes.size());
-  const char* base = static_cast<const char*>(ctx->call_tables);
-  SiteTables t{};
-  (mode == 0 ? t.F : t.B) = resolve(base, o);
-  t.nnz = site_nnz(W);
+  w = resolve(static_cast<const char*>(ctx->call_tables), o);
   return t;
 }
 

@@ -284,7 +284,8 @@ void env_right(tdvp_ctx_s* ctx, const SiteTables& tb, int ml, int wl, int wr, in
 // One CSR table (mode 0: F, 1: B) of a single host W for a kernel-level call, in
 // the context's buffer for them: valid until the next such call's, in stream
 // order; does not wait for the stream
-SiteTables upload_call_tables(tdvp_ctx_s* ctx, const std::vector<zc>& W, int wl, int wr, int mode);
+SiteTables upload_call_tables(tdvp_ctx_s* ctx, const std::vector<zc>& W, int wl, int wr, int mode,
+                              kern::WInline* small);
 // All three tables of a single host W written into caller-provided device memory (cap bytes at
 // dst, allocates nothing on the device): returns the bytes they take; when
 // that exceeds cap nothing is written and *out is left as it was.

@@ -1502,12 +1502,18 @@ constexpr int WNT = 256;
 constexpr int WMAX_CH = 256;   // channels (MPO index x physical index) of a charged stage
 
 
-template <typename T, int V, bool CHARGED>
+// the MPO tensor in device memory; kern::WInline: in the kernel's arguments
+struct WPointers {
+  const int* __restrict__ rowptr;
+  const int* __restrict__ col;
+  const double* __restrict__ val;
+};
+
+template <typename T, int V, bool CHARGED, class TAB>
 __global__ __launch_bounds__(WNT) void wapply_kernel(const T* __restrict__ in, T* __restrict__ out, long long nQ,
                                                       long long isP, long long is1, long long is2, long long osP,
-                                                      long long os1, long long os2, const int* __restrict__ rowptr,
-                                                      const int* __restrict__ col, const double2* __restrict__ val,
-                                                      int n_out, kern::WCharges wc) {
+                                                      long long os1, long long os2, const TAB tab, int n_out,
+                                                      kern::WCharges wc) {
   using c2 = typename VT<T>::c2;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const long long p = blockIdx.y;
@@ -1537,10 +1543,10 @@ __global__ __launch_bounds__(WNT) void wapply_kernel(const T* __restrict__ in, T
 #pragma unroll
     for (int v = 0; v < V; ++v) sr[v] = si[v] = T(0);
     if (any) {
-      const int e1 = rowptr[o + 1];
-      for (int e = rowptr[o]; e < e1; ++e) {
-        const double2 w = val[e];
-        const int c = col[e];
+      const int e1 = tab.rowptr[o + 1];
+      for (int e = tab.rowptr[o]; e < e1; ++e) {
+        const double2 w = make_double2(tab.val[2 * e], tab.val[2 * e + 1]);
+        const int c = tab.col[e];
         const c2* x = inb + (c >> 1) * is1 + (c & 1) * is2;
         c2 xv[V];
         if constexpr (V == 2) {
@@ -2099,13 +2105,16 @@ void wapply(hipStream_t s, const WTable& t, const void* in, void* out, long long
   const long long gz = std::max<long long>(
       1, std::min<long long>((2048 + gx * nP - 1) / (gx * nP), (t.n_out_ch + WAVES - 1) / WAVES));
   const dim3 grid((unsigned)gx, (unsigned)nP, (unsigned)gz);
-  auto go = [&](auto charged) {
-    hipLaunchKernelGGL((wapply_kernel<T, V, decltype(charged)::value>), grid, dim3(WNT), 0, s,
-                       static_cast<const T*>(in), static_cast<T*>(out), nQ, isP, is1, is2, osP, os1, os2, t.rowptr,
-                       t.col, reinterpret_cast<const double2*>(t.val), t.n_out_ch, w);
+  auto go = [&](auto charged, const auto& tab) {
+    hipLaunchKernelGGL((wapply_kernel<T, V, decltype(charged)::value, std::decay_t<decltype(tab)>>), grid, dim3(WNT), 0,
+                       s, static_cast<const T*>(in), static_cast<T*>(out), nQ, isP, is1, is2, osP, os1, os2, tab,
+                       t.n_out_ch, w);
   };
-  if (wc) go(std::true_type{});
-  else go(std::false_type{});
+  const WPointers dev{t.rowptr, t.col, t.val};
+  if (t.inl && wc) go(std::true_type{}, *t.inl);
+  else if (t.inl) go(std::false_type{}, *t.inl);
+  else if (wc) go(std::true_type{}, dev);
+  else go(std::false_type{}, dev);
   HIP_CHECK(hipGetLastError());
 }
 template void wapply<double>(hipStream_t, const WTable&, const void*, void*, long long, long long, long long,
