@@ -32,12 +32,13 @@ if ROOT not in sys.path:
 
 METRIC = "TDVP sweep time/step & H_eff matvec TFLOP/s, mixed vs FP64, at fixed fidelity"
 # dense matrix-core peaks of the arithmetic each precision runs on
-PEAK_TFLOPS = {"fp64": 78.6, "fp32": 157.3, "bf16": 2500.0, "bf16x3": 2500.0}
+PEAK_TFLOPS = {"fp64": 78.6, "fp32": 2500.0, "bf16": 2500.0, "bf16x3": 2500.0}
 DTYPE = {"fp64": "f64", "fp32": "f32", "bf16": "bf16", "bf16x3": "bf16x3"}
 # matrix-core flops issued per algorithmic flop (8 per complex multiply-add):
-# the FP64 and FP32 GEMMs form a complex product from three real products
-# (6 flops), the BF16 kernel from four, the BF16X3 split from twelve
-MFMA_PER_FLOP = {"fp64": 0.75, "fp32": 0.75, "bf16": 1, "bf16x3": 3}
+# the FP64 GEMM forms a complex product from three real products (6 flops);
+# complex64 runs on the BF16 matrix cores, four real products of one (BF16),
+# three (BF16X3) or six (FP32, three BF16 terms a number) BF16 products each
+MFMA_PER_FLOP = {"fp64": 0.75, "fp32": 6, "bf16": 1, "bf16x3": 3}
 
 
 COPY_PROBE_BYTES = 64 * 1024 * 1024
@@ -792,7 +793,7 @@ def main():
                    "mpo_w_max": int(max(main_run["H"].dims)), "parallelism": "single GPU"},
     }
     out.update({k: v for k, v in res.items() if k not in ("value", "ms_per_step")})
-    out["roofline"] = {"bound": "mfma", "kernel": "one-site H_eff GEMM (gemm_kernel TAG=1)",
+    out["roofline"] = {"bound": "mfma", "kernel": "one-site H_eff GEMM (TAG=1)",
                        "achieved": gemm_tf, "peak": peak, "unit": "TFLOP/s",
                        "frac": (gemm_tf / peak) if gemm_tf else None, "traffic": traffic}
     if args.compare_prec:

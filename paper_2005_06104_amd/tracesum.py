@@ -229,7 +229,7 @@ def main(argv=None):
     ap.add_argument("--top", type=int, default=40)
     ap.add_argument("--ranges", default=None, help="a marker_api_trace.csv of the same run: host time per range")
     ap.add_argument("--counters", action="store_true", help="the file is a rocprofv3 --pmc counter file")
-    ap.add_argument("--kernel", default="gemm_kernel<float, false, false, false, false, 1>")
+    ap.add_argument("--kernel", default=", false, false, 1>")
     ap.add_argument("--calib", default=None, help="name of a plain copy kernel in the same file")
     ap.add_argument("--calib-bytes", type=float, default=None, help="bytes the copy reads (and writes)")
     a = ap.parse_args(argv)
