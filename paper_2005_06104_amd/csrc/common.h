@@ -387,9 +387,6 @@ void wapply(hipStream_t s, const WTable& t, const void* in, void* out, long long
 void zdots(hipStream_t s, const void* V, long long ldv, int nv, const void* w, long long n,
            void* partial, int n_partial_blocks, void* out, bool conjugate = true);
 int zdots_blocks(long long n);
-// w[x] += sign * sum_j c[j] V[j*ldv + x]   (c complex128 on device)
-void zcombine(hipStream_t s, void* w, const void* V, long long ldv, int nv, const void* c,
-              double sign, long long n);
 // out[j] = sum_b partial[b * nv + j] for j < nv (complex128; fixed order)
 void zsum_partials(hipStream_t s, const void* partial, int nb, int nv, void* out);
 // number of blocks (and of partial sums of |w|^2) of zcombine_p over n entries
@@ -403,6 +400,8 @@ void zdots_partial(hipStream_t s, const void* V, long long ldv, int nv, const vo
 // sums of |w|^2 (zcombine_norm_blocks(n) entries, for zscale_invnorm)
 void zcombine_p(hipStream_t s, void* w, const void* V, long long ldv, int nv, const void* partial, int nb,
                 double sign, long long n, void* cout, void* npart);
+// dst[x] = sum_j c[j] V[j*ldv + x], nv <= 64, c in host memory (copied by the call)
+void zcombine_host(hipStream_t s, void* dst, const void* V, long long ldv, int nv, const zc* c, long long n);
 // dst = a * src (complex scalar a)
 void zscale(hipStream_t s, void* dst, const void* src, zc a, long long n);
 // precision conversions (complex)

@@ -77,8 +77,8 @@ struct Lanczos {
     double2* dpart2 = npart + nnp;   // second-pass partial dot products, nnp x (j + 1)
     scal.ensure(320 * ZB);
     double2* S = scal.as<double2>();
-    // S: [0, 64) and [64, 128) the two projection passes, 128 |w|^2, 192.. the
-    // result coefficients, 256 the summed partial norms of long vectors
+    // S: [0, 64) and [64, 128) the two projection passes, 128 |w|^2, 256 the
+    // summed partial norms of long vectors
     constexpr int FOLD = 64;
     char* Vb = static_cast<char*>(V.ensure((size_t)(maxit + 1) * n * ZB));
     auto vec = [&](int j) { return static_cast<void*>(Vb + (size_t)j * n * ZB); };
@@ -202,10 +202,7 @@ struct Lanczos {
     }
     std::vector<zc> cs(dim);
     for (int r = 0; r < dim; ++r) cs[r] = f * c[r];
-    upload(ctx, S + 192, cs.data(), (size_t)dim * ZB);
-    kern::zfill(ctx->stream, x, zc(0.0, 0.0), n, ZB);
-    kern::zcombine(ctx->stream, x, Vb, n, dim, S + 192, 1.0, n);
-    HIP_CHECK(hipStreamSynchronize(ctx->stream));  // `cs` is pageable host memory
+    kern::zcombine_host(ctx->stream, x, Vb, n, dim, cs.data(), n);
     if (timer) timer->collect_all();                // the discarded iteration ran too
     return napp;
   }

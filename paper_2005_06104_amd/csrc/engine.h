@@ -83,9 +83,10 @@ struct MatvecTimer {
     HIP_CHECK(hipEventRecord(ev[cur][k], ctx->stream));
     if (k == 3) pending[cur] = true;
   }
-  // accumulate set `k` (its events must have completed)
+  // accumulate set `k`, once its events have completed
   void collect(int k) {
     if (!pending[k]) return;
+    HIP_CHECK(hipEventSynchronize(ev[k][3]));
     float t = 0.f, g1 = 0.f, g2 = 0.f;
     HIP_CHECK(hipEventElapsedTime(&t, ev[k][0], ev[k][3]));
     HIP_CHECK(hipEventElapsedTime(&g1, ev[k][0], ev[k][1]));
