@@ -209,8 +209,12 @@ __device__ inline int plane_at(int row, int ch) { return row * BKS + ((ch ^ (-(r
 
 // Chunk loads: the buffer's base is the tile's first row at k0, so a chunk
 // costs one address register.  WIDE: leading dimensions whose tile reaches
-// past the buffer's 2^31 bytes, plain addresses.
+// outside the buffer's 2^31 bytes, past its end or (negative ones) before its
+// base, plain addresses.
 constexpr long long LD_WIDE = 1LL << 20;   // 128 rows of 2^20 complex64: 2^30 bytes
+inline bool wide_ld(long long lda, long long ldb, long long limit) {
+  return lda < 0 || ldb < 0 || lda >= limit || ldb >= limit;
+}
 
 template <bool KC, int ROWS, int NTH>
 __device__ inline void chunk_offsets(long long ld, int r0, int R, int tid, unsigned (&off)[ROWS * 4 / NTH], int lo,
@@ -1092,7 +1096,7 @@ template <int TERMS, bool TA, bool TB, int TAG>
 void launch_split(const Product<float>& p, int conj, int tile, int n_items, float* C, long long ldc, long long sc,
                   bool plain, int S, int Kc, long long sps, const int4* kit, const int2* kiv) {
   using TS = SplitTiles<TERMS>;
-  const bool wide = p.lda >= LD_WIDE || p.ldb >= LD_WIDE;
+  const bool wide = wide_ld(p.lda, p.ldb, LD_WIDE);
   const int tm = wide ? 64 : TS::cost[tile].tm, tn = wide ? 64 : TS::cost[tile].tn;
   const dim3 grid = kit ? dim3(n_items)
                         : dim3((p.N + tn - 1) / tn, (p.M + tm - 1) / tm, S > 1 ? S : p.batch);
@@ -1372,7 +1376,7 @@ void launch_direct(const Product<double>& p, int conj, int tile, int n_items, do
   auto go = [&](auto tl) {
     launch_direct_tile<decltype(tl), TA, TB, TAG>(p, n_items, C, ldc, sc, plain, S, parts, Kc, sps, kit, kiv, conj);
   };
-  if (p.lda >= LD_WIDE64 || p.ldb >= LD_WIDE64) return go(DirectWide{});
+  if (wide_ld(p.lda, p.ldb, LD_WIDE64)) return go(DirectWide{});
   if (kit) return go(DirectMapped{});
   switch (tile) {
     case 0: return go(Direct0{});
@@ -1427,7 +1431,7 @@ void launch_gemm_mode(const Product<T>& p) {
   if constexpr (TERMS == 0) {
     S = choose_splits(M, N, K, batch, p.ws_bytes);
     choose_direct_tile<TA, TB>(M, N, K, batch, S, &tile, &in_block);
-    if (p.lda >= LD_WIDE64 || p.ldb >= LD_WIDE64) in_block = false;
+    if (wide_ld(p.lda, p.ldb, LD_WIDE64)) in_block = false;
   } else {
     const double us = choose_split_tile<TERMS>(M, N, K, batch, p.ws_bytes, &tile, &S);
     // on term images where those take less time: large products, and long ones
