@@ -324,7 +324,11 @@ tdvp_status tdvp_squeezing_xi2(int n_spins, double sx, double sy, double sz, dou
 
 /* ---------------------------------------------------- kernel-level calls
  * Device pointers, complex in the precision `prec` (complex128 or complex64),
- * issued on the context's stream, asynchronous. */
+ * issued on the context's stream, asynchronous: a call that is given a
+ * workspace returns before its kernels have run (W_host is copied by then), so
+ * work on another stream waits for an event or tdvp_synchronize.  Under stream
+ * capture such a call is recorded if W has at most 160 nonzero entries, which
+ * travel with the launch; one with more is refused (TDVP_ERR_DEVICE). */
 
 /* Batched complex GEMM C = alpha op(A) op(B) + beta C (row-major), batch
  * strides in elements; op(A) is M x K, op(B) is K x N. */

@@ -407,6 +407,12 @@ SiteTables upload_call_tables(tdvp_ctx_s* ctx, const std::vector<zc>& W, int wl,
     w = kern::WTable{nullptr, nullptr, nullptr, w.n_in_ch, w.n_out_ch, small};
     return t;
   }
+  // A captured copy would be replayed from the pinned buffer and into the tables
+  // of whichever call used them last.
+  hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
+  HIP_CHECK(hipStreamIsCapturing(ctx->stream, &capturing));
+  if (capturing != hipStreamCaptureStatusNone)
+    TDVP_THROW(TDVP_ERR_DEVICE, "an MPO tensor of more than 160 nonzeros cannot be used under stream capture");
   if (ctx->call_tables_cap < blob.bytes.size()) {
     ctx->dfree(ctx->call_tables);
     ctx->call_tables = nullptr;
