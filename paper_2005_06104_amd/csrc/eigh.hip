@@ -31,6 +31,7 @@
 #include <type_traits>
 
 #include "common.h"
+#include "exchange.h"
 #include "wave.h"
 
 namespace {
@@ -140,9 +141,8 @@ __device__ inline double2 hh_v(int c, int k, double2 row_c, double2 sc) {
 // x = tau A v; the owner of row k+1 also publishes that row, from which every
 // workgroup forms the next pivot row by the rank-2 update (and, in the same
 // pass, the norm that the next reflector needs).  Published buffers alternate
-// between two copies, tagged k + 1: a workgroup publishes column k + 1 only
-// after it has read everything of column k, so no copy is overwritten while
-// a reader still needs it.
+// between two copies, tagged k + 1; exchange.h says why none is overwritten
+// while a reader still needs it.
 template <int NMAX, int LDS, bool QLDS>
 __global__ __launch_bounds__(TNT) void tridiag_kernel(TdBatch batch) {
   __shared__ double sred[TNT / 64];     // per-wave |row[k+2:]|^2 of the pivot row
@@ -245,7 +245,8 @@ __global__ __launch_bounds__(TNT) void tridiag_kernel(TdBatch batch) {
       sq.y = wave::group_sum(sq.y, T);
       tqs = cmul(tau, sq);
       const int r = g + rj * G;
-      if (rt == 0 && r >= k + 1) put_tagged(xvp + 4 * (size_t)r, cmul(tau, sa), tag);
+      if (rt == 0 && tdx::publishes(r, k, n, G))
+        put_tagged(xvp + 4 * (size_t)r, r >= k + 1 ? cmul(tau, sa) : double2{0.0, 0.0}, tag);
     }
     if ((k + 1) % G == g) {
       const int j = (k + 1) / G;
@@ -263,7 +264,7 @@ __global__ __launch_bounds__(TNT) void tridiag_kernel(TdBatch batch) {
       }
     }
     // ---- gather this column's x and pivot row as they arrive (every thread
-    // its own entries)
+    // its own entries), and one entry of every workgroup without rows left
     constexpr int NQ = (NMAX + TNT - 1) / TNT;
     double2 xq[NQ], rq[NQ];
     {
@@ -274,9 +275,14 @@ __global__ __launch_bounds__(TNT) void tridiag_kernel(TdBatch batch) {
         gx[q] = gr[q] = c >= n;
         xq[q] = rq[q] = double2{0.0, 0.0};
       }
+      static_assert(TD_G_BIG <= TNT, "an idle workgroup's entry a thread");
+      const int idle = tdx::first_awaited(k, n, G) + tid;
+      bool gi = idle >= k + 1;
       unsigned polls = 0;
       while (true) {
-        bool done = true;
+        double2 zero;
+        if (!gi) gi = get_tagged(xvp + 4 * (size_t)idle, tag, &zero);
+        bool done = gi;
 #pragma unroll
         for (int q = 0; q < NQ; ++q) {
           const int c = k + 1 + tid + q * TNT;
@@ -526,7 +532,7 @@ __global__ __launch_bounds__(TNT, 1) void tridiag_row_kernel(TdBatch batch) {
       s.y = sum64(s.y);
       const unsigned tag = (unsigned)k + 1u;
       unsigned long long* xvp = a.xv + (size_t)(k & 1) * 4 * n;
-      if (own && lane == 0 && (r >= k + 1 || r >= n - G))
+      if (own && lane == 0 && tdx::publishes(r, k, n, G))
         put_packed(xvp + r, r >= k + 1 ? cmul(tau, s) : double2{0.0, 0.0}, tag, n);
 
       // ---- while the others' x arrives: row k + 1, published during column k - 1
@@ -567,9 +573,7 @@ __global__ __launch_bounds__(TNT, 1) void tridiag_row_kernel(TdBatch batch) {
         if (!words.await(tag, a.err)) s_fail = 1;
         words.store(sr, k + 1 + tid, n);
       }
-      // x from row k + 1 on, and at least one entry of every workgroup: none gets
-      // so far ahead of another that it overwrites what that one has yet to read
-      const int xc = min(k + 1, n - G) + tid;
+      const int xc = tdx::first_awaited(k, n, G) + tid;   // x from row k + 1 on, an entry of every workgroup
       __syncthreads();
       // a first look at x any earlier mostly finds it incomplete, and the second
       // comes a round trip later (before the barrier: 1490 us at n = 512; after the
