@@ -492,6 +492,20 @@ bool eigh_rows_desc_tridiag(tdvp_ctx_s* ctx, const void* H, int n, std::vector<d
   return true;
 }
 
+// throws when the n x n matrix holds a number that is not finite; *zero (may be
+// null): whether all are zero
+void require_finite(tdvp_ctx_s* ctx, const void* H, int n, bool* zero) {
+  std::vector<double> h(2 * (size_t)n * n);
+  HIP_CHECK(hipMemcpyAsync(h.data(), H, sizeof(double) * h.size(), hipMemcpyDeviceToHost, ctx->stream));
+  HIP_CHECK(hipStreamSynchronize(ctx->stream));
+  bool z = true;
+  for (double v : h) {
+    if (!std::isfinite(v)) TDVP_THROW(TDVP_ERR_NUMERIC, "eigh: non-finite input matrix (n = " + std::to_string(n) + ")");
+    z = z && v == 0.0;
+  }
+  if (zero) *zero = z;
+}
+
 void eigh_rows_desc_heevd(tdvp_ctx_s* ctx, const void* H, int n, std::vector<double>& lam, void* rows, DBuf& work) {
   const size_t nn = (size_t)n * n;
   const int nb = kern::zdots_blocks((long long)nn);
@@ -523,14 +537,8 @@ void eigh_rows_desc_heevd(tdvp_ctx_s* ctx, const void* H, int n, std::vector<dou
   if (!ok) {
     // divide and conquer failed (no convergence, or a non-finite result):
     // check the input, then use the Jacobi eigensolver on a fresh copy
-    std::vector<double> h(2 * nn);
-    HIP_CHECK(hipMemcpyAsync(h.data(), H, sizeof(rz) * nn, hipMemcpyDeviceToHost, ctx->stream));
-    HIP_CHECK(hipStreamSynchronize(ctx->stream));
     bool zero = true;
-    for (double v : h) {
-      if (!std::isfinite(v)) TDVP_THROW(TDVP_ERR_NUMERIC, "eigh: non-finite input matrix (n = " + std::to_string(n) + ")");
-      zero = zero && v == 0.0;
-    }
+    require_finite(ctx, H, n, &zero);
     if (zero) {   // the library routes do not converge on the zero matrix: V = I, all eigenvalues 0
       kern::zfill(ctx->stream, rows, zc(0.0, 0.0), (long long)nn, 16);
       kern::zshift_diag(ctx->stream, rows, n, 1.0, 1.0);
@@ -561,6 +569,8 @@ void eigh_rows_desc(tdvp_ctx_s* ctx, const void* H, int n, std::vector<double>& 
   if (try_tridiag && eigh_rows_desc_tridiag(ctx, H, n, lam, rows, work, method == EIGH_TRIDIAG_LIB)) return;
   if (method == EIGH_TRIDIAG || method == EIGH_TRIDIAG_LIB)
     TDVP_THROW(TDVP_ERR_NUMERIC, "cooperative tridiagonal eigensolver not applicable");
+  // the reduction failed: the library's solvers are not given a matrix that is not finite
+  if (try_tridiag && n >= 2 && kern::tridiag_groups(n) > 0) require_finite(ctx, H, n, nullptr);
   eigh_rows_desc_heevd(ctx, H, n, lam, rows, work);
 }
 

@@ -141,34 +141,49 @@ __global__ __launch_bounds__(1024) void dc_init_kernel(const DcInitBatch bt) {
   double* __restrict__ Z = ar.Z;
   double* __restrict__ scale_out = ar.scale;
   __shared__ double red[2][16];
+  __shared__ int all_finite[16];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   double md = 0.0, me = 0.0;
-  for (int i = tid; i < n; i += blockDim.x) md = fmax(md, fabs(D[i]));
-  for (int i = tid; i < n - 1; i += blockDim.x) me = fmax(me, fabs(E[i]));
+  bool finite = true;
+  for (int i = tid; i < n; i += blockDim.x) {
+    md = fmax(md, fabs(D[i]));
+    finite = finite && isfinite(D[i]);
+  }
+  for (int i = tid; i < n - 1; i += blockDim.x) {
+    me = fmax(me, fabs(E[i]));
+    finite = finite && isfinite(E[i]);
+  }
   md = wave_max(md);
   me = wave_max(me);
+  finite = __all(finite);
   if (lane == 0) {
     red[0][wave] = md;
     red[1][wave] = me;
+    all_finite[wave] = finite;
   }
   __syncthreads();
+  bool ok = true;
   md = me = 0.0;
   for (int w = 0; w < (int)(blockDim.x >> 6); ++w) {
+    ok = ok && all_finite[w] != 0;
     md = fmax(md, red[0][w]);
     me = fmax(me, red[1][w]);
   }
   double scale = fmax(md, me);
-  if (!(scale > 0.0)) scale = 1.0;   // zero matrix (or NaN: caught by the caller's checks)
+  if (!(scale > 0.0)) scale = 1.0;   // zero matrix
+  scale = fmax(scale, 0x1p-1022);    // its inverse is finite
   const double inv = 1.0 / scale;
   const double bound = md * inv + 2.0 * me * inv;
   if (blockIdx.x == 0) {
-    if (tid == 0) *scale_out = scale;
+    // no order among eigenvalues that are not finite: those of a diagonal matrix
+    // instead, and NaN from the scale
+    if (tid == 0) *scale_out = ok ? scale : __longlong_as_double(0x7ff8000000000000ll);
     for (int i = tid; i < P; i += blockDim.x) {
-      const double e = i < n - 1 ? E[i] * inv : 0.0;
-      const double em = (i >= 1 && i - 1 < n - 1) ? E[i - 1] * inv : 0.0;
+      const double e = ok && i < n - 1 ? E[i] * inv : 0.0;
+      const double em = (ok && i >= 1 && i - 1 < n - 1) ? E[i - 1] * inv : 0.0;
       Ep[i] = e;
       // every m in [1, P) is a cut of exactly one level: subtract both couplings
-      d[i] = i < n ? D[i] * inv - e - em : 2.0 * bound + 1.0;
+      d[i] = !ok ? (double)i : i < n ? D[i] * inv - e - em : 2.0 * bound + 1.0;
     }
   }
   for (long long k = (long long)blockIdx.x * blockDim.x + tid; k < (long long)P * P;
@@ -508,7 +523,8 @@ __global__ __launch_bounds__(DC_WNT) void dc_vectors_kernel(const DcBatch bt) {
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   const int col = a.colpos[base + p];
-  for (int q = lane; q < s; q += 64) a.M[(size_t)(base + a.perm[base + q]) * P + base + col] = y[q];
+  // (the mask changes nothing where perm is the permutation it should be)
+  for (int q = lane; q < s; q += 64) a.M[(size_t)(base + (a.perm[base + q] & (s - 1))) * P + base + col] = y[q];
 }
 
 // Zn[node] = blockdiag(Z1, Z2) M[node]: rows of the left child combine the
@@ -864,7 +880,7 @@ __global__ __launch_bounds__(DC_LNT) void dc_leaf_kernel(const DcLeafBatch bt) {
           y[qq] = sn * yp + c * yq;
         }
       wave_lds_fence();
-      if (on && ln < s) sM[nbase + s_perm[nbase + ln]][nbase + s_col[nbase + p]] = y[ln];
+      if (on && ln < s) sM[nbase + (s_perm[nbase + ln] & (s - 1))][nbase + s_col[nbase + p]] = y[ln];
     }
     __syncthreads();
     // ---- Zn = blockdiag(children) M on each node block
