@@ -65,6 +65,9 @@ typedef enum {
  * exponential, QR/SVD/eigh and the stored site tensors are always FP64.
  *   TDVP_FP32            complex64 operands in full (each real number as three
  *                        BF16 terms, which hold its 24 bits), FP32 accumulation;
+ *                        elements with infinities, NaN or sums of about 2^88 and
+ *                        more are formed a second time on the FP32 matrix cores,
+ *                        a product full of them takes two to three times as long;
  *   TDVP_BF16_FP32ACC    complex64 operands rounded to BF16 (nearest even) as
  *                        they enter the matrix cores, FP32 accumulation;
  *   TDVP_BF16X3_FP32ACC  each FP32 operand split into two BF16 terms

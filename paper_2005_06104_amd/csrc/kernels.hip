@@ -504,6 +504,19 @@ __global__ __launch_bounds__(TL::NTH, TL::OCC) void gemm_split_kernel(
   }
 
   const bool has_beta = (br != 0.f) || (bi != 0.f);
+  auto put = [&](int gm, int gn, float xr, float xi) {
+    float2 o;
+    o.x = ar * xr - ai * xi;
+    o.y = ar * xi + ai * xr;
+    if (has_beta) {
+      const float2 old = Cb[(long long)gm * ldc + gn];
+      o.x += br * old.x - bi * old.y;
+      o.y += br * old.y + bi * old.x;
+    }
+    Cb[(long long)gm * ldc + gn] = o;
+  };
+  static_assert(TERMS < 3 || SI * SJ * 4 <= 32, "a bit per element of a lane");
+  unsigned again = 0;   // TERMS 3: the elements to be formed again, bit (i SJ + j) 4 + r
 #pragma unroll
   for (int i = 0; i < SI; ++i)
 #pragma unroll
@@ -516,40 +529,71 @@ __global__ __launch_bounds__(TL::NTH, TL::OCC) void gemm_split_kernel(
         const int gn = n0 + ln;
         if (gm < M && gn < N && lm >= job.r0 && lm < job.r1 && ln >= job.c0 && ln < job.c1) {
           const float down = TERMS == 3 ? 1.f / (UP3 * UP3) : 1.f;
-          float xr = down * cr[i][j][r], xi = down * ci[i][j][r];
-          if constexpr (TERMS == 3) {
-            // An infinity, or a number or sum that the scale takes to one, has
-            // no such terms (h - x is not finite): the element is formed again
-            // from the operands themselves, in the 3M form of the FP64 kernel.
-            if (!(__builtin_isfinite(xr) && __builtin_isfinite(xi))) {
-              float p1 = 0.f, p2 = 0.f, p3 = 0.f;
-              for (int v = 0; v < kr_.n; ++v) {
-                const int2 I = kr_.at(v);
-                for (int k = I.x; k < I.y; ++k) {
-                  const float2 a = TA ? Ab[(long long)k * lda + gm] : Ab[(long long)gm * lda + k];
-                  const float2 b = TB ? Bb[(long long)gn * ldb + k] : Bb[(long long)k * ldb + gn];
-                  const float ay = (conj & 1) ? -a.y : a.y, by = (conj & 2) ? -b.y : b.y;
-                  p1 = fmaf(a.x, b.x, p1);
-                  p2 = fmaf(ay, by, p2);
-                  p3 = fmaf(a.x + ay, b.x + by, p3);
-                }
-              }
-              xr = p1 - p2;
-              xi = p3 - p1 - p2;
-            }
-          }
-          float2 o;
-          o.x = ar * xr - ai * xi;
-          o.y = ar * xi + ai * xr;
-          if (has_beta) {
-            const float2 old = Cb[(long long)gm * ldc + gn];
-            o.x += br * old.x - bi * old.y;
-            o.y += br * old.y + bi * old.x;
-          }
-          Cb[(long long)gm * ldc + gn] = o;
+          const float xr = down * cr[i][j][r], xi = down * ci[i][j][r];
+          if (TERMS == 3 && !(__builtin_isfinite(xr) && __builtin_isfinite(xi))) again |= 1u << ((i * SJ + j) * 4 + r);
+          else put(gm, gn, xr, xi);
         }
       }
     }
+  if constexpr (TERMS == 3) {
+    // An infinity, or a number or sum that the scale takes to one, has no such
+    // terms (h - x is not finite): these elements are formed again from the
+    // operands themselves, a row of 16 x 16 pieces at a time on the FP32 matrix
+    // cores (v_mfma_f32_16x16x4f32, outputs as above), in the 3M form of the FP64
+    // kernel, U steps of four k in flight.
+    // 2048 x 2048 x 1024: all elements again 550 us, a column of B 230 to 460,
+    // none 174 (a lane per element: 8470; the FP32 matrix cores alone: 278).
+    constexpr int U = 4;
+    const float ca = (conj & 1) ? -1.f : 1.f, cb = (conj & 2) ? -1.f : 1.f;
+    for (int i = 0; i < SI; ++i) {
+      const unsigned mine = again >> (4 * SJ * i) & ((1u << (4 * SJ)) - 1);
+      if (!__any(mine != 0)) continue;
+      const int rt = ro[0] + 16 * i;   // the pieces that a wave has follow one another
+      const int am = rt + lr;
+      const bool aok = m0 + am < M && am >= job.r0 && am < job.r1;
+      const float2* ap = TA ? Ab + (m0 + am) : Ab + (long long)(m0 + am) * lda;
+      f4 p1[SJ], p2[SJ], p3[SJ];
+#pragma unroll
+      for (int j = 0; j < SJ; ++j) p1[j] = p2[j] = p3[j] = f4{0, 0, 0, 0};
+      for (int v = 0; v < kr_.n; ++v) {
+        const int2 I = kr_.at(v);
+        for (int k = I.x; k < I.y; k += 4 * U) {
+          float2 a[U], b[U][SJ];
+#pragma unroll
+          for (int u = 0; u < U; ++u) {
+            const int kk = k + 4 * u + lk;
+            const bool in = kk < I.y;
+            a[u] = float2{0.f, 0.f};
+            if (in && aok) a[u] = TA ? ap[(long long)kk * lda] : ap[kk];
+#pragma unroll
+            for (int j = 0; j < SJ; ++j) {
+              const int bn = co[0] + 16 * j + lr;
+              b[u][j] = float2{0.f, 0.f};
+              if (in && n0 + bn < N && bn >= job.c0 && bn < job.c1)
+                b[u][j] = TB ? Bb[(long long)(n0 + bn) * ldb + kk] : Bb[(long long)kk * ldb + (n0 + bn)];
+            }
+          }
+#pragma unroll
+          for (int u = 0; u < U; ++u) {
+            const float ay = ca * a[u].y, as = a[u].x + ay;
+#pragma unroll
+            for (int j = 0; j < SJ; ++j) {
+              const float by = cb * b[u][j].y;
+              p1[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u].x, b[u][j].x, p1[j], 0, 0, 0);
+              p2[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(ay, by, p2[j], 0, 0, 0);
+              p3[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(as, b[u][j].x + by, p3[j], 0, 0, 0);
+            }
+          }
+        }
+      }
+#pragma unroll
+      for (int j = 0; j < SJ; ++j)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          if (mine >> (4 * j + r) & 1)
+            put(m0 + rt + lk * 4 + r, n0 + co[0] + 16 * j + lr, p1[j][r] - p2[j][r], p3[j][r] - p1[j][r] - p2[j][r]);
+    }
+  }
 }
 
 // ---------------------------------------------------------------- term images
