@@ -359,6 +359,7 @@ struct WTable {
   const int* col;         // device, in-channel index i1*2 + i2
   const double* val;      // device, complex128 coefficients
   int n_in_ch, n_out_ch;
+  int nnz;                // nonzeros: rowptr[n_out_ch]
   const WInline* inl;     // host, or null: goes with the launch instead of the three above
 };
 // Charges of the sparse-MPO stage of a charged contraction (device arrays):

@@ -364,7 +364,7 @@ struct TableBlob {
 
 struct TableOffsets {
   size_t rp, col, val;
-  int n_in, n_out;
+  int n_in, n_out, nnz;
 };
 
 TableOffsets add_table(TableBlob& blob, const std::vector<zc>& W, int wl, int wr, int mode) {
@@ -373,6 +373,7 @@ TableOffsets add_table(TableBlob& blob, const std::vector<zc>& W, int wl, int wr
   build_site_csr(W, wl, wr, mode, rp, col, val);
   TableOffsets o;
   o.rp = blob.add(rp.data(), rp.size() * sizeof(int));
+  o.nnz = (int)col.size();
   if (col.empty()) {   // an empty tensor still has addresses
     col.push_back(0);
     val.push_back(zc(0.0, 0.0));
@@ -386,7 +387,7 @@ TableOffsets add_table(TableBlob& blob, const std::vector<zc>& W, int wl, int wr
 
 kern::WTable resolve(const char* base, const TableOffsets& o) {
   return kern::WTable{reinterpret_cast<const int*>(base + o.rp), reinterpret_cast<const int*>(base + o.col),
-                      reinterpret_cast<const double*>(base + o.val), o.n_in, o.n_out};
+                      reinterpret_cast<const double*>(base + o.val), o.n_in, o.n_out, o.nnz, nullptr};
 }
 
 }  // namespace
@@ -399,12 +400,12 @@ SiteTables upload_call_tables(tdvp_ctx_s* ctx, const std::vector<zc>& W, int wl,
   t.nnz = site_nnz(W);
   kern::WTable& w = mode == 0 ? t.F : t.B;
   w = resolve(blob.bytes.data(), o);
-  const int nnz = w.rowptr[w.n_out_ch];
+  const int nnz = w.nnz;
   if (w.n_out_ch <= kern::WInline::MAX_OUT && nnz <= kern::WInline::MAX_NNZ) {
     std::copy_n(w.rowptr, w.n_out_ch + 1, small->rowptr);
     std::copy_n(w.col, nnz, small->col);
     std::copy_n(w.val, 2 * (size_t)nnz, small->val);
-    w = kern::WTable{nullptr, nullptr, nullptr, w.n_in_ch, w.n_out_ch, small};
+    w = kern::WTable{nullptr, nullptr, nullptr, w.n_in_ch, w.n_out_ch, nnz, small};
     return t;
   }
   // A captured copy would be replayed from the pinned buffer and into the tables

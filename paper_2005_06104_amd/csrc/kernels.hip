@@ -1547,8 +1547,6 @@ void dispatch_b(hipStream_t s, int opb, int M, int N, int K, zc alpha, const voi
 // chi = 1024, w = 20, complex64, dense: 108 us, 6.2 TB/s (through LDS, eight
 // bytes a lane: 184 us).
 constexpr int WNT = 256;
-constexpr int WMAX_CH = 256;   // channels (MPO index x physical index) of a charged stage
-
 
 // the MPO tensor in device memory; kern::WInline: in the kernel's arguments
 struct WPointers {
@@ -1638,6 +1636,53 @@ __global__ __launch_bounds__(WNT) void wapply_kernel(const T* __restrict__ in, T
         r.y = on[v] ? si[v] : T(0);
         y[v] = r;
       }
+  }
+}
+
+// Tensors with many nonzeros on large operands: a wave takes an output channel
+// at a time, and its inputs, 64 columns of a row, pass through LDS (64 KiB for the
+// 64 channels of complex128), since waves that read them in different orders read
+// past the caches: each comes from memory once here.  The sums are the direct
+// kernel's, in its order.  Times of a whole matvec: see wapply_by_lds.
+template <typename T, bool CHARGED, class TAB>
+__global__ __launch_bounds__(WNT) void wapply_lds_kernel(const T* __restrict__ in, T* __restrict__ out, long long nQ,
+                                                          long long isP, long long is1, long long is2, long long osP,
+                                                          long long os1, long long os2, const TAB tab, int n_in,
+                                                          int n_out, kern::WCharges wc) {
+  using c2 = typename VT<T>::c2;
+  extern __shared__ __attribute__((aligned(16))) unsigned char wapply_lds[];
+  c2* x = reinterpret_cast<c2*>(wapply_lds);   // [channel][column]
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const long long p = blockIdx.y, q = (long long)blockIdx.x * 64 + lane;
+  const bool there = q < nQ;
+  const c2* inb = reinterpret_cast<const c2*>(in) + p * isP + q;
+  c2* outb = reinterpret_cast<c2*>(out) + p * osP + q;
+  const int dq = CHARGED && there ? wc.qr[q] - wc.ql[p] : 0;
+  for (int c = wave; c < n_in; c += WNT / 64) {
+    c2 v;
+    v.x = v.y = T(0);
+    if (there && (!CHARGED || wc.din[c] == dq)) v = inb[(c >> 1) * is1 + (c & 1) * is2];
+    x[c * 64 + lane] = v;
+  }
+  __syncthreads();
+  if (!there) return;
+  for (int o = wave; o < n_out; o += WNT / 64) {
+    const bool on = !CHARGED || wc.dout[o] == dq;
+    if (!on && wc.zeros_kept) continue;
+    T sr = T(0), si = T(0);
+    if (on) {
+      const int e1 = tab.rowptr[o + 1];
+      for (int e = tab.rowptr[o]; e < e1; ++e) {
+        const double2 w = make_double2(tab.val[2 * e], tab.val[2 * e + 1]);
+        const c2 v = x[tab.col[e] * 64 + lane];
+        sr += T(w.x) * v.x - T(w.y) * v.y;
+        si += T(w.x) * v.y + T(w.y) * v.x;
+      }
+    }
+    c2 r;
+    r.x = sr;
+    r.y = si;
+    outb[(o >> 1) * os1 + (o & 1) * os2] = r;
   }
 }
 
@@ -2133,6 +2178,16 @@ template void gemm_nn_ws<float>(hipStream_t, int, int, int, zc, const void*, lon
 template void gemm<float>(hipStream_t, int, int, int, int, int, zc, const void*, long long, long long,
                           const void*, long long, long long, zc, void*, long long, long long, int, void*, size_t);
 
+// Whether the stage goes through LDS, from the nonzeros an output channel has on
+// average and the blocks of 64 columns of a row.  Matvecs with 32 x 32 channels,
+// FP64, direct / LDS in us: chi = 512 (4096 blocks) with 4 nonzeros 2022 / 2012, 8
+// 2131 / 2056, 32 2908 / 2517, 48 3229 / 2791, all 64 2786 / 3049 (every wave reads
+// every input, in the same order); chi = 256 (1024 blocks) with 8 310 / 307, 32
+// 433 / 433, 48 485 / 504; chi = 64 with 8 47 / 64, 32 62 / 139.  FP32: 512 with 8
+// 802 / 765, 32 1189 / 1005, 64 1174 / 1284.
+static bool wapply_by_lds(const WTable& t, size_t lds, long long blocks) {
+  return lds <= 64 * 1024 && blocks >= 4096 && t.nnz > 6LL * t.n_out_ch && t.nnz <= 56LL * t.n_out_ch;
+}
 template <typename T>
 void wapply(hipStream_t s, const WTable& t, const void* in, void* out, long long nP, long long nQ,
             long long isP, long long isQ, long long is1, long long is2, long long osP, long long osQ,
@@ -2140,13 +2195,27 @@ void wapply(hipStream_t s, const WTable& t, const void* in, void* out, long long
   if (nP <= 0 || nQ <= 0) return;
   if (nP > 65535) TDVP_THROW(TDVP_ERR_ARG, "wapply: P extent too large");
   if (isQ != 1 || osQ != 1) TDVP_THROW(TDVP_ERR_ARG, "wapply: columns must be contiguous");
-  if ((size_t)t.n_in_ch * 64 * sizeof(typename VT<T>::c2) > 64 * 1024)
-    TDVP_THROW(TDVP_ERR_ARG, "wapply: MPO bond dimension too large");
   WCharges w{nullptr, nullptr, nullptr, nullptr, 0};
   if (wc) {
-    if (t.n_in_ch > WMAX_CH || t.n_out_ch > WMAX_CH) TDVP_THROW(TDVP_ERR_ARG, "wapply: too many charged channels");
     if (!wc->ql || !wc->qr || !wc->din || !wc->dout) TDVP_THROW(TDVP_ERR_ARG, "wapply: incomplete charge table");
     w = *wc;
+  }
+  const WPointers dev{t.rowptr, t.col, t.val};
+  auto route = [&](auto&& go) {
+    if (t.inl && wc) go(std::true_type{}, *t.inl);
+    else if (t.inl) go(std::false_type{}, *t.inl);
+    else if (wc) go(std::true_type{}, dev);
+    else go(std::false_type{}, dev);
+    HIP_CHECK(hipGetLastError());
+  };
+  const size_t lds = (size_t)t.n_in_ch * 64 * sizeof(typename VT<T>::c2);
+  if (wapply_by_lds(t, lds, (nQ + 63) / 64 * nP)) {
+    const dim3 grid((unsigned)((nQ + 63) / 64), (unsigned)nP);
+    return route([&](auto charged, const auto& tab) {
+      hipLaunchKernelGGL((wapply_lds_kernel<T, decltype(charged)::value, std::decay_t<decltype(tab)>>), grid, dim3(WNT),
+                         lds, s, static_cast<const T*>(in), static_cast<T*>(out), nQ, isP, is1, is2, osP, os1, os2, tab,
+                         t.n_in_ch, t.n_out_ch, w);
+    });
   }
   // about 2048 blocks of four waves fill the device; fewer rows and columns:
   // the output channels are dealt over the grid as well
@@ -2155,17 +2224,11 @@ void wapply(hipStream_t s, const WTable& t, const void* in, void* out, long long
   const long long gz = std::max<long long>(
       1, std::min<long long>((2048 + gx * nP - 1) / (gx * nP), (t.n_out_ch + WAVES - 1) / WAVES));
   const dim3 grid((unsigned)gx, (unsigned)nP, (unsigned)gz);
-  auto go = [&](auto charged, const auto& tab) {
+  route([&](auto charged, const auto& tab) {
     hipLaunchKernelGGL((wapply_kernel<T, V, decltype(charged)::value, std::decay_t<decltype(tab)>>), grid, dim3(WNT), 0,
                        s, static_cast<const T*>(in), static_cast<T*>(out), nQ, isP, is1, is2, osP, os1, os2, tab,
                        t.n_out_ch, w);
-  };
-  const WPointers dev{t.rowptr, t.col, t.val};
-  if (t.inl && wc) go(std::true_type{}, *t.inl);
-  else if (t.inl) go(std::false_type{}, *t.inl);
-  else if (wc) go(std::true_type{}, dev);
-  else go(std::false_type{}, dev);
-  HIP_CHECK(hipGetLastError());
+  });
 }
 template void wapply<double>(hipStream_t, const WTable&, const void*, void*, long long, long long, long long,
                              long long, long long, long long, long long, long long, long long, long long,
