@@ -545,6 +545,7 @@ __global__ __launch_bounds__(TL::NTH, TL::OCC) void gemm_split_kernel(
     // none 174 (a lane per element: 8470; the FP32 matrix cores alone: 278).
     constexpr int U = 4;
     const float ca = (conj & 1) ? -1.f : 1.f, cb = (conj & 2) ? -1.f : 1.f;
+#pragma unroll 1
     for (int i = 0; i < SI; ++i) {
       const unsigned mine = again >> (4 * SJ * i) & ((1u << (4 * SJ)) - 1);
       if (!__any(mine != 0)) continue;
