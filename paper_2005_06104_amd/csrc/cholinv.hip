@@ -208,11 +208,11 @@ __device__ inline void diag_columns(double2 (*tS)[CB + 1], DiagShare* sh, double
 // row R of L^-1: x_R (column j < R) = -(sum_{q=j}^{R-1} L[R][q] x_q) / L[R][R]
 template <bool FULL, int R>
 __device__ inline void diag_inverse_rows(const double2 (*tS)[CB + 1], double2 (*tY)[CB + 1], DiagShare* sh,
-                                         double2 (&y)[CB / NPART], int mi, int j, int part) {
+                                         double2 (&y)[CB / NPART], unsigned& polls, int mi, int j, int part) {
   if constexpr (R < CB) {
     if (FULL || R < mi) {
-      while (__hip_atomic_load(&sh->done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) <= R) {
-      }
+      // the factor's wave always gets there, bad pivots or not; bounded all the same
+      while (__hip_atomic_load(&sh->done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) <= R && polls <= CSPIN) ++polls;
       asm volatile("" ::: "memory");
       double2 t{0.0, 0.0};
 #pragma unroll
@@ -234,7 +234,7 @@ __device__ inline void diag_inverse_rows(const double2 (*tS)[CB + 1], double2 (*
         if (R - j - part == NPART * m) y[m] = x;   // L^-1[j + p + NPART m][j]
       if (part == 0) tY[R][j] = x;
     }
-    diag_inverse_rows<FULL, R + 1>(tS, tY, sh, y, mi, j, part);
+    diag_inverse_rows<FULL, R + 1>(tS, tY, sh, y, polls, mi, j, part);
   }
 }
 // entries past the block
@@ -256,16 +256,19 @@ __device__ void diag_factor(double2 (*tS)[CB + 1], int mi, DiagShare* sh, int* s
   }
   if (lane == 0) *s_fail = bad;
 }
-__device__ void diag_invert(const double2 (*tS)[CB + 1], double2 (*tY)[CB + 1], int mi, DiagShare* sh, int lane) {
+// false when the wait for the factor ran out
+__device__ bool diag_invert(const double2 (*tS)[CB + 1], double2 (*tY)[CB + 1], int mi, DiagShare* sh, int lane) {
   double2 y[CB / NPART];
 #pragma unroll
   for (int m = 0; m < CB / NPART; ++m) y[m] = double2{0.0, 0.0};
+  unsigned polls = 0;
   if (mi == CB) {
-    diag_inverse_rows<true, 0>(tS, tY, sh, y, mi, lane % CB, lane / CB);
+    diag_inverse_rows<true, 0>(tS, tY, sh, y, polls, mi, lane % CB, lane / CB);
   } else {
     diag_clear(tY, mi, lane);
-    diag_inverse_rows<false, 0>(tS, tY, sh, y, mi, lane % CB, lane / CB);
+    diag_inverse_rows<false, 0>(tS, tY, sh, y, polls, mi, lane % CB, lane / CB);
   }
+  return polls <= CSPIN;
 }
 
 // workgroup barrier for LDS alone: stores to memory stay in flight
@@ -350,7 +353,10 @@ __device__ void diagonal_chain(const Sec& a, const ChainTiles& t, DiagShare* sh,
     if (wave == 0) {
       diag_factor(t.S, mi, sh, s_fail, lane);
     } else if (wave == 3) {
-      diag_invert(t.S, t.Y, mi, sh, lane);
+      if (!diag_invert(t.S, t.Y, mi, sh, lane) && lane == 0) {
+        __hip_atomic_store(a.info, 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        *s_ok = 0;
+      }
     } else if ((wave == 1 || wave == 2) && more) {
       // wave 1: block (r, i), wave 2: block (r, r), from their workgroups' sums
       // over j < r - 2 (none for r < 3), with column j = i - 1 added here
