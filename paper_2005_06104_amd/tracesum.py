@@ -18,12 +18,13 @@ intervals) is attributed to the innermost range the host was in at the
 middle of each gap, and to the kernel that ran before it.
 
     python -m paper_2005_06104_amd.tracesum --counters <counter_collection.csv>
-        [--kernel SUBSTRING] [--marker NAME] [--calib SUBSTRING --calib-bytes N]
+        [--kernel SUBSTRING ...] [--marker NAME] [--calib SUBSTRING --calib-bytes N]
 
 With --counters the file is the counter output of a `rocprofv3 --pmc` run
 (one row per dispatch and counter): the dispatches between the first and
-the last marker dispatch whose name contains SUBSTRING are averaged per
-counter (--marker none: every dispatch of the file); --calib names a plain copy kernel of N bytes read and N written
+the last marker dispatch whose name contains every SUBSTRING (the FP32
+one-site H_eff GEMM where none is given) are averaged per counter, and the
+names listed (--marker none: every dispatch of the file); --calib names a plain copy kernel of N bytes read and N written
 (anywhere in the file), whose FETCH_SIZE / WRITE_SIZE give the factors that
 turn those counters into bytes.
 """
@@ -182,9 +183,15 @@ def _counter_rows(path):
             yield int(r[i_id]), r[i_name], r[i_cn], float(r[i_cv])
 
 
+# the one-site H_eff GEMM (tag 1) on operands of three BF16 terms, any tile
+HEFF_FP32 = ("gemm_split_kernel<", "SplitTile<3,", ", 1>(")
+
+
 def counters(path, kernel, marker="spin_kernel", calib=None, calib_bytes=None):
-    """Per-dispatch averages of every counter for the kernels containing
-    `kernel` inside the marked window, plus the copy calibration."""
+    """Per-dispatch averages of every counter for the kernels whose names contain
+    `kernel` (or every one of several texts) inside the marked window, the names
+    that were averaged over, plus the copy calibration."""
+    texts = [kernel] if isinstance(kernel, str) else list(kernel)
     # one dispatch may appear on several rows (one per counter, or per
     # counter dimension): values of one dispatch and counter are summed
     per = defaultdict(lambda: defaultdict(float))
@@ -199,12 +206,12 @@ def counters(path, kernel, marker="spin_kernel", calib=None, calib_bytes=None):
         lo, hi = marks[0], marks[-1]
     else:   # no window: every dispatch of the file
         lo, hi = min(names) - 1, max(names) + 1
-    sel = [d for d, n in names.items() if lo < d < hi and kernel in n]
+    sel = [d for d, n in names.items() if lo < d < hi and all(t in n for t in texts)]
     if not sel:
-        raise SystemExit(f"no dispatch of {kernel!r} between the markers in {path}")
+        raise SystemExit(f"no dispatch of {texts!r} between the markers in {path}")
     cn = sorted({c for d in sel for c in per[d]})
     avg = {c: sum(per[d].get(c, 0.0) for d in sel) / len(sel) for c in cn}
-    out = {"dispatches": len(sel), "avg": avg}
+    out = {"dispatches": len(sel), "kernels": sorted({names[d] for d in sel}), "avg": avg}
     if calib:
         cal = [d for d, n in names.items() if calib in n]
         if cal and calib_bytes:
@@ -229,14 +236,15 @@ def main(argv=None):
     ap.add_argument("--top", type=int, default=40)
     ap.add_argument("--ranges", default=None, help="a marker_api_trace.csv of the same run: host time per range")
     ap.add_argument("--counters", action="store_true", help="the file is a rocprofv3 --pmc counter file")
-    ap.add_argument("--kernel", default=", false, false, 1>")
+    ap.add_argument("--kernel", action="append", default=None,
+                    help="text in the kernel's name; several: all of them (default: the FP32 one-site H_eff GEMM)")
     ap.add_argument("--calib", default=None, help="name of a plain copy kernel in the same file")
     ap.add_argument("--calib-bytes", type=float, default=None, help="bytes the copy reads (and writes)")
     a = ap.parse_args(argv)
     if a.counters:
         import json
         marker = None if a.marker.lower() == "none" else a.marker
-        print(json.dumps(counters(a.trace, a.kernel, marker, a.calib, a.calib_bytes), indent=1))
+        print(json.dumps(counters(a.trace, a.kernel or HEFF_FP32, marker, a.calib, a.calib_bytes), indent=1))
         return
     print(summarize(a.trace, a.marker, a.split_grid, a.top, a.ranges))
 
