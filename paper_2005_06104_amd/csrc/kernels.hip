@@ -164,7 +164,8 @@ __device__ inline void deal_pieces(const TileJob& job, bool mapped, int wave, in
 //   TERMS 1: plain BF16 inputs;
 //   TERMS 2: x = h + l, three products (about 16 bits);
 //   TERMS 3: x = h + m + l exactly (24 bits), six products; what is left out
-//            (m l, l m, l l) is at most 2^-25 of the product.
+//            (m l, l m, l l) is less than 2^-24 of the product: |m| is at most
+//            2^-8 / (1 + 2^-8) of x, |l| 2^-17 (x = 1 + 2^-8 - 2^-17: 2^-24.01).
 // BF16 ends at 2^-133, FP32 at 2^-149: for TERMS 3 both operands are multiplied
 // by 2^20 on the way in (exact) and the sums by 2^-40 on the way out, so that
 // the last term of every normal FP32 number is there (2% of a large product's
@@ -211,7 +212,7 @@ __device__ inline int plane_at(int row, int ch) { return row * BKS + ((ch ^ (-(r
 // costs one address register.  WIDE: leading dimensions whose tile reaches
 // outside the buffer's 2^31 bytes, past its end or (negative ones) before its
 // base, plain addresses.
-constexpr long long LD_WIDE = 1LL << 20;   // 128 rows of 2^20 complex64: 2^30 bytes
+constexpr long long LD_WIDE = 1LL << 20;   // 256 rows, 2^20 - 1 complex64 apart: just under 2^31 bytes
 inline bool wide_ld(long long lda, long long ldb, long long limit) {
   return lda < 0 || ldb < 0 || lda >= limit || ldb >= limit;
 }
@@ -402,6 +403,8 @@ __global__ __launch_bounds__(TL::NTH, TL::OCC) void gemm_split_kernel(
   constexpr int TERMS = TL::TERMS, TM = TL::TM, TN = TL::TN, WM = TL::WM, WN = TL::WN, NTH = TL::NTH;
   constexpr int SI = TM / WM / 16, SJ = TN / WN / 16, PA = TM * BKS, PB = TN * BKS;
   constexpr bool BN = SI > SJ;
+  static_assert(TL::WIDE || ((TM > TN ? TM : TN) * (LD_WIDE - 1) + BKS) * 8 <= (long long)BUF_BYTES,
+                "a tile's rows within the buffer");
   __shared__ __attribute__((aligned(16))) unsigned short As[2 * TERMS * PA], Bs[2 * TERMS * PB];
 
   const int tid = threadIdx.x;
@@ -862,6 +865,8 @@ __global__ __launch_bounds__(TL::NTH, TL::NTH > 512 ? 4 : 2) void gemm_direct_ke
     long long ldc, long long sc, int S, int Kc, long long sps, const int4* __restrict__ kit,
     const int2* __restrict__ kiv, int conj) {
   constexpr int SI = TL::SI, SJ = TL::SJ, WN = TL::WN, PF = TL::PF, E = SI * SJ * 4;
+  static_assert(TL::WIDE || ((TL::TM > TL::TN ? TL::TM : TL::TN) * (LD_WIDE64 - 1) + 4) * 16 <= (long long)BUF_BYTES,
+                "a tile's rows within the buffer");
   extern __shared__ unsigned char direct_lds[];
   const int tid = threadIdx.x, lane = tid & 63, lr = lane & 15, lk = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1776,7 +1781,6 @@ __global__ void zscale_kernel(double2* __restrict__ dst, const double2* __restri
   dst[x] = make_double2(ar * v.x - ai * v.y, ar * v.y + ai * v.x);
 }
 
-// dst = src / sqrt(Re *nrm2): normalisation by a norm that is still on the device
 // w += sign * V c with c_j the sum of the nb partial dot products
 // partial[b * nv + j] (zdots_partial_kernel's layout): every block forms c
 // itself, in the same fixed order, so no separate reduction launch is
