@@ -394,8 +394,94 @@ struct SplitTile {
   static constexpr bool MAPPED = MAPPED_, WIDE = WIDE_;
 };
 
+// Three terms: an infinity, or a number or sum that the scale takes to one, has
+// none (h - x is not finite).  Such elements of a wave (a bit each in `again`, (i
+// SJ + j) 4 + r) are formed again from the operands themselves, a row of 16 x 16
+// pieces at a time on the FP32 matrix cores (v_mfma_f32_16x16x4f32, outputs as
+// the BF16 one), in the 3M form of the FP64 kernel, U steps of four k in flight.
+// 2048 x 2048 x 1024: all elements again 550 us, a column of B 230 to 460,
+// none 174 (a lane per element: 8470; the FP32 matrix cores alone: 278).
+struct Again {
+  const float2 *A, *B;
+  float2* C;
+  long long lda, ldb, ldc;
+  KIter kr;
+  int m0, n0;           // the tile's first row and column in C
+  int r0, r1, c0, c1;   // the tile's rows and columns that are there
+  int ro, co;           // the wave's first in the tile
+  int conj;
+  float ar, ai, br, bi;
+};
+template <bool TA, bool TB, int SI, int SJ>
+__device__ inline void form_again(const Again w, unsigned again) {
+  constexpr int U = 4;
+  const int lane = threadIdx.x & 63, lr = lane & 15, lk = lane >> 4;
+  const float ca = (w.conj & 1) ? -1.f : 1.f, cb = (w.conj & 2) ? -1.f : 1.f;
+  const bool has_beta = w.br != 0.f || w.bi != 0.f;
+#pragma unroll 1
+  for (int i = 0; i < SI; ++i) {
+    const unsigned mine = again >> (4 * SJ * i) & ((1u << (4 * SJ)) - 1);
+    if (!__any(mine != 0)) continue;
+    const int rt = w.ro + 16 * i;   // the pieces that a wave has follow one another
+    const int am = rt + lr;
+    const bool aok = am >= w.r0 && am < w.r1;
+    const float2* ap = TA ? w.A + (w.m0 + am) : w.A + (long long)(w.m0 + am) * w.lda;
+    f4 p1[SJ], p2[SJ], p3[SJ];
+#pragma unroll
+    for (int j = 0; j < SJ; ++j) p1[j] = p2[j] = p3[j] = f4{0, 0, 0, 0};
+    for (int v = 0; v < w.kr.n; ++v) {
+      const int2 I = w.kr.at(v);
+      for (int k = I.x; k < I.y; k += 4 * U) {
+        float2 a[U], b[U][SJ];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const int kk = k + 4 * u + lk;
+          const bool in = kk < I.y;
+          a[u] = float2{0.f, 0.f};
+          if (in && aok) a[u] = TA ? ap[(long long)kk * w.lda] : ap[kk];
+#pragma unroll
+          for (int j = 0; j < SJ; ++j) {
+            const int bn = w.co + 16 * j + lr;
+            b[u][j] = float2{0.f, 0.f};
+            if (in && bn >= w.c0 && bn < w.c1)
+              b[u][j] = TB ? w.B[(long long)(w.n0 + bn) * w.ldb + kk] : w.B[(long long)kk * w.ldb + (w.n0 + bn)];
+          }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const float ay = ca * a[u].y, as = a[u].x + ay;
+#pragma unroll
+          for (int j = 0; j < SJ; ++j) {
+            const float by = cb * b[u][j].y;
+            p1[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u].x, b[u][j].x, p1[j], 0, 0, 0);
+            p2[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(ay, by, p2[j], 0, 0, 0);
+            p3[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(as, b[u][j].x + by, p3[j], 0, 0, 0);
+          }
+        }
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < SJ; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int lm = rt + lk * 4 + r, ln = w.co + 16 * j + lr;
+        if (mine >> (4 * j + r) & 1) {
+          const float xr = p1[j][r] - p2[j][r], xi = p3[j][r] - p1[j][r] - p2[j][r];
+          float2* c = w.C + (long long)(w.m0 + lm) * w.ldc + (w.n0 + ln);
+          float2 o{w.ar * xr - w.ai * xi, w.ar * xi + w.ai * xr};
+          if (has_beta) {
+            const float2 old = *c;
+            o.x += w.br * old.x - w.bi * old.y;
+            o.y += w.br * old.y + w.bi * old.x;
+          }
+          *c = o;
+        }
+      }
+  }
+}
+
 // conj: bit 0 conjugates A, bit 1 conjugates B (on the way into LDS).
-template <class TL, bool TA, bool TB, int TAG>
+template <class TL, bool TA, bool TB, bool BETA, int TAG>
 __global__ __launch_bounds__(TL::NTH, TL::OCC) void gemm_split_kernel(
     int M, int N, int K, float ar, float ai, const float* __restrict__ A, long long lda, long long sa,
     const float* __restrict__ B, long long ldb, long long sb, float br, float bi, float* __restrict__ C, long long ldc,
@@ -506,98 +592,52 @@ __global__ __launch_bounds__(TL::NTH, TL::OCC) void gemm_split_kernel(
     kend = nkend;
   }
 
-  const bool has_beta = (br != 0.f) || (bi != 0.f);
-  auto put = [&](int gm, int gn, float xr, float xi) {
+  const float2* c_some = Cb + ((long long)(m0 + job.r0) * ldc + (n0 + job.c0));   // an element that is there
+  auto put = [&](float2* c, float xr, float xi, float2 old) {
     float2 o;
     o.x = ar * xr - ai * xi;
     o.y = ar * xi + ai * xr;
-    if (has_beta) {
-      const float2 old = Cb[(long long)gm * ldc + gn];
+    if constexpr (BETA) {
       o.x += br * old.x - bi * old.y;
       o.y += br * old.y + bi * old.x;
     }
-    Cb[(long long)gm * ldc + gn] = o;
+    *c = o;
   };
   static_assert(TERMS < 3 || SI * SJ * 4 <= 32, "a bit per element of a lane");
   unsigned again = 0;   // TERMS 3: the elements to be formed again, bit (i SJ + j) 4 + r
 #pragma unroll
-  for (int i = 0; i < SI; ++i)
-#pragma unroll
-    for (int j = 0; j < SJ; ++j) {
-      if (TL::MAPPED && (i >= ni || j >= nj)) continue;
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int lm = ro[i] + lk * 4 + r, ln = co[j] + lr;
-        const int gm = m0 + lm;
-        const int gn = n0 + ln;
-        if (gm < M && gn < N && lm >= job.r0 && lm < job.r1 && ln >= job.c0 && ln < job.c1) {
-          const float down = TERMS == 3 ? 1.f / (UP3 * UP3) : 1.f;
-          const float xr = down * cr[i][j][r], xi = down * ci[i][j][r];
-          if (TERMS == 3 && !(__builtin_isfinite(xr) && __builtin_isfinite(xi))) again |= 1u << ((i * SJ + j) * 4 + r);
-          else put(gm, gn, xr, xi);
-        }
-      }
-    }
-  if constexpr (TERMS == 3) {
-    // An infinity, or a number or sum that the scale takes to one, has no such
-    // terms (h - x is not finite): these elements are formed again from the
-    // operands themselves, a row of 16 x 16 pieces at a time on the FP32 matrix
-    // cores (v_mfma_f32_16x16x4f32, outputs as above), in the 3M form of the FP64
-    // kernel, U steps of four k in flight.
-    // 2048 x 2048 x 1024: all elements again 550 us, a column of B 230 to 460,
-    // none 174 (a lane per element: 8470; the FP32 matrix cores alone: 278).
-    constexpr int U = 4;
-    const float ca = (conj & 1) ? -1.f : 1.f, cb = (conj & 2) ? -1.f : 1.f;
-#pragma unroll 1
-    for (int i = 0; i < SI; ++i) {
-      const unsigned mine = again >> (4 * SJ * i) & ((1u << (4 * SJ)) - 1);
-      if (!__any(mine != 0)) continue;
-      const int rt = ro[0] + 16 * i;   // the pieces that a wave has follow one another
-      const int am = rt + lr;
-      const bool aok = m0 + am < M && am >= job.r0 && am < job.r1;
-      const float2* ap = TA ? Ab + (m0 + am) : Ab + (long long)(m0 + am) * lda;
-      f4 p1[SJ], p2[SJ], p3[SJ];
-#pragma unroll
-      for (int j = 0; j < SJ; ++j) p1[j] = p2[j] = p3[j] = f4{0, 0, 0, 0};
-      for (int v = 0; v < kr_.n; ++v) {
-        const int2 I = kr_.at(v);
-        for (int k = I.x; k < I.y; k += 4 * U) {
-          float2 a[U], b[U][SJ];
-#pragma unroll
-          for (int u = 0; u < U; ++u) {
-            const int kk = k + 4 * u + lk;
-            const bool in = kk < I.y;
-            a[u] = float2{0.f, 0.f};
-            if (in && aok) a[u] = TA ? ap[(long long)kk * lda] : ap[kk];
-#pragma unroll
-            for (int j = 0; j < SJ; ++j) {
-              const int bn = co[0] + 16 * j + lr;
-              b[u][j] = float2{0.f, 0.f};
-              if (in && n0 + bn < N && bn >= job.c0 && bn < job.c1)
-                b[u][j] = TB ? Bb[(long long)(n0 + bn) * ldb + kk] : Bb[(long long)kk * ldb + (n0 + bn)];
-            }
-          }
-#pragma unroll
-          for (int u = 0; u < U; ++u) {
-            const float ay = ca * a[u].y, as = a[u].x + ay;
-#pragma unroll
-            for (int j = 0; j < SJ; ++j) {
-              const float by = cb * b[u][j].y;
-              p1[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u].x, b[u][j].x, p1[j], 0, 0, 0);
-              p2[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(ay, by, p2[j], 0, 0, 0);
-              p3[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(as, b[u][j].x + by, p3[j], 0, 0, 0);
-            }
-          }
-        }
-      }
+  for (int i = 0; i < SI; ++i) {
+    if (TL::MAPPED && i >= ni) break;
+    auto there = [&](int j, int r) {
+      const int lm = ro[i] + lk * 4 + r, ln = co[j] + lr;
+      return m0 + lm < M && n0 + ln < N && lm >= job.r0 && lm < job.r1 && ln >= job.c0 && ln < job.c1;
+    };
+    auto c_at = [&](int j, int r) { return Cb + ((long long)(m0 + ro[i] + lk * 4 + r) * ldc + (n0 + co[j] + lr)); };
+    // what C held comes in one round trip, not in one an element: no branches
+    float2 old[SJ][4];
+    if constexpr (BETA) {
 #pragma unroll
       for (int j = 0; j < SJ; ++j)
 #pragma unroll
-        for (int r = 0; r < 4; ++r)
-          if (mine >> (4 * j + r) & 1)
-            put(m0 + rt + lk * 4 + r, n0 + co[0] + 16 * j + lr, p1[j][r] - p2[j][r], p3[j][r] - p1[j][r] - p2[j][r]);
+        for (int r = 0; r < 4; ++r) old[j][r] = *(there(j, r) ? c_at(j, r) : c_some);
+    }
+#pragma unroll
+    for (int j = 0; j < SJ; ++j) {
+      if (TL::MAPPED && j >= nj) continue;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        if (!there(j, r)) continue;
+        constexpr float down = TERMS == 3 ? 1.f / (UP3 * UP3) : 1.f;
+        const float xr = down * cr[i][j][r], xi = down * ci[i][j][r];
+        if (TERMS == 3 && !(__builtin_isfinite(xr) && __builtin_isfinite(xi))) again |= 1u << ((i * SJ + j) * 4 + r);
+        else put(c_at(j, r), xr, xi, old[j][r]);
+      }
     }
   }
+  if constexpr (TERMS == 3)
+    form_again<TA, TB, SI, SJ>(Again{Ab, Bb, Cb, lda, ldb, ldc, kr_, m0, n0, job.r0, min(job.r1, M - m0), job.c0,
+                                     min(job.c1, N - n0), ro[0], co[0], conj, ar, ai, br, bi},
+                               again);
 }
 
 // ---------------------------------------------------------------- term images
@@ -691,7 +731,7 @@ struct ImageTile {
 
 // IA, IB: images of op(A) (rows m) and op(B) (rows n) of nkc k blocks, padded to
 // whole tiles by the host.  Split s of S takes k from s Kc.
-template <class TL>
+template <class TL, bool BETA>
 __global__ __launch_bounds__(TL::NTH, TL::OCC) void gemm_image_kernel(
     int M, int N, int K, float ar, float ai, const unsigned short* __restrict__ IA,
     const unsigned short* __restrict__ IB, int nkc, float br, float bi, float* __restrict__ C, long long ldc, int S,
@@ -769,27 +809,34 @@ __global__ __launch_bounds__(TL::NTH, TL::OCC) void gemm_image_kernel(
     }
   }
 
-  const bool has_beta = (br != 0.f) || (bi != 0.f);
 #pragma unroll
-  for (int i = 0; i < SI; ++i)
+  for (int i = 0; i < SI; ++i) {
+    const int gm0 = m0 + wm * (TM / WM) + i * 16 + lk * 4, gn0 = n0 + wn * (TN / WN) + lr;
+    auto there = [&](int j, int r) { return gm0 + r < M && gn0 + j * 16 < N; };
+    auto c_at = [&](int j, int r) { return Cb + ((long long)(gm0 + r) * ldc + (gn0 + j * 16)); };
+    float2 old[SJ][4];   // what C held, in one round trip
+    if constexpr (BETA) {
+#pragma unroll
+      for (int j = 0; j < SJ; ++j)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) old[j][r] = *(there(j, r) ? c_at(j, r) : Cb + ((long long)m0 * ldc + n0));
+    }
 #pragma unroll
     for (int j = 0; j < SJ; ++j)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int gm = m0 + wm * (TM / WM) + i * 16 + lk * 4 + r, gn = n0 + wn * (TN / WN) + j * 16 + lr;
-        if (gm < M && gn < N) {
-          const float xr = cr[i][j][r], xi = ci[i][j][r];
-          float2 o;
-          o.x = ar * xr - ai * xi;
-          o.y = ar * xi + ai * xr;
-          if (has_beta) {
-            const float2 old = Cb[(long long)gm * ldc + gn];
-            o.x += br * old.x - bi * old.y;
-            o.y += br * old.y + bi * old.x;
-          }
-          Cb[(long long)gm * ldc + gn] = o;
+        if (!there(j, r)) continue;
+        const float xr = cr[i][j][r], xi = ci[i][j][r];
+        float2 o;
+        o.x = ar * xr - ai * xi;
+        o.y = ar * xi + ai * xr;
+        if constexpr (BETA) {
+          o.x += br * old[j][r].x - bi * old[j][r].y;
+          o.y += br * old[j][r].y + bi * old[j][r].x;
         }
+        *c_at(j, r) = o;
       }
+  }
 }
 
 // ---------------------------------------------------------------- FP64 GEMM
@@ -858,7 +905,7 @@ template <bool KC, bool WIDE, int NP> struct DirectOperand {
 
 // S splits over the grid, or (PARTS > 1) a block's waves as parts of Kc each;
 // conj: bit 0 conjugates A, bit 1 conjugates B
-template <class TL, bool TA, bool TB, int TAG>
+template <class TL, bool TA, bool TB, bool BETA, int TAG>
 __global__ __launch_bounds__(TL::NTH, TL::NTH > 512 ? 4 : 2) void gemm_direct_kernel(
     int M, int N, int K, double ar, double ai, const double* __restrict__ A, long long lda, long long sa,
     const double* __restrict__ B, long long ldb, long long sb, double br, double bi, double* __restrict__ C,
@@ -978,15 +1025,20 @@ __global__ __launch_bounds__(TL::NTH, TL::NTH > 512 ? 4 : 2) void gemm_direct_ke
     for (int e = 0; e < E; ++e) red[(wk * E + e) * 64] = x[e];
     __syncthreads();
   }
-  const bool has_beta = (br != 0.0) || (bi != 0.0);
   double2* Cb = reinterpret_cast<double2*>(C) + job.bz * sc + job.split * sps;
-#pragma unroll
-  for (int e = 0; e < E; ++e) {
-    const int i = e / 4 / SJ, j = e / 4 % SJ, r = e % 4;
-    if (i >= ni || j >= nj) continue;
+  // row of the MFMA's result r: lane / 16 + 4 r, column lane % 16
+  auto there = [&](int e) {
+    const int lm = ro[e / 4 / SJ] + lk + 4 * (e % 4), ln = co[e / 4 % SJ] + lr;
+    return job.m0 + lm < M && job.n0 + ln < N && lm >= job.r0 && lm < job.r1 && ln >= job.c0 && ln < job.c1;
+  };
+  auto c_at = [&](int e) {
+    return Cb + ((long long)(job.m0 + ro[e / 4 / SJ] + lk + 4 * (e % 4)) * ldc + (job.n0 + co[e / 4 % SJ] + lr));
+  };
+  const double2* c_some = Cb + ((long long)(job.m0 + job.r0) * ldc + (job.n0 + job.c0));   // an element that is there
+  // the entry's sum over the parts
+  auto sum = [&](int e) {
     double2 v = x[e];
     if (parts > 1) {
-      if (e % parts != wk) continue;   // the parts' waves share the sums and stores
       v = double2{0.0, 0.0};
       for (int w = 0; w < parts; ++w) {
         const double2 u = red[(w * E + e) * 64];
@@ -994,17 +1046,36 @@ __global__ __launch_bounds__(TL::NTH, TL::NTH > 512 ? 4 : 2) void gemm_direct_ke
         v.y += u.y;
       }
     }
-    // row of the MFMA's result r: lane / 16 + 4 r, column lane % 16
-    const int lm = ro[i] + lk + 4 * r, ln = co[j] + lr;
-    const int gm = job.m0 + lm, gn = job.n0 + ln;
-    if (gm < M && gn < N && lm >= job.r0 && lm < job.r1 && ln >= job.c0 && ln < job.c1) {
+    return v;
+  };
+  auto mine = [&](int e) {   // the parts' waves share the sums and stores
+    return e / 4 / SJ < ni && e / 4 % SJ < nj && (parts == 1 || e % parts == wk);
+  };
+  if constexpr (!BETA) {
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      if (!mine(e)) continue;
+      const double2 v = sum(e);
+      if (there(e)) *c_at(e) = double2{ar * v.x - ai * v.y, ar * v.y + ai * v.x};
+    }
+    return;
+  }
+  constexpr int G = E < 8 ? E : 8;
+#pragma unroll
+  for (int e0 = 0; e0 < E; e0 += G) {
+    // what C held comes in one round trip, not in one an entry: no branches
+    double2 old[G];
+#pragma unroll
+    for (int g = 0; g < G; ++g) old[g] = *(there(e0 + g) ? c_at(e0 + g) : c_some);
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      const int e = e0 + g;
+      if (!mine(e)) continue;
+      const double2 v = sum(e);
       double2 o{ar * v.x - ai * v.y, ar * v.y + ai * v.x};
-      if (has_beta) {
-        const double2 old = Cb[(long long)gm * ldc + gn];
-        o.x += br * old.x - bi * old.y;
-        o.y += br * old.y + bi * old.x;
-      }
-      Cb[(long long)gm * ldc + gn] = o;
+      o.x += br * old[g].x - bi * old[g].y;
+      o.y += br * old[g].y + bi * old[g].x;
+      if (there(e)) *c_at(e) = o;
     }
   }
 }
@@ -1135,9 +1206,13 @@ template <> struct SplitTiles<1> {
 template <class TL, bool TA, bool TB, int TAG>
 void launch_split_tile(dim3 grid, const Product<float>& p, float* C, long long ldc, long long sc, bool plain, int S,
                        int Kc, long long sps, const int4* kit, const int2* kiv, int conj) {
-  hipLaunchKernelGGL((gemm_split_kernel<TL, TA, TB, TAG>), grid, dim3(TL::NTH), 0, p.s, p.M, p.N, p.K,
-                     plain ? 1.f : p.ar, plain ? 0.f : p.ai, p.A, p.lda, p.sa, p.B, p.ldb, p.sb, plain ? 0.f : p.br,
-                     plain ? 0.f : p.bi, C, ldc, sc, S, Kc, sps, kit, kiv, conj);
+  auto go = [&](auto beta) {
+    hipLaunchKernelGGL((gemm_split_kernel<TL, TA, TB, decltype(beta)::value, TAG>), grid, dim3(TL::NTH), 0, p.s, p.M, p.N,
+                       p.K, plain ? 1.f : p.ar, plain ? 0.f : p.ai, p.A, p.lda, p.sa, p.B, p.ldb, p.sb, p.br, p.bi, C, ldc,
+                       sc, S, Kc, sps, kit, kiv, conj);
+  };
+  if (plain || (p.br == 0.f && p.bi == 0.f)) go(std::false_type{});
+  else go(std::true_type{});
 }
 
 // kit null: the dense grid on tile `tile` of SplitTiles (S > 1: partial
@@ -1311,12 +1386,15 @@ void launch_images(const Product<float>& p, bool ta, bool tb, int conj, const Im
         float* C = p.C + 2 * (m0 * p.ldc + n0);
         auto product = [&](auto tl) {
           using TL = decltype(tl);
-          if (S == 1)
-            hipLaunchKernelGGL((gemm_image_kernel<TL>), grid, dim3(TL::NTH), 0, p.s, M, N, K, p.ar, p.ai, ia, ib, nkc, br,
-                               bi, C, p.ldc, 1, Kc, 0LL);
+          if (S > 1)
+            hipLaunchKernelGGL((gemm_image_kernel<TL, false>), grid, dim3(TL::NTH), 0, p.s, M, N, K, 1.f, 0.f, ia, ib, nkc,
+                               0.f, 0.f, part, (long long)N, S, Kc, mn);
+          else if (br == 0.f && bi == 0.f)
+            hipLaunchKernelGGL((gemm_image_kernel<TL, false>), grid, dim3(TL::NTH), 0, p.s, M, N, K, p.ar, p.ai, ia, ib, nkc,
+                               0.f, 0.f, C, p.ldc, 1, Kc, 0LL);
           else
-            hipLaunchKernelGGL((gemm_image_kernel<TL>), grid, dim3(TL::NTH), 0, p.s, M, N, K, 1.f, 0.f, ia, ib, nkc, 0.f,
-                               0.f, part, (long long)N, S, Kc, mn);
+            hipLaunchKernelGGL((gemm_image_kernel<TL, true>), grid, dim3(TL::NTH), 0, p.s, M, N, K, p.ar, p.ai, ia, ib, nkc,
+                               br, bi, C, p.ldc, 1, Kc, 0LL);
         };
         if (g.tile == 0) product(typename TS::T0{});
         else product(typename TS::T1{});
@@ -1411,13 +1489,18 @@ void launch_direct_tile(const Product<double>& p, int n_items, double* C, long l
   const dim3 grid = kit ? dim3(n_items)
                         : dim3((p.N + TL::TN - 1) / TL::TN, (p.M + TL::TM - 1) / TL::TM, S > 1 ? S : p.batch);
   const size_t lds = parts > 1 ? (size_t)parts * TL::SI * TL::SJ * 256 * sizeof(double2) : 0;
-  if (lds > 64 * 1024) {   // per device, and cheap next to a launch that takes this much
-    HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_direct_kernel<TL, TA, TB, TAG>),
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-  }
-  hipLaunchKernelGGL((gemm_direct_kernel<TL, TA, TB, TAG>), grid, dim3(TL::WM * TL::WN * parts * 64), lds, p.s, p.M,
-                     p.N, p.K, plain ? 1.0 : p.ar, plain ? 0.0 : p.ai, p.A, p.lda, p.sa, p.B, p.ldb, p.sb,
-                     plain ? 0.0 : p.br, plain ? 0.0 : p.bi, C, ldc, sc, S, Kc, sps, kit, kiv, conj);
+  auto go = [&](auto beta) {
+    const auto kernel = gemm_direct_kernel<TL, TA, TB, decltype(beta)::value, TAG>;
+    if (lds > 64 * 1024) {   // per device, and cheap next to a launch that takes this much
+      HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                    (int)lds));
+    }
+    hipLaunchKernelGGL(kernel, grid, dim3(TL::WM * TL::WN * parts * 64), lds, p.s, p.M, p.N, p.K, plain ? 1.0 : p.ar,
+                       plain ? 0.0 : p.ai, p.A, p.lda, p.sa, p.B, p.ldb, p.sb, p.br, p.bi, C, ldc, sc, S, Kc, sps, kit, kiv,
+                       conj);
+  };
+  if (plain || (p.br == 0.0 && p.bi == 0.0)) go(std::false_type{});
+  else go(std::true_type{});
 }
 
 template <bool TA, bool TB, int TAG>
