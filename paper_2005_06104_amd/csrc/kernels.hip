@@ -184,13 +184,20 @@ constexpr float UP3 = 0x1p20f;
 
 typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
+typedef short s4 __attribute__((ext_vector_type(4)));
 typedef float f2v __attribute__((ext_vector_type(2)));
+typedef unsigned u2v __attribute__((ext_vector_type(2)));
 typedef float f4u __attribute__((ext_vector_type(4), aligned(8)));
 
 __device__ inline f4 mfma_bf16(uint4 a, uint4 b, f4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf8, a), __builtin_bit_cast(bf8, b), c, 0, 0,
                                                   0);
 }
+// four k values a lane (v_mfma_f32_16x16x16_bf16: 4*(l/16)..+3)
+__device__ inline f4 mfma_bf16(uint2 a, uint2 b, f4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(s4, a), __builtin_bit_cast(s4, b), c, 0, 0, 0);
+}
+__device__ inline uint2 bf16_flip(uint2 v, unsigned s) { return uint2{v.x ^ s, v.y ^ s}; }
 __device__ inline uint4 bf16_flip(uint4 v, unsigned s) { return uint4{v.x ^ s, v.y ^ s, v.z ^ s, v.w ^ s}; }
 
 // Operand tile of ROWS rows (m of A or n of B) x 32 k in chunks of eight
@@ -289,14 +296,16 @@ __device__ inline void chunk_load(const float2* __restrict__ X, long long ld, in
   }
 }
 
-// the TERMS BF16 terms of eight numbers (neg: of their negatives), packed
-template <int TERMS>
-__device__ inline void bf16_terms(const float (&x)[8], bool neg, uint4 (&o)[TERMS]) {
+// the TERMS BF16 terms of eight (uint4) or four (uint2) numbers (neg: of their
+// negatives), packed
+template <int TERMS, class V>
+__device__ inline void bf16_terms(const float (&x)[sizeof(V) / 2], bool neg, V (&o)[TERMS]) {
   const float up = neg ? -UP3 : UP3;
   const unsigned flip = neg ? 0x80008000u : 0u;
-  unsigned w[TERMS][4];
+  constexpr int P = sizeof(V) / 4;
+  unsigned w[TERMS][P];
 #pragma unroll
-  for (int p = 0; p < 4; ++p) {
+  for (int p = 0; p < P; ++p) {
     f2v v;
     v.x = TERMS == 3 ? x[2 * p] * up : x[2 * p];
     v.y = TERMS == 3 ? x[2 * p + 1] * up : x[2 * p + 1];
@@ -311,7 +320,8 @@ __device__ inline void bf16_terms(const float (&x)[8], bool neg, uint4 (&o)[TERM
   }
 #pragma unroll
   for (int t = 0; t < TERMS; ++t) {
-    o[t] = uint4{w[t][0], w[t][1], w[t][2], w[t][3]};
+    if constexpr (P == 4) o[t] = uint4{w[t][0], w[t][1], w[t][2], w[t][3]};
+    else o[t] = uint2{w[t][0], w[t][1]};
     if (TERMS < 3) o[t] = bf16_flip(o[t], flip);
   }
 }
@@ -344,17 +354,17 @@ __device__ inline void chunk_store(unsigned short* P, int tid, const float2 (&v)
 // cr += a_r b_r - a_i b_i, ci += a_r b_i + a_i b_r over a step's 32 k,
 // for one row piece and NJ column pieces.  The sign goes to A, or, if the caller
 // has more row than column pieces, to b_n = -b_i.
-template <int TERMS, int NJ, bool BN = false>
-__device__ inline void step_products(const uint4 (&a_r)[TERMS], const uint4 (&a_i)[TERMS],
-                                     const uint4 (&b_r)[NJ][TERMS], const uint4 (&b_i)[NJ][TERMS],
-                                     const uint4 (&b_n)[NJ][TERMS], f4 (&cr)[NJ], f4 (&ci)[NJ]) {
+template <int TERMS, int NJ, bool BN = false, class V>
+__device__ inline void step_products(const V (&a_r)[TERMS], const V (&a_i)[TERMS], const V (&b_r)[NJ][TERMS],
+                                     const V (&b_i)[NJ][TERMS], const V (&b_n)[NJ][TERMS], f4 (&cr)[NJ],
+                                     f4 (&ci)[NJ]) {
   // TERMS 3: a step's products are summed on their own and added to the running
   // sums once: a sum over K rounds K / 32 times at its full size instead of
   // 3/8 K times (M x N x K = 20480 x 2048 x 1024: error 1.1e-7 against 7.1e-7
   // with the running sums in the matrix cores and 8.0e-7 on the FP32 matrix
   // cores).  Fewer terms: too few products a step for that.
   constexpr bool APART = TERMS == 3;
-  uint4 a_n[TERMS];
+  V a_n[TERMS];
 #pragma unroll
   for (int t = 0; t < TERMS; ++t) a_n[t] = BN ? a_i[t] : bf16_flip(a_i[t], 0x80008000u);
   f4 xr[NJ], xi[NJ];
@@ -638,6 +648,147 @@ __global__ __launch_bounds__(TL::NTH, TL::OCC) void gemm_split_kernel(
     form_again<TA, TB, SI, SJ>(Again{Ab, Bb, Cb, lda, ldb, ldc, kr_, m0, n0, job.r0, min(job.r1, M - m0), job.c0,
                                      min(job.c1, N - n0), ro[0], co[0], conj, ar, ai, br, bi},
                                again);
+}
+
+// ---------------------------------------------------------------- short products
+// Three terms, K of at most 32: one step, so nothing is staged.  Every wave loads
+// its SI row pieces in the MFMA layout (lane l: row l % 16, k KL (l / 16) on),
+// converts them and multiplies them with NJ column pieces, one after the other:
+// the sums of a gemm_split_kernel of one step, the same bits.  What bounds it: the
+// store (and, with beta, the load) of C on large outputs, with the vector
+// instructions close behind, so C and the operands are addressed by 32-bit offsets
+// and a wave looks at its elements one by one only if one is not finite.
+// M x N x K (batch), staged / here in us: 8000 x 5000 x 8 97 / 71, with beta 277 /
+// 143 (the store alone at 5.5 TB/s: 58); 2000 x 1500 x 16 13.7 / 11.6; 386 x 133 x 8
+// (200) 46 / 25; 887 x 2 x 4 (200) 26 / 11; 14 x 304972 x 8 45 / 18.
+template <int KL_, int SI_, int NJ_, int WM_, int WN_> struct ShortTile {
+  static constexpr int KL = KL_, SI = SI_, NJ = NJ_, WM = WM_, WN = WN_, TM = WM * SI * 16, TN = WN * NJ * 16;
+  static_assert(WM * WN == 4 && SI * NJ * 4 <= 32, "four waves; a bit per element of a lane");
+  static_assert((TM > TN ? TM : TN) * LD_WIDE * 8 <= (long long)BUF_BYTES, "a tile's rows within the buffer");
+};
+
+// A lane's KL numbers of a piece: off is the first one's offset from the
+// uniform base x (BUF_BYTES: a row that is not there), left how many of them there are.
+template <bool KC, int KL>
+__device__ inline void short_load(const float2* __restrict__ x, long long ld, unsigned off, int left, float2 (&v)[KL]) {
+  const __amdgpu_buffer_rsrc_t rs =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<float2*>(x), 0, (int)BUF_BYTES, 0x00020000);
+#pragma unroll
+  for (int j = 0; j < KL; ++j)
+    v[j] = __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(
+                                          rs, (int)((j < left ? off : BUF_BYTES) + (KC ? 8u * j : 0u)), KC ? 0 : j * (int)ld * 8, 0));
+}
+template <int KL, class V>
+__device__ inline void short_terms(const float2 (&v)[KL], bool conj, V (&tr)[3], V (&ti)[3]) {
+  float re[KL], im[KL];
+#pragma unroll
+  for (int j = 0; j < KL; ++j) {
+    re[j] = v[j].x;
+    im[j] = v[j].y;
+  }
+  bf16_terms<3>(re, false, tr);
+  bf16_terms<3>(im, conj, ti);
+}
+
+template <class TL, bool TA, bool TB>
+__global__ __launch_bounds__(256, 3) void gemm_short_kernel(int M, int N, int K, float ar, float ai,
+                                                             const float* __restrict__ A, long long lda, long long sa,
+                                                             const float* __restrict__ B, long long ldb, long long sb,
+                                                             float br, float bi, float* __restrict__ C, long long ldc,
+                                                             long long sc, int conj) {
+  constexpr int KL = TL::KL, SI = TL::SI, NJ = TL::NJ;
+  using V = std::conditional_t<KL == 8, uint4, uint2>;
+  constexpr float down = 1.f / (UP3 * UP3);
+  const int lane = threadIdx.x & 63, lr = lane & 15, lk = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int m0 = blockIdx.y * TL::TM + wave / TL::WN * SI * 16, n0 = blockIdx.x * TL::TN + wave % TL::WN * NJ * 16;
+  if (m0 >= M || n0 >= N) return;
+  const int mr = M - m0, nr = min(N - n0, NJ * 16);   // rows and columns that are there
+  const float2* Ab = reinterpret_cast<const float2*>(A) + (long long)blockIdx.z * sa;
+  const float2* Bb = reinterpret_cast<const float2*>(B) + (long long)blockIdx.z * sb;
+  float2* Cb = reinterpret_cast<float2*>(C) + (long long)blockIdx.z * sc;
+  const int left = K - KL * lk;
+  const float2 *xa = TA ? Ab + m0 : Ab + (long long)m0 * lda, *xb = TB ? Bb + (long long)n0 * ldb : Bb + n0;
+  auto b_off = [&](int j) {
+    const int row = j * 16 + lr;
+    return row < nr ? (TB ? (unsigned)row * (unsigned)ldb + (unsigned)KL * lk : (unsigned)KL * lk * (unsigned)ldb + row) * 8u : BUF_BYTES;
+  };
+  float2 va[SI][KL], vb[2][KL];
+#pragma unroll
+  for (int i = 0; i < SI; ++i) {
+    const int row = i * 16 + lr;
+    const unsigned o = (TA ? (unsigned)KL * lk * (unsigned)lda + row : (unsigned)row * (unsigned)lda + (unsigned)KL * lk) * 8u;
+    short_load<!TA, KL>(xa, lda, row < mr ? o : BUF_BYTES, left, va[i]);
+  }
+  short_load<TB, KL>(xb, ldb, b_off(0), left, vb[0]);
+
+  // C from the wave's first element on; row r of a piece is r ldc further
+  const __amdgpu_buffer_rsrc_t rc =
+      __builtin_amdgcn_make_buffer_rsrc(Cb + ((long long)m0 * ldc + n0), 0, (int)BUF_BYTES, 0x00020000);
+  const int lc = (int)ldc * 8;
+  const bool has_beta = (br != 0.f) || (bi != 0.f), whole = mr >= SI * 16 && nr >= NJ * 16;
+  // the offset of element r = 0 of piece (i, j), past the buffer if it is not there
+  auto c_off = [&](int i, int j, int r) {
+    const unsigned o = (unsigned)((i * 16 + lk * 4) * (int)ldc + j * 16 + lr) * 8u;
+    return whole || (i * 16 + lk * 4 + r < mr && j * 16 + lr < nr) ? o : BUF_BYTES;
+  };
+  float2 old[SI][4];
+  auto load_c = [&](int j, float2 (&o)[SI][4]) {
+#pragma unroll
+    for (int i = 0; i < SI; ++i)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        o[i][r] = __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(rc, (int)c_off(i, j, r), r * lc, 0));
+  };
+
+  V a_r[SI][3], a_i[SI][3];
+#pragma unroll
+  for (int i = 0; i < SI; ++i) short_terms(va[i], conj & 1, a_r[i], a_i[i]);
+  unsigned again = 0;
+#pragma unroll
+  for (int j = 0; j < NJ; ++j) {
+    if (j * 16 >= nr) break;
+    if (j + 1 < NJ) short_load<TB, KL>(xb, ldb, b_off(j + 1), left, vb[(j + 1) & 1]);
+    if (has_beta) load_c(j, old);
+    V b_r[1][3], b_i[1][3];
+    short_terms(vb[j & 1], conj & 2, b_r[0], b_i[0]);
+    f4 cr[SI][1], ci[SI][1];
+    float t = 0.f;   // not a zero if one of the sums is not finite
+#pragma unroll
+    for (int i = 0; i < SI; ++i) {
+      cr[i][0] = ci[i][0] = f4{0, 0, 0, 0};
+      step_products<3, 1>(a_r[i], a_i[i], b_r, b_i, b_i, cr[i], ci[i]);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) t = fmaf(cr[i][0][r], 0.f, fmaf(ci[i][0][r], 0.f, t));
+    }
+    const bool some = __any(!(t == 0.f));
+#pragma unroll
+    for (int i = 0; i < SI; ++i)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const float xr = down * cr[i][0][r], xi = down * ci[i][0][r];
+        f2v o;
+        o.x = ar * xr - ai * xi;
+        o.y = ar * xi + ai * xr;
+        if (has_beta) {
+          const float2 c = old[i][r];
+          o.x += br * c.x - bi * c.y;
+          o.y += br * c.y + bi * c.x;
+        }
+        unsigned off = c_off(i, j, r);
+        if (some && !(__builtin_isfinite(xr) && __builtin_isfinite(xi))) {
+          if (off != BUF_BYTES) again |= 1u << ((i * NJ + j) * 4 + r);
+          off = BUF_BYTES;
+        }
+        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u2v, o), rc, (int)off, r * lc, 0);
+      }
+  }
+  KIter all;
+  all.iv = nullptr;
+  all.n = 1;
+  all.one = make_int2(0, K);
+  form_again<TA, TB, SI, NJ>(Again{Ab, Bb, Cb, lda, ldb, ldc, all, m0, n0, 0, min(SI * 16, mr), 0, nr, 0, 0, conj, ar, ai, br, bi},
+                             again);
 }
 
 // ---------------------------------------------------------------- term images
@@ -1215,6 +1366,36 @@ void launch_split_tile(dim3 grid, const Product<float>& p, float* C, long long l
   else go(std::true_type{});
 }
 
+// Which products are short.  Staged / short in us: 3752 x 3222 x 24 32.5 / 32, 8000 x
+// 5000 x 24 106 / 98, x 32 102 / 108, 2000 x 1500 x 32 13.3 / 15; but 700 x 700 x 32
+// 7.3 / 6.3, 14 x 304972 x 32 43 / 27.  Up to K = 16 a lane holds four k (v_mfma 16 x
+// 16 x 16: half the numbers to convert), from 17 on eight.
+inline bool short_product(const Product<float>& p) {
+  if (p.K < 1 || wide_ld(p.lda, p.ldb, LD_WIDE) || wide_ld(p.ldc, p.ldc, LD_WIDE)) return false;
+  return p.K <= 24 || (p.K <= 32 && (p.M <= 16 || p.N <= 16 || (double)p.M * p.N * p.batch < 1e6));
+}
+
+template <bool TA, bool TB> void launch_short(const Product<float>& p, int conj) {
+  auto go = [&](auto tl) {
+    using TL = decltype(tl);
+    const dim3 grid((p.N + TL::TN - 1) / TL::TN, (p.M + TL::TM - 1) / TL::TM, p.batch);
+    hipLaunchKernelGGL((gemm_short_kernel<TL, TA, TB>), grid, dim3(256), 0, p.s, p.M, p.N, p.K, p.ar, p.ai, p.A, p.lda,
+                       p.sa, p.B, p.ldb, p.sb, p.br, p.bi, p.C, p.ldc, p.sc, conj);
+  };
+  auto tile = [&](auto kl) {
+    constexpr int KL = decltype(kl)::value;
+    const double mn = (double)p.M * p.N * p.batch;
+    // narrow and low outputs: tiles as narrow or low
+    if (p.N <= 16) go(ShortTile<KL, 2, 1, 4, 1>{});
+    else if (p.M <= 16) go(ShortTile<KL, 1, 2, 1, 4>{});
+    else if (mn < 1e6) go(ShortTile<KL, 2, 1, 2, 2>{});
+    else if (mn < 2e7 || p.N < 1024) go(ShortTile<KL, 2, 2, 2, 2>{});
+    else go(ShortTile<KL, 2, 4, 2, 2>{});
+  };
+  if (p.K <= 16) tile(std::integral_constant<int, 4>{});
+  else tile(std::integral_constant<int, 8>{});
+}
+
 // kit null: the dense grid on tile `tile` of SplitTiles (S > 1: partial
 // products, plain); otherwise a block-sparse map of n_items items.
 template <int TERMS, bool TA, bool TB, int TAG>
@@ -1566,6 +1747,12 @@ void launch_gemm_mode(const Product<T>& p) {
     choose_direct_tile<TA, TB>(M, N, K, batch, S, &tile, &in_block);
     if (wide_ld(p.lda, p.ldb, LD_WIDE64)) in_block = false;
   } else {
+    if constexpr (TERMS == 3) {
+      if (short_product(p)) {
+        launch_short<TA, TB>(p, CONJ);
+        return;
+      }
+    }
     const double us = choose_split_tile<TERMS>(M, N, K, batch, p.ws_bytes, &tile, &S);
     // on term images where those take less time: large products, and long ones
     // whose few tiles repeat the conversion one after the other

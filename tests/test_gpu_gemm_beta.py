@@ -70,3 +70,36 @@ def test_elements_formed_again_are_added_to_c(env):
         a, b, y0 = (x.to(torch.complex128) for x in (A, B, Y0))
         bound = 12 * (K + 4) * 2.0 ** -24 * (_mag(a) @ _mag(b)) + 2.0 ** -20 * _mag(y0)
         assert bool(((Y.to(torch.complex128) - (a @ b - y0)).abs() <= bound).all())
+
+
+@pytest.mark.parametrize("M,N", [(1, 1), (16, 40), (40, 16), (31, 17), (70, 67), (129, 65)])
+def test_short_products_are_the_staged_ones(env, M, N):
+    # rows of C 2^20 apart take the staged kernel: the same terms and sums
+    T, torch, ctx = env
+    ld = 1 << 20
+    far = torch.empty(M, ld, dtype=torch.complex64, device="cuda")
+    for K in (1, 2, 3, 4, 5, 7, 8, 9, 15, 16, 17, 20, 23, 24, 25, 31, 32):
+        for opa, opb in ((0, 0), (1, 2), (2, 3), (3, 1)):
+            A, B, rand = _operands(torch, torch.complex64, opa, opb, M, N, K, 1, K)
+            Y0 = rand(M, N)
+            for alpha, beta in ((1.0, 0.0), (0.5 - 2j, 1j)):
+                Y, far[:, :N] = Y0.clone(), Y0
+                for out, ldc in ((Y, N), (far, ld)):
+                    T.tdvp_gemm(ctx, opa, opb, M, N, K, alpha, A, A.shape[2], 0, B, B.shape[2], 0, beta, out, ldc, 0, 1,
+                                prec="fp32")
+                assert torch.equal(Y, far[:, :N]), (K, opa, opb, beta)
+
+
+@pytest.mark.parametrize("M,N,batch", [(1000, 1001, 1), (4099, 4900, 1), (21, 2000, 30)])
+@pytest.mark.parametrize("K", [3, 16, 17, 24])
+def test_large_short_products(env, M, N, batch, K):
+    T, torch, ctx = env
+    for opa, opb in ((0, 0), (2, 1)):
+        A, B, rand = _operands(torch, torch.complex64, opa, opb, M, N, K, batch, K)
+        Y = torch.full((batch, M, N), float("nan"), dtype=torch.complex64, device="cuda")
+        T.tdvp_gemm(ctx, opa, opb, M, N, K, 1.0, A, A.shape[2], M * K, B, B.shape[2], K * N, 0.0, Y, N, M * N, batch,
+                    prec="fp32")
+        for b in range(batch):
+            a, c = (x.to(torch.complex128) for x in (_op(A[b], opa), _op(B[b], opb)))
+            bound = (C["fp32"] + (12 * K + 64) * 2.0 ** -24) * (_mag(a) @ _mag(c))
+            assert bool(((Y[b].to(torch.complex128) - a @ c).abs() <= bound).all())
