@@ -1648,6 +1648,17 @@ void choose_direct_tile(int M, int N, int K, int batch, int S, int* tile, bool* 
   double best = 1e29;
   *tile = 0;
   *in_block = false;
+  // Few steps and many outputs: what counts is how many waves a SIMD holds (four of
+  // tile 1, two of tiles 0 and 3), on the largest products the loads too, and whole
+  // lines of C where its rows are short.  Tile 0 / 1 / by the estimate / 64 x 64 tiles
+  // through LDS in us: 1537 x 1679 x 25 20.1 / 18.2 / 23.8 / 21.2, 1598 x 2987 x 22
+  // 27 / 23 / 29.5 / 30, 3500 x 3500 x 20 52 / 45 / - / 59, 5912 x 3503 x 21 102 / 114 /
+  // 103 / 112, 295595 x 45 x 18 with beta 118 / 151 / 135 / 114.
+  const double mn = (double)M * N * batch;
+  if (S == 1 && K <= 32 && mn >= 1e6) {
+    *tile = (mn <= 1.8e7 || mn * K <= 2.5e8) && (N <= 32 || N >= 64) ? 1 : 0;
+    return;
+  }
   for (int ib = 0; ib < 2; ++ib) {
     if (ib && S == 1) break;
     const double us[N_DIRECT] = {
