@@ -212,7 +212,8 @@ __device__ inline void diag_inverse_rows(const double2 (*tS)[CB + 1], double2 (*
   if constexpr (R < CB) {
     if (FULL || R < mi) {
       // the factor's wave always gets there, bad pivots or not; bounded all the same
-      while (__hip_atomic_load(&sh->done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) <= R && polls <= CSPIN) ++polls;
+      while (__hip_atomic_load(&sh->done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) <= R && polls <= CSPIN)
+        ++polls;
       asm volatile("" ::: "memory");
       double2 t{0.0, 0.0};
 #pragma unroll

@@ -674,9 +674,10 @@ __device__ inline void short_load(const float2* __restrict__ x, long long ld, un
   const __amdgpu_buffer_rsrc_t rs =
       __builtin_amdgcn_make_buffer_rsrc(const_cast<float2*>(x), 0, (int)BUF_BYTES, 0x00020000);
 #pragma unroll
-  for (int j = 0; j < KL; ++j)
-    v[j] = __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(
-                                          rs, (int)((j < left ? off : BUF_BYTES) + (KC ? 8u * j : 0u)), KC ? 0 : j * (int)ld * 8, 0));
+  for (int j = 0; j < KL; ++j) {
+    const unsigned o = (j < left ? off : BUF_BYTES) + (KC ? 8u * j : 0u);
+    v[j] = __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(rs, (int)o, KC ? 0 : j * (int)ld * 8, 0));
+  }
 }
 template <int KL, class V>
 __device__ inline void short_terms(const float2 (&v)[KL], bool conj, V (&tr)[3], V (&ti)[3]) {
@@ -708,17 +709,20 @@ __global__ __launch_bounds__(256, 3) void gemm_short_kernel(int M, int N, int K,
   const float2* Bb = reinterpret_cast<const float2*>(B) + (long long)blockIdx.z * sb;
   float2* Cb = reinterpret_cast<float2*>(C) + (long long)blockIdx.z * sc;
   const int left = K - KL * lk;
+  // the lane's first entry of a row, from the operand's first row on
+  auto at = [&](bool kc, long long ld, int row) {
+    return (kc ? (unsigned)row * (unsigned)ld + (unsigned)(KL * lk) : (unsigned)(KL * lk) * (unsigned)ld + row) * 8u;
+  };
   const float2 *xa = TA ? Ab + m0 : Ab + (long long)m0 * lda, *xb = TB ? Bb + (long long)n0 * ldb : Bb + n0;
   auto b_off = [&](int j) {
     const int row = j * 16 + lr;
-    return row < nr ? (TB ? (unsigned)row * (unsigned)ldb + (unsigned)KL * lk : (unsigned)KL * lk * (unsigned)ldb + row) * 8u : BUF_BYTES;
+    return row < nr ? at(TB, ldb, row) : BUF_BYTES;
   };
   float2 va[SI][KL], vb[2][KL];
 #pragma unroll
   for (int i = 0; i < SI; ++i) {
     const int row = i * 16 + lr;
-    const unsigned o = (TA ? (unsigned)KL * lk * (unsigned)lda + row : (unsigned)row * (unsigned)lda + (unsigned)KL * lk) * 8u;
-    short_load<!TA, KL>(xa, lda, row < mr ? o : BUF_BYTES, left, va[i]);
+    short_load<!TA, KL>(xa, lda, row < mr ? at(!TA, lda, row) : BUF_BYTES, left, va[i]);
   }
   short_load<TB, KL>(xb, ldb, b_off(0), left, vb[0]);
 
@@ -727,7 +731,7 @@ __global__ __launch_bounds__(256, 3) void gemm_short_kernel(int M, int N, int K,
       __builtin_amdgcn_make_buffer_rsrc(Cb + ((long long)m0 * ldc + n0), 0, (int)BUF_BYTES, 0x00020000);
   const int lc = (int)ldc * 8;
   const bool has_beta = (br != 0.f) || (bi != 0.f), whole = mr >= SI * 16 && nr >= NJ * 16;
-  // the offset of element r = 0 of piece (i, j), past the buffer if it is not there
+  // the offset of row r = 0 of piece (i, j), past the buffer if element r is not there
   auto c_off = [&](int i, int j, int r) {
     const unsigned o = (unsigned)((i * 16 + lk * 4) * (int)ldc + j * 16 + lr) * 8u;
     return whole || (i * 16 + lk * 4 + r < mr && j * 16 + lr < nr) ? o : BUF_BYTES;
@@ -787,8 +791,8 @@ __global__ __launch_bounds__(256, 3) void gemm_short_kernel(int M, int N, int K,
   all.iv = nullptr;
   all.n = 1;
   all.one = make_int2(0, K);
-  form_again<TA, TB, SI, NJ>(Again{Ab, Bb, Cb, lda, ldb, ldc, all, m0, n0, 0, min(SI * 16, mr), 0, nr, 0, 0, conj, ar, ai, br, bi},
-                             again);
+  form_again<TA, TB, SI, NJ>(
+      Again{Ab, Bb, Cb, lda, ldb, ldc, all, m0, n0, 0, min(SI * 16, mr), 0, nr, 0, 0, conj, ar, ai, br, bi}, again);
 }
 
 // ---------------------------------------------------------------- term images
@@ -1358,9 +1362,9 @@ template <class TL, bool TA, bool TB, int TAG>
 void launch_split_tile(dim3 grid, const Product<float>& p, float* C, long long ldc, long long sc, bool plain, int S,
                        int Kc, long long sps, const int4* kit, const int2* kiv, int conj) {
   auto go = [&](auto beta) {
-    hipLaunchKernelGGL((gemm_split_kernel<TL, TA, TB, decltype(beta)::value, TAG>), grid, dim3(TL::NTH), 0, p.s, p.M, p.N,
-                       p.K, plain ? 1.f : p.ar, plain ? 0.f : p.ai, p.A, p.lda, p.sa, p.B, p.ldb, p.sb, p.br, p.bi, C, ldc,
-                       sc, S, Kc, sps, kit, kiv, conj);
+    hipLaunchKernelGGL((gemm_split_kernel<TL, TA, TB, decltype(beta)::value, TAG>), grid, dim3(TL::NTH), 0, p.s, p.M,
+                       p.N, p.K, plain ? 1.f : p.ar, plain ? 0.f : p.ai, p.A, p.lda, p.sa, p.B, p.ldb, p.sb,
+                       plain ? 0.f : p.br, plain ? 0.f : p.bi, C, ldc, sc, S, Kc, sps, kit, kiv, conj);
   };
   if (plain || (p.br == 0.f && p.bi == 0.f)) go(std::false_type{});
   else go(std::true_type{});
@@ -1567,15 +1571,13 @@ void launch_images(const Product<float>& p, bool ta, bool tb, int conj, const Im
         float* C = p.C + 2 * (m0 * p.ldc + n0);
         auto product = [&](auto tl) {
           using TL = decltype(tl);
-          if (S > 1)
-            hipLaunchKernelGGL((gemm_image_kernel<TL, false>), grid, dim3(TL::NTH), 0, p.s, M, N, K, 1.f, 0.f, ia, ib, nkc,
-                               0.f, 0.f, part, (long long)N, S, Kc, mn);
-          else if (br == 0.f && bi == 0.f)
-            hipLaunchKernelGGL((gemm_image_kernel<TL, false>), grid, dim3(TL::NTH), 0, p.s, M, N, K, p.ar, p.ai, ia, ib, nkc,
-                               0.f, 0.f, C, p.ldc, 1, Kc, 0LL);
-          else
-            hipLaunchKernelGGL((gemm_image_kernel<TL, true>), grid, dim3(TL::NTH), 0, p.s, M, N, K, p.ar, p.ai, ia, ib, nkc,
-                               br, bi, C, p.ldc, 1, Kc, 0LL);
+          auto go = [&](auto beta, float alr, float ali, float* out, long long ldo, int parts, long long sps) {
+            hipLaunchKernelGGL((gemm_image_kernel<TL, decltype(beta)::value>), grid, dim3(TL::NTH), 0, p.s, M, N, K, alr,
+                               ali, ia, ib, nkc, br, bi, out, ldo, parts, Kc, sps);
+          };
+          if (S > 1) go(std::false_type{}, 1.f, 0.f, part, N, S, mn);
+          else if (br == 0.f && bi == 0.f) go(std::false_type{}, p.ar, p.ai, C, p.ldc, 1, 0);
+          else go(std::true_type{}, p.ar, p.ai, C, p.ldc, 1, 0);
         };
         if (g.tile == 0) product(typename TS::T0{});
         else product(typename TS::T1{});
@@ -1688,8 +1690,8 @@ void launch_direct_tile(const Product<double>& p, int n_items, double* C, long l
                                     (int)lds));
     }
     hipLaunchKernelGGL(kernel, grid, dim3(TL::WM * TL::WN * parts * 64), lds, p.s, p.M, p.N, p.K, plain ? 1.0 : p.ar,
-                       plain ? 0.0 : p.ai, p.A, p.lda, p.sa, p.B, p.ldb, p.sb, p.br, p.bi, C, ldc, sc, S, Kc, sps, kit, kiv,
-                       conj);
+                       plain ? 0.0 : p.ai, p.A, p.lda, p.sa, p.B, p.ldb, p.sb, plain ? 0.0 : p.br,
+                       plain ? 0.0 : p.bi, C, ldc, sc, S, Kc, sps, kit, kiv, conj);
   };
   if (plain || (p.br == 0.0 && p.bi == 0.0)) go(std::false_type{});
   else go(std::true_type{});

@@ -65,6 +65,8 @@ def test_elements_formed_again_are_added_to_c(env):
     for M, N, K in ((70, 67, 5), (70, 67, 45), (300, 20, 2500)):
         A, B, rand = _operands(torch, torch.complex64, 0, 0, M, N, K, 1, K)
         A, B, Y0 = A[0] * 2.0 ** 50, B[0] * 2.0 ** 54, rand(M, N) * 2.0 ** 104
+        # what a product leaves in the scratch of its K parts is not added to the next one's
+        T.tdvp_gemm(ctx, 0, 0, M, N, K, 1.0, A * 2.0 ** 12, K, 0, B, N, 0, 0.0, torch.empty_like(Y0), N, 0, 1, prec="fp32")
         Y = Y0.clone()
         T.tdvp_gemm(ctx, 0, 0, M, N, K, 1.0, A, K, 0, B, N, 0, -1.0, Y, N, 0, 1, prec="fp32")
         a, b, y0 = (x.to(torch.complex128) for x in (A, B, Y0))
