@@ -582,12 +582,21 @@ def _w_host(W: np.ndarray):
     return Wc, Wc.view(np.float64).ctypes.data_as(C.POINTER(C.c_double))
 
 
+def _done_for(ctx: Context, workspace):
+    """A call with a workspace returns before its kernels have run, on the
+    context's stream.  A caller on another stream may read the result, or drop
+    a tensor, at once: its call ends with them."""
+    if workspace is not None and ctx._torch.cuda.current_stream(ctx.device) != ctx.stream:
+        tdvp_synchronize(ctx)
+
+
 def tdvp_heff_apply(ctx: Context, W: np.ndarray, L, Rt, Cin, Y, workspace=None, prec: Optional[str] = None):
     ml, wl, _ = L.shape
     wr, mr, _ = Rt.shape
     Wc, wp = _w_host(W)
     ctx.check(ctx.lib.tdvp_heff_apply(ctx.h, _prec_of(L, prec), ml, wl, wr, mr, wp, _tp(L), _tp(Rt), _tp(Cin), _tp(Y),
                                       _tp(workspace)), "tdvp_heff_apply")
+    _done_for(ctx, workspace)
 
 
 def tdvp_heff_apply_u1(ctx: Context, W: np.ndarray, L, Rt, Cin, Y, ql, qr, qwl, qwr, prec: Optional[str] = None):
@@ -635,6 +644,7 @@ def tdvp_env_left(ctx: Context, W: np.ndarray, L, A, Lout, workspace=None, prec:
     Wc, wp = _w_host(W)
     ctx.check(ctx.lib.tdvp_env_left(ctx.h, _prec_of(L, prec), ml, wl, wr, mr, wp, _tp(L), _tp(A), _tp(Lout),
                                     _tp(workspace)), "tdvp_env_left")
+    _done_for(ctx, workspace)
 
 
 def tdvp_env_right(ctx: Context, W: np.ndarray, Rt, B, Rout, workspace=None, prec: Optional[str] = None):
@@ -644,3 +654,4 @@ def tdvp_env_right(ctx: Context, W: np.ndarray, Rt, B, Rout, workspace=None, pre
     Wc, wp = _w_host(W)
     ctx.check(ctx.lib.tdvp_env_right(ctx.h, _prec_of(Rt, prec), ml, wl, wr, mr, wp, _tp(Rt), _tp(B), _tp(Rout),
                                      _tp(workspace)), "tdvp_env_right")
+    _done_for(ctx, workspace)
