@@ -2328,7 +2328,6 @@ __global__ void zscatter_kernel(double2* __restrict__ dst, long long ldd, const 
   dst[r * ldd + c] = src[i * lds + j];
 }
 
-// dst[j] = H[idx[j]*n + idx[j]]; rows[pos[j]*n + idx[j]] = 1 (unit eigenvector of a 1 x 1 block)
 template <typename D, typename S>
 __device__ inline D cconv(S v) {
   D d;
@@ -2370,6 +2369,7 @@ __global__ void zrandom_blocks_kernel(double2* __restrict__ E, int R, int C, con
   E[idx] = v;
 }
 
+// dst[j] = H[idx[j]*n + idx[j]]; rows[pos[j]*n + idx[j]] = 1 (unit eigenvector of a 1 x 1 block)
 __global__ void zunit_blocks_kernel(double2* __restrict__ dst, const double2* __restrict__ H, long long n,
                                     const int* __restrict__ idx, const int* __restrict__ pos, int cnt,
                                     double2* __restrict__ rows) {
