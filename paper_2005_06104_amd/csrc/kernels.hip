@@ -602,6 +602,10 @@ __global__ __launch_bounds__(TL::NTH, TL::OCC) void gemm_split_kernel(
     kend = nkend;
   }
 
+  // No load is in flight any more, which the compiler sees only here: it waits
+  // for one between the stores, and so for the stores, otherwise (A k-contiguous,
+  // B transposed, 64 x 64 x 40: 8.3 us, so 7.2).
+  __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0)
   const float2* c_some = Cb + ((long long)(m0 + job.r0) * ldc + (n0 + job.c0));   // an element that is there
   auto put = [&](float2* c, float xr, float xi, float2 old) {
     float2 o;
