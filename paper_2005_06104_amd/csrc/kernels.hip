@@ -1659,10 +1659,18 @@ void choose_direct_tile(int M, int N, int K, int batch, int S, int* tile, bool* 
   // lines of C where its rows are short.  Tile 0 / 1 / by the estimate / 64 x 64 tiles
   // through LDS in us: 1537 x 1679 x 25 20.1 / 18.2 / 23.8 / 21.2, 1598 x 2987 x 22
   // 27 / 23 / 29.5 / 30, 3500 x 3500 x 20 52 / 45 / - / 59, 5912 x 3503 x 21 102 / 114 /
-  // 103 / 112, 295595 x 45 x 18 with beta 118 / 151 / 135 / 114.
+  // 103 / 112, 295595 x 45 x 18 with beta 118 / 151 / 135 / 114.  Rows of C of two
+  // tiles of 32 lose their lines only where the two run on different XCDs, not where
+  // the tiles are dealt in bands (a multiple of eight, see tile_job), with beta: 5219 x
+  // 56 x 12 (30) 51.3 / 48.8 / - / 50, 102400 x 50 x 30 50 / 40 / - / 48; 6250 tiles of
+  // 200000 x 45 x 12 56 / 68 / - / 54; nor past the 256 MB memory-side cache, 204800 x
+  // 60 x 30 112 / 119 / - / 103.
   const double mn = (double)M * N * batch;
   if (S == 1 && K <= 32 && mn >= 1e6) {
-    *tile = (mn <= 1.8e7 || mn * K <= 2.5e8) && (N <= 32 || N >= 64) ? 1 : 0;
+    const long long tiles = (long long)((M + Direct1::TM - 1) / Direct1::TM) * ((N + Direct1::TN - 1) / Direct1::TN) * batch;
+    const double bytes = (mn + ((double)M + N) * K * batch) * sizeof(double2);
+    const bool bands = tiles % 8 == 0 && bytes <= 256e6;
+    *tile = (mn <= 1.8e7 || mn * K <= 2.5e8) && (N <= 32 || N >= 64 || bands) ? 1 : 0;
     return;
   }
   for (int ib = 0; ib < 2; ++ib) {
