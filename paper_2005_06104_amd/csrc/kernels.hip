@@ -1628,11 +1628,12 @@ template <class TL, bool TA, bool TB> double direct_cost(int M, int N, int K, in
   const double mn = (double)M * N * sizeof(double2);
   const double blocks = (double)((M + TL::TM - 1) / TL::TM) * ((N + TL::TN - 1) / TL::TN) * (in_block ? 1 : S) * batch;
   const double per_cu = std::ceil(blocks / 256.0), waves = TL::WM * TL::WN * (in_block ? S : 1);
-  // a CU holds eight blocks of one 32 x 32 wave, and up to four more run after them at
-  // the pace of a lone wave: 474 x 5086 x 198 91 us, four waves a block 69 (64 x 64
-  // tiles through LDS 72), 2235 x 966 x 371 152 / 118 (128); with two full rounds of
-  // eight the blocks of one wave are ahead again, 3148 x 1307 x 104 61 / 71
-  if (S == 1 && TL::PARTS > 1 && TL::SI * TL::SJ == 4 && per_cu > 8.0 && per_cu <= 12.0) return 1e30;
+  // a CU holds eight blocks of one 32 x 32 wave, and one to four after a full round
+  // run at the pace of a lone wave: 474 x 5086 x 198 (ten a CU) 91 us, four waves a block
+  // 69 (64 x 64 tiles through LDS 72), 2235 x 966 x 371 152 / 118 (128); over random
+  // shapes of 9 to 12, 17 to 20 and 25 to 28 a CU 1.10 to 1.12 times the time, of 13 to
+  // 16 and 37 to 40 0.99 to 1.01 (3148 x 1307 x 104 61 / 71)
+  if (S == 1 && TL::PARTS > 1 && TL::SI * TL::SJ == 4 && per_cu > 8.0 && (int)(per_cu - 1.0) % 8 < 4) return 1e30;
   const double steps = std::ceil(std::ceil((double)K / S) / 4);
   double per_simd = std::ceil(per_cu * waves / 4.0);
   if (waves == 2.0 || waves == 3.0) per_simd = std::max(per_simd, 2.0);
